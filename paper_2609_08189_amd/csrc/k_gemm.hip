@@ -16,7 +16,7 @@
 // dispatch) owns a contiguous run of a grouped tile order: the tiles it runs at
 // once share a few row panels and a few weight panels in its L2.
 //
-// f32 path: a plain LDS-tiled VALU GEMM with full bounds checks (small shapes).
+// f32 path: small tiles on the fp32 matrix cores with full bounds checks (narrow shapes).
 #include <limits.h>
 
 #include <algorithm>
@@ -1133,81 +1133,139 @@ hipError_t run_big(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_count
 }
 
 // ---------------------------------------------------------------------------
-// fp32 VALU GEMM (64 x 64 tile, 4 x 4 outputs per thread, full bounds checks)
+// fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4f32: products and sums in fp32)
+//
+// A workgroup of four waves computes a 16 R x 16 R output tile; the waves take every fourth
+// 16-deep k-step and their partial tiles are added in wave order through LDS.  The fragments come
+// straight from memory: lane l holds k = 4 (l >> 4) .. + 3 of row l & 15 of a k-step as one 16-byte
+// load, and element e of it feeds MFMA e of the step (both operands take the k in that order, so
+// every k meets its own).  A batch of U steps is loaded before its products.
+// The fp32 shapes are narrow, so their launches are short of workgroups and bound by the chain of
+// dependent loads, not by the arithmetic: a 64 x 64 LDS tile on the VALU walked K = 688 in 43
+// dependent steps on 4 workgroups at 64 rows.  Measured against it: the 4-layer stack of
+// d = 256, d_ff = 688 at 64 tokens 1318 -> 508 us, 2 layers of d = 2048, d_ff = 5632 at 20 tokens
+// 3460 -> 407 us and at 2048 tokens 6489 -> 4540 us, so it serves every size.
 // ---------------------------------------------------------------------------
 
-template <bool DUAL, class Epi>
+// elements k .. k + 3 of a row, zero past K; VEC: K and both row pitches are multiples of four
+template <bool VEC>
+__device__ __forceinline__ f32x4 f32_frag(const float* row, int k, int K) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (k < K) v = *reinterpret_cast<const f32x4*>(row + k);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < K) v[e] = row[k + e];
+  }
+  return v;
+}
+
+template <bool DUAL, int R, bool VEC, class Epi>
 __global__ __launch_bounds__(256) void f32_gemm(ARows<float> A, BRows<float> B, Epi epi,
                                                const int* __restrict__ m_count, int M_fixed,
                                                int N, int K) {
-  __shared__ float As[16][68];
-  __shared__ float Bs[16][68];
-  __shared__ float Us[DUAL ? 16 : 1][68];
+  constexpr int BT = 16 * R;                   // rows and columns of the tile
+  constexpr int U = R == 1 ? 8 : 4;            // k-steps per batch of loads
+  constexpr int RP = BT + 1;
+  __shared__ float red[DUAL ? 2 : 1][4][BT][RP];
   const int M = m_count ? *m_count : M_fixed;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  const int m0 = blockIdx.x * BT, n0 = blockIdx.y * BT;
   if (m0 >= M) return;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4], acu[4][4];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int r16 = lane & 15, k4 = 4 * (lane >> 4);
+  // rows and columns past the end repeat the last one: their results are not stored
+  const float *ar[R], *br[R], *ur[R];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = acu[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int e = threadIdx.x; e < 64 * 16; e += 256) {
-      const int r = e >> 4, kk = e & 15, k = k0 + kk;
-      const int m = m0 + r, n = n0 + r;
-      As[kk][r] = (m < M && k < K) ? A.row(m)[k] : 0.f;
-      if (DUAL) {
-        Bs[kk][r] = (n < N && k < K) ? B.gate_row(n)[k] : 0.f;
-        Us[kk][r] = (n < N && k < K) ? B.up_row(n)[k] : 0.f;
-      } else {
-        Bs[kk][r] = (n < N && k < K) ? B.row(n)[k] : 0.f;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4], u[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = As[kk][ty * 4 + i];
-        b[i] = Bs[kk][tx * 4 + i];
-        if (DUAL) u[i] = Us[kk][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-          if (DUAL) acu[i][j] = fmaf(a[i], u[j], acu[i][j]);
-        }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      if constexpr (DUAL) {
-        epi.store2(m, n, acc[i][j], acu[i][j]);
-      } else {
-        epi.store(m, n, acc[i][j]);
-      }
+  for (int i = 0; i < R; ++i) {
+    ar[i] = A.row(min(m0 + 16 * i + r16, M - 1));
+    const int n = min(n0 + 16 * i + r16, N - 1);
+    if constexpr (DUAL) {
+      br[i] = B.gate_row(n);
+      ur[i] = B.up_row(n);
+    } else {
+      br[i] = B.row(n);
     }
   }
+  f32x4 acc[R][R], acu[R][R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j) acc[i][j] = acu[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nks = (K + 15) / 16;
+  for (int s0 = wave; s0 < nks; s0 += 4 * U) {
+    f32x4 fa[U][R], fb[U][R], fu[U][R];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = 16 * (s0 + 4 * u) + k4;    // past K in the last batch: zeros
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        fa[u][i] = f32_frag<VEC>(ar[i], k, K);
+        fb[u][i] = f32_frag<VEC>(br[i], k, K);
+        if constexpr (DUAL) fu[u][i] = f32_frag<VEC>(ur[i], k, K);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][i][e], fb[u][j][e], acc[i][j], 0, 0, 0);
+            if constexpr (DUAL)
+              acu[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][i][e], fu[u][j][e], acu[i][j], 0, 0, 0);
+          }
+  }
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        red[0][wave][16 * i + k4 + r][16 * j + r16] = acc[i][j][r];
+        if constexpr (DUAL) red[1][wave][16 * i + k4 + r][16 * j + r16] = acu[i][j][r];
+      }
+  __syncthreads();
+  for (int e = threadIdx.x; e < BT * BT; e += 256) {
+    const int i = e / BT, c = e % BT;
+    if (m0 + i >= M || n0 + c >= N) continue;
+    float v = 0.f, w = 0.f;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      v += red[0][g][i][c];
+      if constexpr (DUAL) w += red[1][g][i][c];
+    }
+    if constexpr (DUAL)
+      epi.store2(m0 + i, n0 + c, v, w);
+    else
+      epi.store(m0 + i, n0 + c, v);
+  }
+}
+
+template <bool DUAL, int R, class Epi>
+hipError_t run_f32_r(ARows<float> A, BRows<float> B, Epi epi, const int* m_count, int M_max, int N,
+                     int K, bool vec, hipStream_t s) {
+  const dim3 grid((M_max + 16 * R - 1) / (16 * R), (N + 16 * R - 1) / (16 * R));
+  if (vec)
+    f32_gemm<DUAL, R, true, Epi><<<grid, 256, 0, s>>>(A, B, epi, m_count, M_max, N, K);
+  else
+    f32_gemm<DUAL, R, false, Epi><<<grid, 256, 0, s>>>(A, B, epi, m_count, M_max, N, K);
+  return hipGetLastError();
 }
 
 template <bool DUAL, class Epi>
 hipError_t run_f32(ARows<float> A, BRows<float> B, Epi epi, const int* m_count, int M_max, int N,
                    int K, hipStream_t s) {
   if (M_max <= 0 || N <= 0) return hipSuccess;
-  dim3 grid((N + 63) / 64, (M_max + 63) / 64);
-  f32_gemm<DUAL, Epi><<<grid, 256, 0, s>>>(A, B, epi, m_count, M_max, N, K);
-  return hipGetLastError();
+  const auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+  const bool vec = K % 4 == 0 && A.ld % 4 == 0 && B.ld % 4 == 0 && al(A.base) && al(B.b0) && al(B.b1);
+  // 32 x 32 tiles halve the operand bytes per product once they fill the CUs
+  const long long t32 = static_cast<long long>((M_max + 31) / 32) * ((N + 31) / 32);
+  if (t32 >= 2 * kCUs) return run_f32_r<DUAL, 2>(A, B, epi, m_count, M_max, N, K, vec, s);
+  return run_f32_r<DUAL, 1>(A, B, epi, m_count, M_max, N, K, vec, s);
 }
 
 // ---------------------------------------------------------------------------

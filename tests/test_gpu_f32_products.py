@@ -1,0 +1,21 @@
+"""fp32 products at the edges of their tiles: K and N off the 16-deep steps and 16- or 32-wide tiles, row pitches
+that are not multiples of four (no 16-byte loads), one row, and enough rows for the 32 x 32 tiles."""
+import pytest
+
+from paper_2609_08189_amd import synth
+from tests.parity import check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,d_ff,d_r", [(1, 128, 5, 1), (17, 256, 691, 15), (33, 256, 688, 16), (700, 256, 2101, 15),
+                                          (700, 256, 2100, 20)])
+def test_f32_layer_products(T, d, d_ff, d_r):
+    """Against the oracle at fp32's 1e-4 (sums of at most 2101 products: about 1e-6)."""
+    from paper_2609_08189_amd.device import DeviceProblem
+    w = synth.Workload("f32_products", "f32", d=d, d_ff=d_ff, d_r=d_r, L_R=4, d_m=32, T=T, mode="budget", budget=0.27)
+    print(f"case T={T} d={d} d_ff={d_ff} d_r={d_r}", flush=True)
+    prob = synth.make_problem(w, seed=21, layer_j=3)
+    dp = DeviceProblem(prob)
+    dp.run_layer(3)
+    check_layer(prob, dp.results(), 3)
