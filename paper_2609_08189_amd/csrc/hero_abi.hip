@@ -394,21 +394,29 @@ int run_layer(const LayerCall& c) {
     ra.cvec = ra.hs + t * D.d_head;
     ra.bvec = ra.cvec + t * D.d_m;
   }
-  e = timed(HERO_K_ROUTER_PRE, st, [&] { return launch_router_pre(ra, st); });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-  // the ablations without memory access leave S, zeta (or the stored pairs) untouched
-  if (!(ra.abl & (HERO_ABL_NO_MEMREAD | HERO_ABL_NO_HISTORY))) {
-    e = timed(HERO_K_ROUTER_MEM, st, [&] {
-      return c.hist ? launch_router_mem_hist(ra, st) : launch_router_mem(ra, st);
-    });
+  const auto nothing = [] { return hipSuccess; };
+  if (router_token_fits(D.dtype, T, D.d_m, D.d_s, D.d_h, D.d_a, D.d_e, D.d_p, D.d_head)) {
+    // few tokens: one launch, timed as the memory pass
+    ra.c_read = c.c_read;
+    e = timed(HERO_K_ROUTER_PRE, st, nothing);
+    if (e == hipSuccess)
+      e = timed(HERO_K_ROUTER_MEM, st, [&] { return launch_router_token(ra, c.hist != nullptr, st); });
+    if (e == hipSuccess) e = timed(HERO_K_ROUTER_POST, st, nothing);
     if (e != hipSuccess) return HERO_E_LAUNCH;
-    if (c.c_read &&
-        hipMemcpyAsync(c.c_read, ra.cvec, static_cast<size_t>(T) * D.d_m * sizeof(float), hipMemcpyDeviceToDevice,
-                       st) != hipSuccess)
-      return HERO_E_LAUNCH;
+  } else {
+    if (c.c_read) ra.cvec = c.c_read;
+    e = timed(HERO_K_ROUTER_PRE, st, [&] { return launch_router_pre(ra, st); });
+    if (e != hipSuccess) return HERO_E_LAUNCH;
+    // the ablations without memory access leave S, zeta (or the stored pairs) untouched
+    if (!(ra.abl & (HERO_ABL_NO_MEMREAD | HERO_ABL_NO_HISTORY))) {
+      e = timed(HERO_K_ROUTER_MEM, st, [&] {
+        return c.hist ? launch_router_mem_hist(ra, st) : launch_router_mem(ra, st);
+      });
+      if (e != hipSuccess) return HERO_E_LAUNCH;
+    }
+    e = timed(HERO_K_ROUTER_POST, st, [&] { return launch_router_post(ra, st); });
+    if (e != hipSuccess) return HERO_E_LAUNCH;
   }
-  e = timed(HERO_K_ROUTER_POST, st, [&] { return launch_router_post(ra, st); });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
 
   SelectArgs sa{};
   sa.logit = logit;

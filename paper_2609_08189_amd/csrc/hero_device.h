@@ -76,10 +76,46 @@ __device__ __forceinline__ void st8(float* p, const float* v) {
   *reinterpret_cast<f32x4*>(p + 4) = b;
 }
 
+// Eight consecutive elements as loaded (bf16 stays packed: 4 registers per chunk).
+template <typename T> struct Raw8;
+template <> struct Raw8<bf16_t> {
+  u32x4 v;
+  __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const u32x4*>(p); }
+  __device__ __forceinline__ void zero() { v = u32x4{0u, 0u, 0u, 0u}; }
+  __device__ __forceinline__ float operator[](int i) const {
+    const uint32_t w = v[i >> 1];
+    return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
+  }
+};
+template <> struct Raw8<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const f32x4*>(p);
+    b = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  __device__ __forceinline__ void zero() { a = b = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ float operator[](int i) const { return i < 4 ? a[i] : b[i - 4]; }
+};
+
 __device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + expf(-x)); }
 __device__ __forceinline__ float siluf_(float x) { return x / (1.0f + expf(-x)); }
 // ELU(x) + 1, with exp(x) evaluated directly below zero.
 __device__ __forceinline__ float phif_(float x) { return x > 0.0f ? x + 1.0f : expf(x); }
+
+// Sum over the aligned group of PI lanes a lane is in (a power of two up to 32), left in every lane
+// of the group: DPP moves up to 16 lanes (quad swaps, then mirrors of rows whose quads agree).
+template <int PI>
+__device__ __forceinline__ float group_sum(float v) {
+  static_assert(PI >= 1 && PI <= 32 && (PI & (PI - 1)) == 0, "lanes");
+#define HERO_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctrl, 0xf, 0xf, true))
+  if constexpr (PI >= 2) HERO_DPP_ADD(0xB1);    // lanes 1 0 3 2 of each quad
+  if constexpr (PI >= 4) HERO_DPP_ADD(0x4E);    // lanes 2 3 0 1
+  if constexpr (PI >= 8) HERO_DPP_ADD(0x141);   // half rows mirrored
+  if constexpr (PI >= 16) HERO_DPP_ADD(0x140);  // rows mirrored
+#undef HERO_DPP_ADD
+  if constexpr (PI >= 32) v += __shfl_xor(v, 16, kWave);
+  return v;
+}
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -51,6 +51,8 @@ struct RouterTailArgs {
   // w_{j,i} of the j-1 stored pairs (hw[i] for entry i, i.e. routed layer i+1)
   float* kv;
   float hw[64];
+  // router_token: where the memory read c goes as well, or null (the three kernels write cvec)
+  float* c_read;
 };
 size_t router_scratch_floats(int d_m, int d_head, int T);
 // router state, q/k/v, W_n s, the s part of the history head, local head
@@ -59,6 +61,10 @@ hipError_t launch_router_pre(const RouterTailArgs& a, hipStream_t s);
 hipError_t launch_router_mem(const RouterTailArgs& a, hipStream_t s);
 // nu, history head, p, m, logit and gate
 hipError_t launch_router_post(const RouterTailArgs& a, hipStream_t s);
+// the three kernels in one, a workgroup per token, for calls of few tokens and the router widths
+// it covers (hist: the memory in depth-history form); no intermediates in memory
+bool router_token_fits(int dtype, int T, int d_m, int d_s, int d_h, int d_a, int d_e, int d_p, int d_head);
+hipError_t launch_router_token(const RouterTailArgs& a, bool hist, hipStream_t s);
 // memory read as attention over the stored pairs, then the layer's own pair appended
 hipError_t launch_router_mem_hist(const RouterTailArgs& a, hipStream_t s);
 // matrix-form state S, zeta after n layers from a history (weights w[i] for entry i)

@@ -1,4 +1,5 @@
-// Router of one routed layer after the two large projections (Sec. 3.2), as three kernels:
+// Router of one routed layer after the two large projections (Sec. 3.2), as three kernels (calls
+// of few tokens run them as one, router_token):
 //
 //   router_pre   (8 tokens per workgroup, reuses each weight across them)
 //     z^h = W_hu SiLU(inv_rms * W_hd hbar)                       hidden encoder (unit-gain RMSNorm)
@@ -991,6 +992,402 @@ __global__ __launch_bounds__(NT) void history_state_kernel(const float* __restri
   }
 }
 
+// ---------------------------------------------------------------------------
+// router_token: the whole router after its two large projections in one launch, one token per
+// workgroup of 512 threads, for calls of few tokens (a decode step).
+//
+// With few tokens each of the three kernels above is a chain of latencies on a handful of
+// workgroups: a round trip to HBM for its inputs (the router's weights have left the caches: the
+// FFN weights of a layer stream through them between two layers), a few barriers, a launch.
+// Here every weight of the router and the token's memory are loaded at the start, in one round
+// trip, into registers (PRE: the widths where they fit); what follows works from LDS between
+// barriers.  A matrix [O][I] is spread over the threads in pieces of eight inputs: thread t holds
+// piece t mod PI (PI >= I / 8, a power of two) of rows t / PI, t / PI + 512 / PI, ..., so it needs
+// the same eight inputs for every row, and a row's sum is formed over PI neighbouring lanes.
+// Weights are widened to fp32 and every product and sum is fp32.
+// ---------------------------------------------------------------------------
+constexpr int NTT = 512;                 // threads per token
+constexpr int NWT = NTT / kWave;
+constexpr int kTokenMaxS = 64;           // widths the thread layout covers: d_s, d_h, d_a
+constexpr int kTokenMaxP = 128;          // d_p
+constexpr int kHistMax = 64;             // stored pairs
+// Most tokens of a call: one round of workgroups with bf16 weights, eight with fp32, whose three
+// kernels are VALU chains.  Measured against the three kernels, a layer of d = 4096, d_ff = 14336,
+// d_m = 128 (bf16): 126 -> 117 us at 1 token, 186 -> 174 at 256, 223 -> 225 at 400, 365 -> 388 at
+// 1024; depth-history memory 156 -> 137 at 48.  fp32, four layers of d = 256, d_m = 32:
+// 426 -> 208 us at 300 tokens, 614 -> 569 at 2048, 818 -> 989 at 4096.
+constexpr int kTokenRowsBf16 = 256, kTokenRowsF32 = 2048;
+
+template <typename W, int PI, int R>
+struct TokenMat {
+  Raw8<W> w[R];
+  static constexpr int ROWS = NTT / PI;  // rows per pass
+  // row(o): first element of row o; zero past O rows and past I inputs (I % 8 == 0)
+  template <class Row>
+  __device__ __forceinline__ void load(int O, int I, Row row) {
+    const int sl = static_cast<int>(threadIdx.x) % PI, o0 = static_cast<int>(threadIdx.x) / PI;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int o = o0 + ROWS * r;
+      if (o < O && 8 * sl < I)
+        w[r].load(row(o) + 8 * sl);
+      else
+        w[r].zero();
+    }
+  }
+  // f(o, sum) for every row o < O this thread's group holds, sum in all PI lanes of the group
+  template <class F>
+  __device__ __forceinline__ void dot(const float* x, int O, F f) const {
+    const int sl = static_cast<int>(threadIdx.x) % PI, o0 = static_cast<int>(threadIdx.x) / PI;
+    float xv[8];
+    *reinterpret_cast<f32x4*>(xv) = *reinterpret_cast<const f32x4*>(x + 8 * sl);
+    *reinterpret_cast<f32x4*>(xv + 4) = *reinterpret_cast<const f32x4*>(x + 8 * sl + 4);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float acc = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fmaf(w[r][e], xv[e], acc);
+      acc = group_sum<PI>(acc);
+      const int o = o0 + ROWS * r;
+      if (o < O) f(r, o, acc);
+    }
+  }
+};
+
+// HIST: the memory in depth-history form (kv, hw); otherwise the matrix S of storage type ST
+template <typename W, int DM, typename ST, bool HIST, bool PRE>
+__global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) {
+  constexpr int PM = DM / 8;                                   // pieces of a d_m-wide row
+  constexpr int R_HU = kTokenMaxS * 32 / NTT, R_P2 = kTokenMaxS * 16 / NTT;
+  constexpr int R_Q = 4 * DM * 8 / NTT > 0 ? 4 * DM * 8 / NTT : 1;
+  constexpr int R_TS = MAXE * 8 / NTT;
+  constexpr int R_C = DM * PM / NTT > 0 ? DM * PM / NTT : 1;
+  constexpr int R_TC = MAXE * PM / NTT > 0 ? MAXE * PM / NTT : 1;
+  constexpr int VE = 16 / static_cast<int>(sizeof(ST));        // state elements per 16 bytes
+  constexpr int CV = DM / VE, RP = NTT / CV;                   // vectors per S row, rows per pass
+  constexpr int NR = DM / RP > 0 ? DM / RP : 1;                // S rows per thread
+  constexpr int CH = NR < 8 ? NR : 8;                          // ... per batch
+  constexpr int EPL = DM >= kWave ? DM / kWave : 1;            // history: elements per lane
+  constexpr int HPW = kHistMax / NWT;                          // history: pairs per wave
+  constexpr int NRED = HIST ? NWT : (RP < DM ? RP : DM);
+  LDS16 float xs[MAXE];           // SiLU(inv_rms W_hd hbar)
+  LDS16 float hp[kTokenMaxP];     // path-encoder hidden
+  LDS16 float s[kTokenMaxS];
+  LDS16 float pr[4][DM];          // phi(q), phi(k), v, W_n s
+  LDS16 float hs[MAXE];           // th1[:, :d_s] s
+  LDS16 float cv[DM];             // c
+  LDS16 float red[NRED][DM];
+  __shared__ float bpart[NWT], dpart[NWT], npart[NWT][3], apart[NWT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const size_t t = blockIdx.x;
+  const int j = a.j, d_e = a.d_e, d_head = a.d_head, NP = d_e + d_head;
+  const int d_s = a.d_s, d_h = a.d_h, d_a = a.d_a, d_p = a.d_p;
+  const bool mem = !(a.abl & (ABL_NO_MEMREAD | ABL_NO_HISTORY));
+  const bool ctx = j > 1 && mem;
+
+  // (1) every load of the kernel
+  float pv[MAXSPLIT];
+#pragma unroll
+  for (int z = 0; z < MAXSPLIT; ++z)
+    pv[z] = tid < NP && z < a.p_splits ? a.P[(static_cast<size_t>(z) * a.T + t) * NP + tid] : 0.f;
+  const f32x4 rs = *reinterpret_cast<const f32x4*>(a.rowstat + 4 * t);
+  const float pprev = j > 1 ? a.p_hist[t] : 1.f, mprev = j > 1 ? a.m_hist[t] : 1.f;
+  const float beta = a.beta ? a.beta[t] : 0.f;
+  const W* w_p1 = static_cast<const W*>(a.w_p1);
+  W p1[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) p1[k] = tid < d_p ? w_p1[tid * 6 + k] : W(0);
+  const bool head = tid >= d_e && tid < NP;
+  const W ps2 = head ? static_cast<const W*>(a.ps2)[tid - d_e] : W(0);
+  TokenMat<W, 32, R_HU> m_hu;
+  TokenMat<W, 16, R_P2> m_p2;
+  TokenMat<W, 8, R_Q> m_q;
+  TokenMat<W, 8, R_TS> m_ts;
+  TokenMat<W, PM, R_C> m_c;
+  TokenMat<W, PM, R_TC> m_tc;
+  W wnu[R_TC], th2[R_TC];
+  auto load_hu = [&] {
+    m_hu.load(d_h, d_e, [&](int o) { return static_cast<const W*>(a.w_hu) + o * d_e; });
+    m_p2.load(d_a, d_p, [&](int o) { return static_cast<const W*>(a.w_p2) + o * d_p; });
+  };
+  auto load_s = [&] {
+    m_q.load(4 * DM, d_s, [&](int o) {
+      const int m = o / DM;
+      const void* w = m == 0 ? a.w_q : m == 1 ? a.w_k : m == 2 ? a.w_v : a.w_n;
+      return static_cast<const W*>(w) + (o - m * DM) * d_s;
+    });
+    m_ts.load(d_head, d_s, [&](int o) { return static_cast<const W*>(a.th1) + o * a.ld_th1; });
+  };
+  auto load_c = [&] {
+    m_c.load(DM, DM, [&](int o) { return static_cast<const W*>(a.w_c) + o * DM; });
+    m_tc.load(d_head, DM, [&](int o) { return static_cast<const W*>(a.th1) + o * a.ld_th1 + d_s; });
+#pragma unroll
+    for (int r = 0; r < R_TC; ++r) {
+      const int o = tid / PM + NTT / PM * r;
+      wnu[r] = o < d_head ? static_cast<const W*>(a.th1)[o * a.ld_th1 + d_s + DM] : W(0);
+      th2[r] = o < d_head ? static_cast<const W*>(a.th2)[o] : W(0);
+    }
+  };
+  // the token's memory: S rows rg, rg + RP, ... (columns VE cq ..), or the wave's pairs
+  const int cq = tid % CV, rg = tid / CV;
+  const bool on = rg < DM;
+  ST* Sp = HIST ? nullptr : static_cast<ST*>(a.S) + t * DM * DM + VE * cq;
+  u32x4 sv[HIST ? 1 : CH];
+  auto load_mem = [&](int i0) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+      if (on) sv[c] = *reinterpret_cast<const u32x4*>(Sp + (rg + RP * (i0 + c)) * DM);
+  };
+  float* H = HIST ? a.kv + t * a.L_R * 2 * DM : nullptr;
+  const int np = j - 1;                       // stored pairs
+  const bool hl = lane * EPL < DM;
+  float hk[HIST ? HPW : 1][EPL], hv[HIST ? HPW : 1][EPL];
+  float zv = 0.f;
+  if constexpr (HIST) {
+    if (mem) {
+#pragma unroll
+      for (int u = 0; u < HPW; ++u) {
+        const int i = wave + NWT * u;
+#pragma unroll
+        for (int x = 0; x < EPL; ++x) {
+          hk[u][x] = i < np && hl ? H[static_cast<size_t>(i) * 2 * DM + lane * EPL + x] : 0.f;
+          hv[u][x] = i < np && hl ? H[static_cast<size_t>(i) * 2 * DM + DM + lane * EPL + x] : 0.f;
+        }
+      }
+    }
+  } else if (ctx) {
+    if constexpr (PRE && NR == CH) load_mem(0);
+    if (tid < DM) zv = a.zeta[t * DM + tid];
+  }
+  if constexpr (PRE) {
+    load_hu();
+    load_s();
+    load_c();
+  }
+
+  // (2) SiLU of the pre-activations, the local head's shares, the path encoder's hidden layer
+  float p = pv[0];
+#pragma unroll
+  for (int z = 1; z < MAXSPLIT; ++z) p += pv[z];
+  if (tid < d_e) xs[tid] = siluf_(rs[0] * p);
+  const float bsum = wave_sum(head ? ldf(&ps2) * siluf_(p) : 0.f);
+  if (lane == 0) bpart[wave] = bsum;
+  for (int e = d_e + tid; e < MAXE; e += NTT) xs[e] = 0.f;
+  if (tid < kTokenMaxP) {
+    float h = 0.f;
+    if (tid < d_p) {
+      const float dj = j >= 2 ? sqrtf(rs[1]) : 0.f;
+      const float gam = j >= 3 ? rs[2] / (dj * sqrtf(rs[3]) + a.eps) : 0.f;
+      const bool pos = !(a.abl & ABL_NO_POS);
+      const float xp[6] = {pos ? static_cast<float>(j) / static_cast<float>(a.L_R) : 0.f,
+                           pos ? static_cast<float>(a.L_R - j) / static_cast<float>(a.L_R) : 0.f,
+                           pos ? dj : 0.f, pos ? gam : 0.f, pprev, mprev};
+#pragma unroll
+      for (int k = 0; k < 6; ++k) h = fmaf(ldf(&p1[k]), xp[k], h);
+      h = siluf_(h);
+    }
+    hp[tid] = h;
+  }
+  if (tid < kTokenMaxS) s[tid] = 0.f;
+  if constexpr (!PRE) load_hu();
+  __syncthreads();
+
+  // (3) s = [z_h; z_a]
+  m_hu.dot(xs, d_h, [&](int, int o, float v) {
+    if (tid % 32 == 0) s[o] = v;
+  });
+  m_p2.dot(hp, d_a, [&](int, int o, float v) {
+    if (tid % 16 == 0) s[d_h + o] = a.abl & ABL_NO_AUX ? 0.f : v;
+  });
+  if constexpr (!PRE) load_s();
+  __syncthreads();
+
+  // (4) phi(q), phi(k), v, W_n s and the s part of the history head
+  m_q.dot(s, 4 * DM, [&](int, int o, float v) {
+    if (tid % 8 == 0) pr[o / DM][o % DM] = o < 2 * DM ? phif_(v) : v;
+  });
+  m_ts.dot(s, d_head, [&](int, int o, float v) {
+    if (tid % 8 == 0) hs[o] = v;
+  });
+  if constexpr (!PRE) load_c();
+  __syncthreads();
+
+  // (5) memory read, then write
+  if constexpr (HIST) {
+    float c[EPL], den = 0.f;
+#pragma unroll
+    for (int x = 0; x < EPL; ++x) c[x] = 0.f;
+    if (mem) {
+#pragma unroll
+      for (int u = 0; u < HPW; ++u) {
+        const int i = wave + NWT * u;
+        if (i < np) {
+          float d = 0.f;
+#pragma unroll
+          for (int x = 0; x < EPL; ++x)
+            if (hl) d = fmaf(pr[0][lane * EPL + x], hk[u][x], d);
+          const float al = a.hw[i] * wave_sum(d);
+          den += al;
+#pragma unroll
+          for (int x = 0; x < EPL; ++x) c[x] = fmaf(al, hv[u][x], c[x]);
+        }
+      }
+      for (int e = tid; e < 2 * DM; e += NTT) H[static_cast<size_t>(np) * 2 * DM + e] = pr[1 + e / DM][e % DM];
+    }
+    if (lane == 0) dpart[wave] = den;
+    if (hl)
+#pragma unroll
+      for (int x = 0; x < EPL; ++x) red[wave][lane * EPL + x] = c[x];
+  } else {
+    const float rho = 1.0f / (1.0f + expf(-a.eta));
+    float d = 0.f;
+    if (mem && tid < DM) {
+      d = pr[0][tid] * zv;
+      a.zeta[t * DM + tid] = fmaf(rho, zv, pr[1][tid]);
+    }
+    d = wave_sum(d);
+    if (lane == 0) dpart[wave] = d;
+    float vr[VE], cacc[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      vr[e] = pr[2][VE * cq + e];
+      cacc[e] = 0.f;
+    }
+    if (mem && on) {
+      for (int i0 = 0; i0 < NR; i0 += CH) {
+        if (ctx && !(PRE && NR == CH)) load_mem(i0);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          const int r = rg + RP * (i0 + c);
+          const float qv = pr[0][r], kv = pr[1][r];
+          float o[VE];
+#pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            float x = 0.f;
+            if (ctx) {
+              if constexpr (VE == 4)
+                x = __uint_as_float(sv[c][e]);
+              else
+                x = __uint_as_float(e & 1 ? sv[c][e >> 1] & 0xffff0000u : sv[c][e >> 1] << 16);
+            }
+            cacc[e] = fmaf(qv, x, cacc[e]);
+            o[e] = ctx ? fmaf(rho, x, kv * vr[e]) : kv * vr[e];
+          }
+          u32x4 w;
+          if constexpr (VE == 4) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(o[e]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              w[e] = static_cast<uint32_t>(f32_to_bf16(o[2 * e])) |
+                     (static_cast<uint32_t>(f32_to_bf16(o[2 * e + 1])) << 16);
+          }
+          *reinterpret_cast<u32x4*>(Sp + r * DM) = w;
+        }
+      }
+    }
+    if (on)
+#pragma unroll
+      for (int e = 0; e < VE; ++e) red[rg][VE * cq + e] = cacc[e];
+  }
+  __syncthreads();
+  if (tid < DM) {
+    float c = 0.f, den = 0.f;
+#pragma unroll
+    for (int g = 0; g < NRED; ++g) c += red[g][tid];
+#pragma unroll
+    for (int w = 0; w < NWT; ++w) den += dpart[w];
+    c = ctx ? c / (den + a.eps) : 0.f;
+    cv[tid] = c;
+    if (a.c_read && mem) a.c_read[t * DM + tid] = c;
+  }
+  __syncthreads();
+
+  // (6) W_c c beside W_n s for nu; the c part of the history head
+  float nn = 0.f, cc = 0.f, nc = 0.f, pre[R_TC];
+  m_c.dot(cv, DM, [&](int, int o, float v) {
+    const float n = pr[3][o];
+    if (tid % PM == 0) {
+      nn = fmaf(n, n, nn);
+      cc = fmaf(v, v, cc);
+      nc = fmaf(n, v, nc);
+    }
+  });
+#pragma unroll
+  for (int r = 0; r < R_TC; ++r) pre[r] = 0.f;
+  m_tc.dot(cv, d_head, [&](int r, int o, float v) { pre[r] = v + hs[o]; });
+  nn = wave_sum(nn);
+  cc = wave_sum(cc);
+  nc = wave_sum(nc);
+  if (lane == 0) {
+    npart[wave][0] = nn;
+    npart[wave][1] = cc;
+    npart[wave][2] = nc;
+  }
+  __syncthreads();
+  float tot[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < NWT; ++w)
+#pragma unroll
+    for (int e = 0; e < 3; ++e) tot[e] += npart[w][e];
+  const float nu = ctx ? 1.0f - tot[2] / (sqrtf(tot[0]) * sqrtf(tot[1]) + a.eps) : 0.f;
+  float av = 0.f;
+#pragma unroll
+  for (int r = 0; r < R_TC; ++r)   // rows past d_head have th2 = 0
+    av = fmaf(ldf(&th2[r]), siluf_(fmaf(ldf(&wnu[r]), nu, pre[r])), av);
+  av = wave_sum(tid % PM == 0 ? av : 0.f);
+  if (lane == 0) apart[wave] = av;
+  __syncthreads();
+  if (tid == 0) {
+    const bool hist = !(a.abl & ABL_NO_HISTORY);
+    float aa = 0.f, b = 0.f;
+#pragma unroll
+    for (int w = 0; w < NWT; ++w) {
+      aa += apart[w];
+      b += bpart[w];
+    }
+    if (!hist) aa = 0.f;
+    const float ph = sigmoidf_(aa / a.T_hist);
+    a.p_hist[t] = hist ? ph : 1.0f;
+    a.m_hist[t] = hist ? mprev * ph : 1.0f;
+    const float l = aa + b + beta;
+    a.logit[t] = l;
+    a.gate[t] = sigmoidf_(l);
+  }
+}
+
+template <typename W, int DM>
+hipError_t launch_token_dm(const RouterTailArgs& a, bool hist, hipStream_t s) {
+  // the widths whose weights and memory fit the registers of two waves per SIMD
+  constexpr bool PRE = sizeof(W) == 2 ? DM <= 128 : DM <= 64;
+  if (hist) {
+    router_token_kernel<W, DM, float, true, PRE><<<a.T, NTT, 0, s>>>(a);
+  } else if (a.state_bf16) {
+    if constexpr (DM >= 64)
+      router_token_kernel<W, DM, bf16_t, false, PRE><<<a.T, NTT, 0, s>>>(a);
+    else
+      return hipErrorInvalidValue;
+  } else {
+    router_token_kernel<W, DM, float, false, PRE><<<a.T, NTT, 0, s>>>(a);
+  }
+  return hipGetLastError();
+}
+
+template <typename W>
+hipError_t launch_token(const RouterTailArgs& a, bool hist, hipStream_t s) {
+  switch (a.d_m) {
+    case 32: return launch_token_dm<W, 32>(a, hist, s);
+    case 64: return launch_token_dm<W, 64>(a, hist, s);
+    case 128: return launch_token_dm<W, 128>(a, hist, s);
+    case 256:
+      if constexpr (sizeof(W) == 2) return launch_token_dm<W, 256>(a, hist, s);
+      return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+  }
+}
+
 #undef LDS16
 
 hipError_t launch_pre_post(const RouterTailArgs& a, bool post, hipStream_t s) {
@@ -1034,6 +1431,18 @@ hipError_t launch_pre_post(const RouterTailArgs& a, bool post, hipStream_t s) {
 
 size_t router_scratch_floats(int d_m, int d_head, int T) {
   return static_cast<size_t>(T) * (4 * d_m + d_head + d_m + 1);
+}
+
+bool router_token_fits(int dtype, int T, int d_m, int d_s, int d_h, int d_a, int d_e, int d_p, int d_head) {
+  return T <= (dtype == 1 ? kTokenRowsBf16 : kTokenRowsF32) && (dtype == 1 || d_m <= 128) && d_s <= kTokenMaxS && d_h <= kTokenMaxS && d_a <= kTokenMaxS && d_p <= kTokenMaxP &&
+         d_e <= MAXE && d_head <= MAXE && d_s % 8 == 0 && d_e % 8 == 0 && d_p % 8 == 0;
+}
+
+hipError_t launch_router_token(const RouterTailArgs& a, bool hist, hipStream_t s) {
+  if (a.T <= 0) return hipSuccess;
+  if (a.p_splits < 1 || a.p_splits > MAXSPLIT || (hist && (a.j < 1 || a.j > a.L_R || a.L_R > kHistMax)))
+    return hipErrorInvalidValue;
+  return a.dtype == 1 ? launch_token<bf16_t>(a, hist, s) : launch_token<float>(a, hist, s);
 }
 
 hipError_t launch_router_pre(const RouterTailArgs& a, hipStream_t s) {

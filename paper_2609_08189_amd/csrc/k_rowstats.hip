@@ -13,25 +13,6 @@
 
 namespace hero {
 
-// Eight consecutive elements as loaded (bf16 stays packed: 4 registers per chunk).
-template <typename T> struct Raw8;
-template <> struct Raw8<bf16_t> {
-  u32x4 v;
-  __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const u32x4*>(p); }
-  __device__ __forceinline__ float operator[](int i) const {
-    const uint32_t w = v[i >> 1];
-    return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
-  }
-};
-template <> struct Raw8<float> {
-  f32x4 a, b;
-  __device__ __forceinline__ void load(const float* p) {
-    a = *reinterpret_cast<const f32x4*>(p);
-    b = *reinterpret_cast<const f32x4*>(p + 4);
-  }
-  __device__ __forceinline__ float operator[](int i) const { return i < 4 ? a[i] : b[i - 4]; }
-};
-
 // One workgroup per token, its row split over the 4 waves (8 elements per lane per pass, up to
 // four passes kept in registers for the normalisation), the four sums reduced across the waves
 // through LDS.  Measured against four tokens per workgroup (one per wave): 26.8 against 28.4 us at
