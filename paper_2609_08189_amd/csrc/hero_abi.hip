@@ -41,9 +41,9 @@ struct Layout {
       total;
 };
 
-// At most this many tokens (a decode batch) the row statistics run beside the router product and
-// the adapter branch beside the FFN branch, on a second stream (the adapter with a partial-sum
-// region of its own).
+// At most this many tokens (a decode batch) the adapter branch runs beside the FFN branch with a
+// partial-sum region of its own: inside the FFN's launches (decode_route_fits), or on a second
+// stream (wide adapters).
 constexpr int kOverlapTokens = 256;
 
 Layout layout_of(const hero_dims& d, int T, bool stack) {
@@ -322,23 +322,29 @@ int run_layer(const LayerCall& c) {
     hipError_t x = hipEventRecord(sd->join, sd->s);
     return x == hipSuccess ? hipStreamWaitEvent(st, sd->join, 0) : x;
   };
-  // the row statistics (for the router's path vector and the branches' input) and the router's
-  // pre-activation product both read only hbar: side by side for a decode batch (with many
-  // tokens the product fills every CU and the statistics pass, starved, only stretches)
-  const bool ovl_rows = sd && T <= kOverlapTokens;
-  const hipStream_t s_rows = ovl_rows ? sd->s : st;
-  hipError_t e = ovl_rows ? fork() : hipSuccess;
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-  e = timed(HERO_K_ROWSTATS, s_rows, [&] {
-    return launch_rowstats(D.dtype, c.hbar, c.j >= 2 ? c.prev1 : nullptr, c.j >= 3 ? c.prev2 : nullptr,
-                           c.ffn->norm_w, T, D.d, c.j, D.eps_norm, rowstat, u, s_rows);
-  });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-  e = timed(HERO_K_ROUTER_GEMM, st, [&] {
-    return launch_router_gemm(D.dtype, c.hbar, c.rt->w_hd, c.rt->ps1, T, D.d, D.d_e, D.d_head, P, st);
-  });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-  if (ovl_rows && join() != hipSuccess) return HERO_E_LAUNCH;
+  const auto nothing = [] { return hipSuccess; };
+  hipError_t e = hipSuccess;
+  const void* prev1 = c.j >= 2 ? c.prev1 : nullptr;
+  const void* prev2 = c.j >= 3 ? c.prev2 : nullptr;
+  if (decode_head_fits(D.dtype, T, D.d, D.d_e, D.d_e + D.d_head)) {
+    // few tokens: the row pass and the router's product in one launch, timed as the product
+    e = timed(HERO_K_ROWSTATS, st, nothing);
+    if (e == hipSuccess)
+      e = timed(HERO_K_ROUTER_GEMM, st, [&] {
+        return launch_decode_head(c.hbar, prev1, prev2, c.ffn->norm_w, c.rt->w_hd, c.rt->ps1, T, D.d, D.d_e, D.d_head,
+                                  c.j, D.eps_norm, P, rowstat, u, st);
+      });
+    if (e != hipSuccess) return HERO_E_LAUNCH;
+  } else {
+    e = timed(HERO_K_ROWSTATS, st, [&] {
+      return launch_rowstats(D.dtype, c.hbar, prev1, prev2, c.ffn->norm_w, T, D.d, c.j, D.eps_norm, rowstat, u, st);
+    });
+    if (e != hipSuccess) return HERO_E_LAUNCH;
+    e = timed(HERO_K_ROUTER_GEMM, st, [&] {
+      return launch_router_gemm(D.dtype, c.hbar, c.rt->w_hd, c.rt->ps1, T, D.d, D.d_e, D.d_head, P, st);
+    });
+    if (e != hipSuccess) return HERO_E_LAUNCH;
+  }
 
   RouterTailArgs ra{};
   ra.dtype = D.dtype;
@@ -394,7 +400,6 @@ int run_layer(const LayerCall& c) {
     ra.cvec = ra.hs + t * D.d_head;
     ra.bvec = ra.cvec + t * D.d_m;
   }
-  const auto nothing = [] { return hipSuccess; };
   if (router_token_fits(D.dtype, T, D.d_m, D.d_s, D.d_h, D.d_a, D.d_e, D.d_p, D.d_head)) {
     // few tokens: one launch, timed as the memory pass
     ra.c_read = c.c_read;
@@ -432,18 +437,30 @@ int run_layer(const LayerCall& c) {
   sa.idx_ad = idx_ad;
   sa.counts = counts;
   sa.lambda = lambda;
-  e = timed(HERO_K_SELECT, st, [&] { return launch_select(sa, st); });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-
   // grid sizes: exact in budget mode, T in threshold mode (tiles past the device count exit)
   const int n_ffn_max = c.rc->mode == HERO_MODE_BUDGET ? T - n_skip : T;
   const int n_ad_max = c.rc->mode == HERO_MODE_BUDGET ? n_skip : T;
   void* act = ws + L.act;
   float* part = reinterpret_cast<float*>(ws + L.part);
   float* part_ad = reinterpret_cast<float*>(ws + L.part_ad);
+  if (decode_route_fits(D.dtype, T, n_ffn_max, D.d, D.d_ff, D.d_r)) {
+    // a decode step: the decision and the adapter's down-projection inside the gate/up launch, the
+    // adapter's up-projection with the down product's reduction (timed as the adapter's up)
+    const DecodeRoute r{sa, n_ffn_max, n_ad_max, D.d, D.d_ff, D.d_r, u, c.hbar, c.ffn->w_gate, c.ffn->w_up,
+                        c.ffn->w_gate_up_tiled, c.ffn->w_down, c.ffn->w_down_tiled, c.ad->w1, c.ad->w2, gate, act,
+                        c.h_out, part, part_ad};
+    e = timed(HERO_K_SELECT, st, nothing);
+    if (e == hipSuccess) e = timed(HERO_K_FFN_GATE_UP, st, [&] { return launch_route_gateup(r, st); });
+    if (e == hipSuccess) e = timed(HERO_K_FFN_DOWN, st, [&] { return launch_route_down(r, st); });
+    if (e == hipSuccess) e = timed(HERO_K_ADAPTER_DOWN, st, nothing);
+    if (e == hipSuccess) e = timed(HERO_K_ADAPTER_UP, st, [&] { return launch_route_finish(r, st); });
+    return e == hipSuccess ? HERO_OK : HERO_E_LAUNCH;
+  }
+  e = timed(HERO_K_SELECT, st, [&] { return launch_select(sa, st); });
+  if (e != hipSuccess) return HERO_E_LAUNCH;
   // the two branches write disjoint rows of h_out and read only hbar, u, the gates and the lists:
   // for a decode batch the adapter's latency-bound launches run beside the FFN's weight stream
-  const bool ovl = sd && T <= kOverlapTokens && n_ffn_max > 0 && n_ad_max > 0;
+  const bool ovl = sd && D.dtype == HERO_BF16 && T <= kOverlapTokens && n_ffn_max > 0 && n_ad_max > 0;
   const hipStream_t s_ad = ovl ? sd->s : st;
   if (ovl && fork() != hipSuccess) return HERO_E_LAUNCH;
   if (n_ffn_max > 0) {

@@ -20,6 +20,18 @@ hipError_t launch_rowstats(int dtype, const void* hbar, const void* prev1, const
 // written as router_gemm_splits(dtype, d, T, d_e + d_head) partial sums over K slices, slice z at
 // P + z T (d_e + d_head).
 int router_gemm_splits(int dtype, int d, int T, int N);
+// launch_router_gemm and launch_rowstats in one launch, for bf16 calls of at most 256 tokens
+// (router_gemm_splits slices of P)
+constexpr int kDecodeTokens = 256;
+bool decode_head_fits(int dtype, int T, int d, int d_e, int N);
+hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                              const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                              float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);
+// ... on the tiles of launch_router_gemm, for its more than 64 tokens
+bool decode_head_tiles_fit(int N);
+hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                                    const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                                    float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);
 hipError_t launch_router_gemm(int dtype, const void* hbar, const void* w_hd, const void* ps1,
                               int T, int d, int d_e, int d_head, float* P, hipStream_t s);
 
@@ -104,6 +116,23 @@ hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const
 hipError_t launch_ffn_down(int dtype, const void* act, const int* idx_ffn, const int* counts,
                            int n_max, const void* w_down, const void* w_down_tiled, const void* hbar,
                            const float* gate, void* h_out, float* part, int d, int d_ff, hipStream_t s);
+// A routed decode step after the router, in three launches: the branch decision and the adapter's
+// down-projection beside the gate/up product; the down product; its reduction and scatter beside
+// the adapter's up-projection.  For bf16 calls of at most 256 tokens with a FFN row for certain or
+// possible (n_ffn_max > 0) and an adapter rank up to 128.  part: ffn_part_floats, part_ad:
+// adapter_part_floats.
+struct DecodeRoute {
+  SelectArgs sel;
+  int n_ffn_max, n_ad_max, d, d_ff, d_r;
+  const void *u, *hbar, *w_gate, *w_up, *w_gate_up_tiled, *w_down, *w_down_tiled, *w1, *w2;
+  const float* gate;
+  void *act, *h_out;
+  float *part, *part_ad;
+};
+bool decode_route_fits(int dtype, int T, int n_ffn_max, int d, int d_ff, int d_r);
+hipError_t launch_route_gateup(const DecodeRoute& r, hipStream_t s);
+hipError_t launch_route_down(const DecodeRoute& r, hipStream_t s);
+hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s);
 // The frozen FFN weights in the decode products' streaming order (bf16): W [N][K] becomes
 // [K/64][N/16][G][16][64], i.e. 16 x 64 tiles of 2 KiB, k-tile by k-tile, each k-tile's row of
 // 16-row blocks contiguous, with G = 2 matrices alternating tile by tile (W_g then W_u) or G = 1 (W_d).

@@ -25,6 +25,7 @@
 
 #include "hero_device.h"
 #include "hero_kernels.h"
+#include "hero_rows.h"
 
 namespace hero {
 namespace {
@@ -75,6 +76,17 @@ struct EpiStoreF32 {  // P[m][n] = acc; the MFMA path's K-slice z writes out + z
     *reinterpret_cast<f32x4*>(o) = *reinterpret_cast<const f32x4*>(v);
     *reinterpret_cast<f32x4*>(o + 4) = *reinterpret_cast<const f32x4*>(v + 4);
   }
+};
+
+// EpiStoreF32 of the router's product in a decode step, whose launch also holds the row pass:
+// workgroups (x >= tile_blocks, y) take token (x - tile_blocks) gridDim.y + y
+struct EpiStoreF32Rows : EpiStoreF32 {
+  static constexpr bool kRows = true;
+  int tile_blocks, T, d, j;
+  const bf16_t *hbar, *prev1, *prev2, *norm_w;
+  float eps_norm;
+  float* rowstat;
+  bf16_t* u;
 };
 
 template <typename T>
@@ -246,6 +258,12 @@ struct DualHook : std::false_type {};
 template <class E>
 struct DualHook<E, std::void_t<decltype(E::kDualHook)>> : std::true_type {};
 
+// An epilogue with kRows brings the row pass of a decode step along (EpiStoreF32Rows)
+template <class E, class = void>
+struct RowsHook : std::false_type {};
+template <class E>
+struct RowsHook<E, std::void_t<decltype(E::kRows)>> : std::true_type {};
+
 template <class C, class Epi>
 __device__ __forceinline__ void swiglu_bwd_tile(const Epi& epi, f32x16 (&acc)[C::TM][C::TN], unsigned char* smem, int m0,
                                 int nt, int wave, int wm, int wn, int M, int lane);
@@ -329,6 +347,16 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
   constexpr int NR = C::TM + C::TN;     // fragment reads per k-step
   constexpr int NL = A_LD + B_LD;       // stage loads per k-tile
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::NS * C::STAGE];
+  if constexpr (RowsHook<Epi>::value) {
+    if (static_cast<int>(blockIdx.x) >= epi.tile_blocks) {
+      const int t = (static_cast<int>(blockIdx.x) - epi.tile_blocks) * static_cast<int>(gridDim.y) +
+                    static_cast<int>(blockIdx.y);
+      if (t < epi.T)
+        rowstats_row<bf16_t, C::NT>(t, epi.hbar, epi.prev1, epi.prev2, epi.norm_w, epi.d, epi.j, epi.eps_norm,
+                                    epi.rowstat, epi.u);
+      return;
+    }
+  }
   // Workgroups go to the 8 XCDs round-robin; XCD x takes the contiguous range
   // [x per, (x+1) per) of a grouped tile order (GROUP_M row tiles by every column tile),
   // so that the 32 tiles one XCD runs at a time share 8 row panels and 4 column panels
@@ -860,6 +888,185 @@ hipError_t run_tile(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_coun
 }
 
 // ---------------------------------------------------------------------------
+// A routed decode step (at most 256 tokens) folds the branch decision and the adapter's
+// down-projection into the gate/up launch, whose weight stream hides them (decode_route):
+//   * every workgroup's activation producers decide the branches for themselves, one wave over up
+//     to four tokens a lane, while the weight producers fill their ring; one workgroup also writes
+//     the mask, the lists, the counts and lambda;
+//   * the adapter's z = u W_1^T is formed for every token, so it waits for no decision: the launch
+//     leaves CUs over (the busiest of ceil(nb / G) column blocks sets the time, and fewer
+//     workgroups G reach the same maximum), and the first workgroups are the adapter's.
+// The down product's reduction carries the adapter's up-projection the same way (decode_finish).
+// Five launches on one stream instead of eleven on two, whose forks and joins cost an eager call
+// about 7 us each: one 8B layer at 1 token 107 -> 85 us, 48 tokens 140 -> 102, the 7B decode stack of
+// 256 tokens (a graph) 4.42 -> 3.74 ms with decode_head.
+// ---------------------------------------------------------------------------
+constexpr int kRouteTokens = 256;
+
+struct RouteArgs {
+  SelectArgs sel;
+  int na;                  // adapter workgroups (a multiple of 8): row tiles of 32 tokens x K-slices
+  int slices, d_r;
+  const bf16_t *u, *w1;
+  float* part;             // [slices][T][d_r]
+};
+
+struct RouteFinish {
+  const float* part_ad;
+  const int *idx_ad, *idx_ffn, *counts;
+  const bf16_t *w2, *hbar;
+  const float* gate;
+  bf16_t* out;
+  int T, d, up_blocks;
+  const float* part;
+  int S, n_ffn_max;
+  size_t stride;
+};
+
+// The branch decision of select_kernel for T <= 256 tokens by one wave: lane l holds tokens
+// l, l + 64, ...  The n_skip-th smallest key is found bit by bit over ballots, its ties by token
+// index.  list receives the FFN tokens in ascending order (256 ints); write: the outputs of
+// SelectArgs too.  Returns the FFN count.
+__device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* list, bool write) {
+  constexpr int Q = kRouteTokens / kWave;
+  float l[Q];
+  uint32_t key[Q];
+  unsigned long long valid[Q], skip[Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int t = lane + kWave * i;
+    l[i] = t < a.T ? a.logit[t] : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    key[i] = order_key(l[i]);
+    valid[i] = __ballot(lane + kWave * i < a.T);
+    skip[i] = 0;
+  }
+  if (a.mode == 0) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) skip[i] = valid[i] & ~__ballot(l[i] >= a.thr);
+  } else if (a.n_skip > 0) {
+    // act: the tokens whose key agrees with the sought one in the bits taken so far; k: its rank
+    // among them; skip: the tokens with smaller keys
+    unsigned long long act[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) act[i] = valid[i];
+    int k = a.n_skip;
+    for (int bit = 31; bit >= 0; --bit) {
+      unsigned long long zero[Q];
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        zero[i] = act[i] & __ballot(((key[i] >> bit) & 1u) == 0u);
+        n += __popcll(zero[i]);
+      }
+      const bool low = k <= n;
+#pragma unroll
+      for (int i = 0; i < Q; ++i) {
+        if (!low) skip[i] |= zero[i];
+        act[i] = low ? zero[i] : act[i] & ~zero[i];
+      }
+      if (!low) k -= n;
+    }
+    // the first k of the tied tokens
+    int before = 0;
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+      const int r = before + __popcll(act[i] & ((1ull << lane) - 1ull));
+      skip[i] |= __ballot(((act[i] >> lane) & 1ull) && r < k);
+      before += __popcll(act[i]);
+    }
+  }
+  int nf = 0, na = 0;
+  float lmin = __builtin_inff();
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    const int t = lane + kWave * i;
+    const unsigned long long ffn = valid[i] & ~skip[i], ad = valid[i] & skip[i];
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const bool f = (ffn >> lane) & 1ull;
+    const int pf = nf + __popcll(ffn & below), pa = na + __popcll(ad & below);
+    if (f) list[pf] = t;
+    if (write && t < a.T) {
+      a.mask[t] = f ? 1 : 0;
+      if (f)
+        a.idx_ffn[pf] = t;
+      else
+        a.idx_ad[pa] = t;
+    }
+    if (f) lmin = fminf(lmin, l[i]);
+    nf += __popcll(ffn);
+    na += __popcll(ad);
+  }
+  if (write) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) lmin = fminf(lmin, __shfl_xor(lmin, off, kWave));
+    if (lane == 0) {
+      a.counts[0] = nf;
+      a.counts[1] = na;
+      a.lambda[0] = a.mode == 1 ? lmin : a.thr;
+    }
+  }
+  return nf;
+}
+
+// z of 32 tokens against all d_r = 32 TN columns over one K-slice, by the eight waves of a
+// workgroup, each over an eighth of the slice; the partial tiles are added in wave order
+template <int TN>
+__device__ __forceinline__ void route_adapter(const RouteArgs& a, int K, int wg, unsigned char* smem) {
+  constexpr int SB = 4, R = 32 * TN, RPITCH = R + 1;
+  float* red = reinterpret_cast<float*>(smem);
+  static_assert(8 * 32 * RPITCH * 4 <= 160 * 1024, "partials fit in LDS");
+  const int T = a.sel.T;
+  const int tile = wg / a.slices, g = wg % a.slices, m0 = 32 * tile;
+  if (m0 >= T) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kw = K / a.slices / 8, kbeg = g * (K / a.slices) + wave * kw;
+  const bf16_t* arow = a.u + static_cast<size_t>(min(m0 + (lane & 31), T - 1)) * K + 8 * (lane >> 5);
+  const bf16_t* brow = a.w1 + static_cast<size_t>(lane & 31) * K + 8 * (lane >> 5);
+  f32x16 acc[TN];
+#pragma unroll
+  for (int b = 0; b < TN; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+  for (int k = kbeg; k < kbeg + kw; k += 16 * SB) {
+    bf16x8 fa[SB], fb[SB][TN];
+#pragma unroll
+    for (int st = 0; st < SB; ++st) {
+      const int kk = min(k + 16 * st, kbeg + kw - 16);   // past the slice: loaded again, not used
+      fa[st] = *reinterpret_cast<const bf16x8*>(arow + kk);
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+        fb[st][b] = *reinterpret_cast<const bf16x8*>(brow + static_cast<size_t>(32 * b) * K + kk);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int st = 0; st < SB; ++st)
+      if (k + 16 * st < kbeg + kw)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[st], fb[st][b], acc[b], 0, 0, 0);
+  }
+#pragma unroll
+  for (int b = 0; b < TN; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+      red[(wave * 32 + i) * RPITCH + b * 32 + (lane & 31)] = acc[b][r];
+    }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 32 * R; e += 512) {
+    const int i = e / R, n = e % R;
+    if (m0 + i >= T) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += red[(w * 32 + i) * RPITCH + n];
+    a.part[(static_cast<size_t>(g) * T + m0 + i) * R + n] = v;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Skinny products: a batch of at most 256 rows (a decode step) against weights streamed once
 // from HBM.  The output columns are cut into 16-column blocks spread evenly over the workgroups
 // (block group x takes the contiguous blocks [x nb / G, (x + 1) nb / G), and for the gate/up
@@ -915,31 +1122,69 @@ __device__ __forceinline__ void wait_vm() {
 // rows land in the same LDS slots either way, so the results are identical.  In the tiled order
 // a workgroup's weights of one k-tile are one contiguous run of 2 KiB tiles, and the workgroups
 // running the same k-tile read neighbouring runs, instead of 128-byte visits of rows 8 KiB apart.
-template <class C>
+// ROUTE: a routed decode step's gate/up product (decode_route): the first route.na workgroups are
+// the adapter's, and the rows come from the decision made here instead of m_count and A.idx.
+template <class C, bool ROUTE = false>
 __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t* __restrict__ b0,
                                                   const bf16_t* __restrict__ b1, int ldb, int tiled,
                                                   void* __restrict__ out, int ld, size_t split_stride,
                                                   const int* __restrict__ m_count, int n_max, int K,
-                                                  int nb, int G, int S) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[C::LDS];
+                                                  int nb, int G, int S,
+                                                  typename std::conditional<ROUTE, RouteArgs, int>::type route) {
+  // a routed step's launch also holds the adapter's partial tiles (at most 129 KiB + 4 KiB)
+  constexpr int kLds = ROUTE && C::LDS < 8 * 32 * 129 * 4 ? 8 * 32 * 129 * 4 : C::LDS;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
+  if constexpr (ROUTE) {
+    if (static_cast<int>(blockIdx.x) < route.na) {
+      switch (route.d_r) {
+        case 32: route_adapter<1>(route, K, blockIdx.x, smem); break;
+        case 64: route_adapter<2>(route, K, blockIdx.x, smem); break;
+        case 96: route_adapter<3>(route, K, blockIdx.x, smem); break;
+        default: route_adapter<4>(route, K, blockIdx.x, smem); break;
+      }
+      return;
+    }
+  }
   unsigned char* const sa = smem;
   unsigned char* const sb = smem + C::NSA * C::A_STAGE;
   // G block groups x S K-slices in slice-major order, laid over the 8 XCDs (round-robin dispatch)
   // in contiguous runs: the workgroups of one XCD share one or two K-slices of the activations
   // in its L2
-  const int id = static_cast<int>(blockIdx.x), N = G * S;
+  int id = static_cast<int>(blockIdx.x);
+  if constexpr (ROUTE) id -= route.na;
+  const int N = G * S;
   const int L = N % 8 == 0 ? (id & 7) * (N >> 3) + (id >> 3) : id;
   const int x = L % G, y = L / G;
   const int blk0 = x * nb / G;
   const int cnt = (x + 1) * nb / G - blk0;
-  const int M = m_count ? min(*m_count, n_max) : n_max;
-  if (M <= 0) return;
+  // the row count; a routed step in threshold mode counts the decisions (in budget mode n_max rows,
+  // at least one, are certain)
+  auto rows_of = [&]() -> int {
+    if constexpr (ROUTE) {
+      if (route.sel.mode != 0) return n_max;
+      int n = 0;
+#pragma unroll
+      for (int i = 0; i < kRouteTokens / kWave; ++i) {
+        const int t = static_cast<int>(threadIdx.x & 63) + kWave * i;
+        n += __popcll(__ballot(t < route.sel.T && route.sel.logit[min(t, route.sel.T - 1)] >= route.sel.thr));
+      }
+      return n;
+    } else {
+      return m_count ? min(*m_count, n_max) : n_max;
+    }
+  };
   const int nkt = K / BK;
   const int kt0 = y * nkt / S;
   const int nk = (y + 1) * nkt / S - kt0;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   constexpr int NSA = C::NSA, NSB = C::NSB;
+  const int M = ROUTE && wave >= 6 ? 1 : rows_of();   // the weight producers of a routed step count later
+  if (M <= 0) {
+    if constexpr (ROUTE)
+      if (id == 0 && wave == 0) select_wave(route.sel, lane, reinterpret_cast<int*>(smem), true);
+    return;
+  }
 
   if (wave >= 6) {
     // weight producer: loads q = 2 i + pw, LDS rows 8q .. 8q + 7 = half (q & 1) of block slot q / 2;
@@ -972,6 +1217,13 @@ __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t
     };
     for (int t = 0; t < NSB; ++t)
       if (t < nk) issue(t);
+    if constexpr (ROUTE) {
+      // no FFN row: the other waves have left; this one leaves when its loads have landed
+      if (rows_of() <= 0) {
+        wait_vm<0>();
+        return;
+      }
+    }
     // before barrier j tile j + 1 has landed; tiles up to j + NSB - 1 may be in flight
     for (int j = -1; j < nk; ++j) {
       if (j < 0) {
@@ -990,15 +1242,24 @@ __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t
     // activation producer: loads q = 2 i + pw, LDS rows 8q .. 8q + 7; rows past M repeat row M - 1
     const int pw = wave - 4;
     uint32_t off[C::AL];
+    // the wave's own list of FFN tokens, in the 1 KiB of the first stage that only its loads fill
+    const int* rows = A.idx;
+    if constexpr (ROUTE) {
+      int* list = reinterpret_cast<int*>(sa + pw * 1024);
+      select_wave(route.sel, lane, list, id == 0 && pw == 0);
+      rows = list;
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
 #pragma unroll
     for (int i = 0; i < C::AL; ++i) {
       const int r = 8 * (2 * i + pw) + (lane >> 3);
       const int ch = (lane & 7) ^ ((r >> 1) & 7);
       const int m = min(r, M - 1);
-      const int row = A.idx ? A.idx[m] : m;
+      const int row = rows ? rows[m] : m;
       off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(A.ld * 2) + kt0 * ROWB + ch * 16;
     }
     const unsigned char* abase = reinterpret_cast<const unsigned char*>(A.base);
+    if constexpr (ROUTE) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the list is read before it is overwritten
     auto issue = [&](int t) {
       unsigned char* st = sa + (t % NSA) * C::A_STAGE;
 #pragma unroll
@@ -1101,7 +1362,7 @@ template <class C>
 hipError_t run_skinny(ARows<bf16_t> A, const bf16_t* b0, const bf16_t* b1, int ldb, int tiled, void* out, int ld,
                       size_t split_stride, const int* m_count, int n_max, int K, int nb, int G, int S,
                       hipStream_t s) {
-  skinny_gemm<C><<<G * S, 512, 0, s>>>(A, b0, b1, ldb, tiled, out, ld, split_stride, m_count, n_max, K, nb, G, S);
+  skinny_gemm<C><<<G * S, 512, 0, s>>>(A, b0, b1, ldb, tiled, out, ld, split_stride, m_count, n_max, K, nb, G, S, 0);
   return hipGetLastError();
 }
 
@@ -1342,14 +1603,12 @@ __global__ __launch_bounds__(256) void adapter_down_bf16(const bf16_t* __restric
 //   hid = SiLU(sum_g part[g]) for the 32 rows, rounded to bf16 (the MFMA A operand), in LDS;
 //   each wave computes 64 columns; results are staged in LDS and every thread then writes
 //   8-column pieces h_out[t] = hbar[t] + (1 - g_t) acc with hbar fetched at the start.
-template <int KR, int G>
-__global__ __launch_bounds__(256) void adapter_up_bf16(const float* __restrict__ part,
-                                                       const int* __restrict__ idx,
-                                                       const int* __restrict__ m_count,
-                                                       const bf16_t* __restrict__ w2,
-                                                       const bf16_t* __restrict__ hbar,
-                                                       const float* __restrict__ gate,
-                                                       bf16_t* __restrict__ out, int T, int d) {
+// BY_TOKEN: the partials are held by token (row idx[m]) instead of by list position.
+template <int KR, int G, bool BY_TOKEN>
+__device__ __forceinline__ void adapter_up_tile(const float* __restrict__ part, const int* __restrict__ idx,
+                                                const int* __restrict__ m_count, const bf16_t* __restrict__ w2,
+                                                const bf16_t* __restrict__ hbar, const float* __restrict__ gate,
+                                                bf16_t* __restrict__ out, int T, int d, int m0, int n0) {
   constexpr int NC = 256;
   constexpr int HP = KR + 8;     // hid row pitch (bf16)
   constexpr int SP = NC + 4;     // staged row pitch (fp32)
@@ -1357,10 +1616,8 @@ __global__ __launch_bounds__(256) void adapter_up_bf16(const float* __restrict__
   __shared__ __attribute__((aligned(16))) bf16_t hid[32 * HP];
   __shared__ __attribute__((aligned(16))) float stg[32 * SP];
   const int M = *m_count;
-  const int m0 = blockIdx.x * 32;
   if (m0 >= M) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n0 = blockIdx.y * NC;
   EpiScatter<bf16_t, true> epi{idx, hbar, gate, out, d};
   typename EpiScatter<bf16_t, true>::Pre pre[PPT];
 #pragma unroll
@@ -1370,7 +1627,7 @@ __global__ __launch_bounds__(256) void adapter_up_bf16(const float* __restrict__
   }
   for (int e = tid; e < 32 * KR / 8; e += 256) {
     const int i = e / (KR / 8), k8 = (e % (KR / 8)) * 8;
-    const int mr = min(m0 + i, M - 1);
+    const int mi = min(m0 + i, M - 1), mr = BY_TOKEN ? idx[mi] : mi;
     f32x4 x[G][2];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -1420,6 +1677,17 @@ __global__ __launch_bounds__(256) void adapter_up_bf16(const float* __restrict__
     const int i = e >> 5, c8 = (e & 31) * 8;
     if (m0 + i < M) epi.emit8(pre[q], m0 + i, n0 + c8, stg + i * SP + c8);
   }
+}
+
+template <int KR, int G>
+__global__ __launch_bounds__(256) void adapter_up_bf16(const float* __restrict__ part,
+                                                       const int* __restrict__ idx,
+                                                       const int* __restrict__ m_count,
+                                                       const bf16_t* __restrict__ w2,
+                                                       const bf16_t* __restrict__ hbar,
+                                                       const float* __restrict__ gate,
+                                                       bf16_t* __restrict__ out, int T, int d) {
+  adapter_up_tile<KR, G, false>(part, idx, m_count, w2, hbar, gate, out, T, d, blockIdx.x * 32, blockIdx.y * 256);
 }
 
 template <int KR>
@@ -1478,6 +1746,24 @@ int router_gemm_splits(int dtype, int d, int T, int N) {
   return static_cast<int>(std::max(1LL, std::min(4LL, kCUs / std::max(1LL, tiles))));
 }
 
+bool decode_head_tiles_fit(int N) { return N % TileRouterSmall::OUT_N == 0; }
+
+hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                                    const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                                    float eps_norm, float* P, float* rowstat, void* u, hipStream_t s) {
+  using C = TileRouterSmall;
+  const int N = d_e + d_head, splits = router_gemm_splits(1, d, T, N);
+  const int mt = (T + C::BM - 1) / C::BM, nt = N / C::OUT_N, tiles = (mt * nt + 7) / 8 * 8;
+  EpiStoreF32Rows epi{{P, N, static_cast<size_t>(T) * N}, tiles, T, d, j, static_cast<const bf16_t*>(hbar),
+                      static_cast<const bf16_t*>(prev1), static_cast<const bf16_t*>(prev2),
+                      static_cast<const bf16_t*>(norm_w), eps_norm, rowstat, static_cast<bf16_t*>(u)};
+  ARows<bf16_t> A{static_cast<const bf16_t*>(hbar), nullptr, d};
+  BRows<bf16_t> B{static_cast<const bf16_t*>(w_hd), static_cast<const bf16_t*>(ps1), d_e, d};
+  const dim3 grid(tiles + (T + splits - 1) / splits, splits);
+  mfma_gemm<C, EpiStoreF32Rows><<<grid, C::NT, 0, s>>>(A, B, epi, nullptr, T, d, mt, nt);
+  return hipGetLastError();
+}
+
 hipError_t launch_router_gemm(int dtype, const void* hbar, const void* w_hd, const void* ps1, int T,
                               int d, int d_e, int d_head, float* P, hipStream_t s) {
   const int N = d_e + d_head;
@@ -1528,32 +1814,52 @@ bool skinny_down_fits(int n_max, int d, int d_ff) {
   return n_max <= kSkinnyRows && d % (16 * kSkinnyDownNB) == 0 && d_ff % BK == 0;
 }
 
+// route (may be null): the launch is a routed decode step's (decode_route)
+struct GateUpCall {
+  ARows<bf16_t> A;
+  const bf16_t *wg, *wu, *tiled;
+  bf16_t* act;
+  const int* counts;
+  int n_max, d, d_ff;
+  const RouteArgs* route;
+};
+
 template <int NB, int RB>
-hipError_t skinny_gateup_nb_rb(ARows<bf16_t> A, const bf16_t* wg, const bf16_t* wu, const bf16_t* tiled,
-                               bf16_t* act, const int* counts, int n_max, int d, int d_ff, hipStream_t s) {
+hipError_t skinny_gateup_nb_rb(const GateUpCall& c, hipStream_t s) {
   using C = Skinny<NB, RB, 3, skinny_nsb(NB, RB, true, 3), true>;
-  const int nb = d_ff / 16, G = std::min(kCUs, nb);
-  if (tiled) return run_skinny<C>(A, tiled, nullptr, 0, nb, act, d_ff, 0, counts, n_max, d, nb, G, 1, s);
-  return run_skinny<C>(A, wg, wu, d, 0, act, d_ff, 0, counts, n_max, d, nb, G, 1, s);
+  const int nb = c.d_ff / 16;
+  const bf16_t *b0 = c.tiled ? c.tiled : c.wg, *b1 = c.tiled ? nullptr : c.wu;
+  const int ldb = c.tiled ? 0 : c.d, tiled = c.tiled ? nb : 0;
+  if (c.route) {
+    // as few workgroups as keep the most blocks of one, at least those the adapter leaves free
+    const int gmin = (nb + NB - 1) / NB;
+    const int G = std::min(nb, std::max(gmin, kCUs - c.route->na) / 8 * 8 >= gmin
+                                   ? std::max(gmin, kCUs - c.route->na) / 8 * 8 : gmin);
+    skinny_gemm<C, true><<<c.route->na + G, 512, 0, s>>>(c.A, b0, b1, ldb, tiled, c.act, c.d_ff, 0, nullptr, c.n_max,
+                                                         c.d, nb, G, 1, *c.route);
+    return hipGetLastError();
+  }
+  return run_skinny<C>(c.A, b0, b1, ldb, tiled, c.act, c.d_ff, 0, c.counts, c.n_max, c.d, nb, std::min(kCUs, nb), 1, s);
 }
 template <int NB>
-hipError_t skinny_gateup_nb(ARows<bf16_t> A, const bf16_t* wg, const bf16_t* wu, const bf16_t* tiled,
-                            bf16_t* act, const int* counts, int n_max, int d, int d_ff, hipStream_t s) {
-  switch ((n_max + 63) / 64) {
-    case 1: return skinny_gateup_nb_rb<NB, 1>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    case 2: return skinny_gateup_nb_rb<NB, 2>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    case 3: return skinny_gateup_nb_rb<NB, 3>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    default: return skinny_gateup_nb_rb<NB, 4>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
+hipError_t skinny_gateup_nb(const GateUpCall& c, hipStream_t s) {
+  switch ((c.n_max + 63) / 64) {
+    case 1: return skinny_gateup_nb_rb<NB, 1>(c, s);
+    case 2: return skinny_gateup_nb_rb<NB, 2>(c, s);
+    case 3: return skinny_gateup_nb_rb<NB, 3>(c, s);
+    default: return skinny_gateup_nb_rb<NB, 4>(c, s);
   }
 }
-hipError_t skinny_gateup(ARows<bf16_t> A, const bf16_t* wg, const bf16_t* wu, const bf16_t* tiled, bf16_t* act,
-                         const int* counts, int n_max, int d, int d_ff, hipStream_t s) {
+int skinny_gateup_blocks(int d_ff) {   // most blocks a workgroup takes
   const int nb = d_ff / 16, G = std::min(kCUs, nb);
-  switch ((nb + G - 1) / G) {   // most blocks a workgroup takes
-    case 1: return skinny_gateup_nb<1>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    case 2: return skinny_gateup_nb<2>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    case 3: return skinny_gateup_nb<3>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
-    default: return skinny_gateup_nb<4>(A, wg, wu, tiled, act, counts, n_max, d, d_ff, s);
+  return (nb + G - 1) / G;
+}
+hipError_t skinny_gateup(const GateUpCall& c, hipStream_t s) {
+  switch (skinny_gateup_blocks(c.d_ff)) {
+    case 1: return skinny_gateup_nb<1>(c, s);
+    case 2: return skinny_gateup_nb<2>(c, s);
+    case 3: return skinny_gateup_nb<3>(c, s);
+    default: return skinny_gateup_nb<4>(c, s);
   }
 }
 template <int RB>
@@ -1622,7 +1928,7 @@ __global__ __launch_bounds__(256) void swiglu_reduce(const float* __restrict__ P
 
 // h_out[t][n] = bf16(hbar[t][n] + g_t y) with y the sum over z < S of P[z][m][n], t = idx[m];
 // one thread per 8 columns of a row, rows m < *m_count
-__global__ __launch_bounds__(256) void scatter_reduce(const float* __restrict__ P, int S, size_t stride,
+__device__ __forceinline__ void scatter_reduce_block(int block, const float* __restrict__ P, int S, size_t stride,
                                                      const int* __restrict__ m_count, int n_max,
                                                      const int* __restrict__ idx,
                                                      const bf16_t* __restrict__ hbar,
@@ -1630,7 +1936,7 @@ __global__ __launch_bounds__(256) void scatter_reduce(const float* __restrict__ 
                                                      bf16_t* __restrict__ out, int d) {
   const int M = m_count ? min(*m_count, n_max) : n_max;
   const int q = d / 8;
-  const size_t e = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+  const size_t e = static_cast<size_t>(block) * 256 + threadIdx.x;
   const int m = static_cast<int>(e / q), n = static_cast<int>(e % q) * 8;
   if (m >= M) return;
   const float* p = P + static_cast<size_t>(m) * d + n;
@@ -1652,6 +1958,31 @@ __global__ __launch_bounds__(256) void scatter_reduce(const float* __restrict__ 
     w[i] = static_cast<uint32_t>(f32_to_bf16(lo)) | (static_cast<uint32_t>(f32_to_bf16(hi)) << 16);
   }
   *reinterpret_cast<u32x4*>(out + o) = w;
+}
+
+__global__ __launch_bounds__(256) void scatter_reduce(const float* __restrict__ P, int S, size_t stride,
+                                                     const int* __restrict__ m_count, int n_max,
+                                                     const int* __restrict__ idx,
+                                                     const bf16_t* __restrict__ hbar,
+                                                     const float* __restrict__ gate,
+                                                     bf16_t* __restrict__ out, int d) {
+  scatter_reduce_block(static_cast<int>(blockIdx.x), P, S, stride, m_count, n_max, idx, hbar, gate, out, d);
+}
+
+// The last launch of a routed decode step: the first up_blocks workgroups are the adapter's
+// up-projection (32 rows x 256 columns each, partials by token), the others scatter_reduce.  The
+// two write disjoint rows of h_out.
+template <int KR, int G>
+__global__ __launch_bounds__(256) void decode_finish(RouteFinish f) {
+  const int b = static_cast<int>(blockIdx.x);
+  if (b < f.up_blocks) {
+    const int nc = f.d / 256;
+    adapter_up_tile<KR, G, true>(f.part_ad, f.idx_ad, f.counts + 1, f.w2, f.hbar, f.gate, f.out, f.T, f.d,
+                                 b / nc * 32, b % nc * 256);
+  } else {
+    scatter_reduce_block(b - f.up_blocks, f.part, f.S, f.stride, f.counts, f.n_ffn_max, f.idx_ffn, f.hbar, f.gate,
+                         f.out, f.d);
+  }
 }
 
 // out[((kt NB + b) G + g) 16 + r][c] = W_g[16 b + r][64 kt + c] with NB = N / 16 blocks (w0: g = 0,
@@ -1707,9 +2038,9 @@ hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(u), idx_ffn, d};
     if (skinny_gateup_fits(n_max, d, d_ff))
-      return skinny_gateup(A, static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up),
-                           static_cast<const bf16_t*>(w_gate_up_tiled), static_cast<bf16_t*>(act), counts,
-                           n_max, d, d_ff, s);
+      return skinny_gateup({A, static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up),
+                            static_cast<const bf16_t*>(w_gate_up_tiled), static_cast<bf16_t*>(act), counts, n_max, d,
+                            d_ff, nullptr}, s);
     const int S = gateup_split(n_max, d, d_ff);
     if (S > 1) {
       BRows<bf16_t> B{static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up), d_ff, d};
@@ -2022,6 +2353,86 @@ hipError_t launch_adapter_up(int dtype, const float* part, const int* idx_ad, co
   EpiScatter<float, true> epi{idx_ad, static_cast<const float*>(hbar), gate,
                               static_cast<float*>(h_out), d};
   return run_f32<false>(A, B, epi, counts, n_max, d, d_r, s);
+}
+
+bool decode_route_fits(int dtype, int T, int n_ffn_max, int d, int d_ff, int d_r) {
+  return dtype == 1 && T <= kRouteTokens && n_ffn_max > 0 && !adapter_wide(d_r) && d % 256 == 0 &&
+         skinny_gateup_fits(n_ffn_max, d, d_ff) && skinny_down_fits(n_ffn_max, d, d_ff);
+}
+
+namespace {
+template <int KR>
+void decode_finish_launch(int G, int blocks, const RouteFinish& f, hipStream_t s) {
+  switch (G) {
+    case 1: decode_finish<KR, 1><<<blocks, 256, 0, s>>>(f); break;
+    case 2: decode_finish<KR, 2><<<blocks, 256, 0, s>>>(f); break;
+    case 4: decode_finish<KR, 4><<<blocks, 256, 0, s>>>(f); break;
+    default: decode_finish<KR, 8><<<blocks, 256, 0, s>>>(f); break;
+  }
+}
+
+// K-slices of the adapter's down-projection beside the gate/up product: the most that leave the
+// product's workgroups a CU each, in whole 16-deep steps for eight waves
+int route_slices(int T, int d, int d_ff) {
+  const int NB = skinny_gateup_blocks(d_ff), spare = kCUs - (d_ff / 16 + NB - 1) / NB;
+  const int tiles = (T + 31) / 32;
+  int G = adapter_groups(d);
+  while (G > 1 && (tiles * G > spare || d % (128 * G) != 0)) G >>= 1;
+  return G;
+}
+}  // namespace
+
+hipError_t launch_route_gateup(const DecodeRoute& r, hipStream_t s) {
+  RouteArgs ra{};
+  ra.sel = r.sel;
+  if (r.n_ad_max > 0) {
+    ra.slices = route_slices(r.sel.T, r.d, r.d_ff);
+    ra.na = ((r.sel.T + 31) / 32 * ra.slices + 7) / 8 * 8;
+    ra.d_r = r.d_r;
+    ra.u = static_cast<const bf16_t*>(r.u);
+    ra.w1 = static_cast<const bf16_t*>(r.w1);
+    ra.part = r.part_ad;
+  }
+  return skinny_gateup({ARows<bf16_t>{static_cast<const bf16_t*>(r.u), nullptr, r.d}, static_cast<const bf16_t*>(r.w_gate),
+                        static_cast<const bf16_t*>(r.w_up), static_cast<const bf16_t*>(r.w_gate_up_tiled),
+                        static_cast<bf16_t*>(r.act), nullptr, r.n_ffn_max, r.d, r.d_ff, &ra}, s);
+}
+
+hipError_t launch_route_down(const DecodeRoute& r, hipStream_t s) {
+  const int S = skinny_down_splits(r.d, r.d_ff);
+  return skinny_down(ARows<bf16_t>{static_cast<const bf16_t*>(r.act), nullptr, r.d_ff},
+                     static_cast<const bf16_t*>(r.w_down), static_cast<const bf16_t*>(r.w_down_tiled), r.part,
+                     static_cast<size_t>(r.n_ffn_max) * r.d, r.sel.counts, r.n_ffn_max, r.d, r.d_ff, S, s);
+}
+
+hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s) {
+  RouteFinish f{};
+  f.part_ad = r.part_ad;
+  f.idx_ad = r.sel.idx_ad;
+  f.idx_ffn = r.sel.idx_ffn;
+  f.counts = r.sel.counts;
+  f.w2 = static_cast<const bf16_t*>(r.w2);
+  f.hbar = static_cast<const bf16_t*>(r.hbar);
+  f.gate = r.gate;
+  f.out = static_cast<bf16_t*>(r.h_out);
+  f.T = r.sel.T;
+  f.d = r.d;
+  f.up_blocks = r.n_ad_max > 0 ? (r.n_ad_max + 31) / 32 * (r.d / 256) : 0;
+  f.part = r.part;
+  f.S = skinny_down_splits(r.d, r.d_ff);
+  f.n_ffn_max = r.n_ffn_max;
+  f.stride = static_cast<size_t>(r.n_ffn_max) * r.d;
+  const size_t n8 = static_cast<size_t>(r.n_ffn_max) * (r.d / 8);
+  const int blocks = f.up_blocks + static_cast<int>((n8 + 255) / 256);
+  const int G = route_slices(r.sel.T, r.d, r.d_ff);
+  switch (r.d_r) {
+    case 32: decode_finish_launch<32>(G, blocks, f, s); break;
+    case 64: decode_finish_launch<64>(G, blocks, f, s); break;
+    case 96: decode_finish_launch<96>(G, blocks, f, s); break;
+    case 128: decode_finish_launch<128>(G, blocks, f, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

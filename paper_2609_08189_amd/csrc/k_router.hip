@@ -25,6 +25,7 @@
 // with S stored in bf16) and is the HBM-bound part; keeping it free of the matrix-vector work lets many workgroups per
 // CU keep HBM busy.  All arithmetic is fp32.
 #include <algorithm>
+#include <type_traits>
 
 #include "hero_device.h"
 #include "hero_kernels.h"
@@ -1004,7 +1005,9 @@ __global__ __launch_bounds__(NT) void history_state_kernel(const float* __restri
 // barriers.  A matrix [O][I] is spread over the threads in pieces of eight inputs: thread t holds
 // piece t mod PI (PI >= I / 8, a power of two) of rows t / PI, t / PI + 512 / PI, ..., so it needs
 // the same eight inputs for every row, and a row's sum is formed over PI neighbouring lanes.
-// Weights are widened to fp32 and every product and sum is fp32.
+// Weights are widened to fp32 and every product and sum is fp32.  At 256 tokens of d_m = 128:
+// 14 us for the 31 us of the three kernels (4 us until the loads are out, 1 us for them, then the
+// chain of seven barriers).
 // ---------------------------------------------------------------------------
 constexpr int NTT = 512;                 // threads per token
 constexpr int NWT = NTT / kWave;
@@ -1022,41 +1025,59 @@ template <typename W, int PI, int R>
 struct TokenMat {
   Raw8<W> w[R];
   static constexpr int ROWS = NTT / PI;  // rows per pass
-  // row(o): first element of row o; zero past O rows and past I inputs (I % 8 == 0)
+  // row(o): first element of row o.  Threads past the O rows or the I inputs (I % 8 == 0) load the
+  // last ones instead of branching (a branch per load made the loads wait for one another)
   template <class Row>
   __device__ __forceinline__ void load(int O, int I, Row row) {
-    const int sl = static_cast<int>(threadIdx.x) % PI, o0 = static_cast<int>(threadIdx.x) / PI;
+    const int sl = min(static_cast<int>(threadIdx.x) % PI, I / 8 - 1), o0 = static_cast<int>(threadIdx.x) / PI;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int o = o0 + ROWS * r;
-      if (o < O && 8 * sl < I)
-        w[r].load(row(o) + 8 * sl);
-      else
-        w[r].zero();
-    }
+    for (int r = 0; r < R; ++r) w[r].load(row(min(o0 + ROWS * r, O - 1)) + 8 * sl);
   }
-  // f(o, sum) for every row o < O this thread's group holds, sum in all PI lanes of the group
+  // f(r, o, sum): lane l of a group gets the sums of the group's rows r = l, l + PI, ... below O, so
+  // that what follows a sum runs once per lane and not once per row in every lane
   template <class F>
-  __device__ __forceinline__ void dot(const float* x, int O, F f) const {
+  __device__ __forceinline__ void dot(const float* x, int O, int I, F f) const {
     const int sl = static_cast<int>(threadIdx.x) % PI, o0 = static_cast<int>(threadIdx.x) / PI;
+    const bool in = 8 * sl < I;
     float xv[8];
     *reinterpret_cast<f32x4*>(xv) = *reinterpret_cast<const f32x4*>(x + 8 * sl);
     *reinterpret_cast<f32x4*>(xv + 4) = *reinterpret_cast<const f32x4*>(x + 8 * sl + 4);
+    constexpr int G = (R + PI - 1) / PI;
+    float mine[G];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       float acc = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) acc = fmaf(w[r][e], xv[e], acc);
-      acc = group_sum<PI>(acc);
-      const int o = o0 + ROWS * r;
-      if (o < O) f(r, o, acc);
+      acc = group_sum<PI>(in ? acc : 0.f);
+      mine[r / PI] = r % PI == 0 || sl == r % PI ? acc : mine[r / PI];
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const int r = g * PI + sl, o = o0 + ROWS * r;
+      if (r < R && o < O) f(g, o, mine[g]);
     }
   }
 };
 
+// A kernel argument held in scalar registers from here on.  Pointers keep the global address space
+// (through a generic pointer the accesses would be flat ones).
+template <typename T>
+__device__ __forceinline__ T keep_scalar(T v) {
+  if constexpr (std::is_pointer<T>::value) {
+    typedef __attribute__((address_space(1))) typename std::remove_pointer<T>::type* G;
+    G g = (G)v;
+    asm volatile("" : "+s"(g));
+    return (T)g;
+  } else {
+    asm volatile("" : "+s"(v));
+    return v;
+  }
+}
+
 // HIST: the memory in depth-history form (kv, hw); otherwise the matrix S of storage type ST
 template <typename W, int DM, typename ST, bool HIST, bool PRE>
-__global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) {
+__global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs args) {
   constexpr int PM = DM / 8;                                   // pieces of a d_m-wide row
   constexpr int R_HU = kTokenMaxS * 32 / NTT, R_P2 = kTokenMaxS * 16 / NTT;
   constexpr int R_Q = 4 * DM * 8 / NTT > 0 ? 4 * DM * 8 / NTT : 1;
@@ -1081,84 +1102,100 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t t = blockIdx.x;
-  const int j = a.j, d_e = a.d_e, d_head = a.d_head, NP = d_e + d_head;
-  const int d_s = a.d_s, d_h = a.d_h, d_a = a.d_a, d_p = a.d_p;
-  const bool mem = !(a.abl & (ABL_NO_MEMREAD | ABL_NO_HISTORY));
+  // the arguments into scalar registers at once (read where they are used, each group of them is a
+  // round trip of its own)
+#define HERO_KEEP(x) const auto a_##x = keep_scalar(args.x)
+  HERO_KEEP(T); HERO_KEEP(j); HERO_KEEP(L_R); HERO_KEEP(d_s); HERO_KEEP(d_h); HERO_KEEP(d_a); HERO_KEEP(d_e);
+  HERO_KEEP(d_p); HERO_KEEP(d_head); HERO_KEEP(eps); HERO_KEEP(T_hist); HERO_KEEP(eta); HERO_KEEP(P);
+  HERO_KEEP(p_splits); HERO_KEEP(rowstat); HERO_KEEP(w_hu); HERO_KEEP(w_p1); HERO_KEEP(w_p2); HERO_KEEP(w_q);
+  HERO_KEEP(w_k); HERO_KEEP(w_v); HERO_KEEP(w_n); HERO_KEEP(w_c); HERO_KEEP(th1); HERO_KEEP(th2); HERO_KEEP(ps2);
+  HERO_KEEP(ld_th1); HERO_KEEP(beta); HERO_KEEP(abl); HERO_KEEP(S); HERO_KEEP(zeta); HERO_KEEP(p_hist);
+  HERO_KEEP(m_hist); HERO_KEEP(logit); HERO_KEEP(gate); HERO_KEEP(kv); HERO_KEEP(c_read);
+#undef HERO_KEEP
+  const int j = a_j, d_e = a_d_e, d_head = a_d_head, NP = d_e + d_head;
+  const int d_s = a_d_s, d_h = a_d_h, d_a = a_d_a, d_p = a_d_p;
+  const bool mem = !(a_abl & (ABL_NO_MEMREAD | ABL_NO_HISTORY));
   const bool ctx = j > 1 && mem;
 
-  // (1) every load of the kernel
+  // (1) every load of the kernel, none under a branch of its own
   float pv[MAXSPLIT];
+  const int pcol = min(tid, NP - 1);
 #pragma unroll
   for (int z = 0; z < MAXSPLIT; ++z)
-    pv[z] = tid < NP && z < a.p_splits ? a.P[(static_cast<size_t>(z) * a.T + t) * NP + tid] : 0.f;
-  const f32x4 rs = *reinterpret_cast<const f32x4*>(a.rowstat + 4 * t);
-  const float pprev = j > 1 ? a.p_hist[t] : 1.f, mprev = j > 1 ? a.m_hist[t] : 1.f;
-  const float beta = a.beta ? a.beta[t] : 0.f;
-  const W* w_p1 = static_cast<const W*>(a.w_p1);
+    pv[z] = a_P[(static_cast<size_t>(min(z, a_p_splits - 1)) * a_T + t) * NP + pcol];
+  const f32x4 rs = *reinterpret_cast<const f32x4*>(a_rowstat + 4 * t);
+  const float pprev = j > 1 ? a_p_hist[t] : 1.f, mprev = j > 1 ? a_m_hist[t] : 1.f;
+  const float beta = a_beta ? a_beta[t] : 0.f;
   W p1[6];
 #pragma unroll
-  for (int k = 0; k < 6; ++k) p1[k] = tid < d_p ? w_p1[tid * 6 + k] : W(0);
+  for (int k = 0; k < 6; ++k) p1[k] = static_cast<const W*>(a_w_p1)[min(tid, d_p - 1) * 6 + k];
   const bool head = tid >= d_e && tid < NP;
-  const W ps2 = head ? static_cast<const W*>(a.ps2)[tid - d_e] : W(0);
+  const W ps2 = static_cast<const W*>(a_ps2)[min(max(tid - d_e, 0), d_head - 1)];
   TokenMat<W, 32, R_HU> m_hu;
   TokenMat<W, 16, R_P2> m_p2;
   TokenMat<W, 8, R_Q> m_q;
   TokenMat<W, 8, R_TS> m_ts;
   TokenMat<W, PM, R_C> m_c;
   TokenMat<W, PM, R_TC> m_tc;
-  W wnu[R_TC], th2[R_TC];
+  // the history head's outputs this lane finishes (rows past the last: not used)
+  constexpr int G_TC = (R_TC + PM - 1) / PM;
+  W wnu[G_TC], th2[G_TC];
+  auto own = [&](int g) {
+    const int r = g * PM + tid % PM;
+    return r < R_TC ? tid / PM + NTT / PM * r : MAXE;
+  };
   auto load_hu = [&] {
-    m_hu.load(d_h, d_e, [&](int o) { return static_cast<const W*>(a.w_hu) + o * d_e; });
-    m_p2.load(d_a, d_p, [&](int o) { return static_cast<const W*>(a.w_p2) + o * d_p; });
+    m_hu.load(d_h, d_e, [&](int o) { return static_cast<const W*>(a_w_hu) + o * d_e; });
+    m_p2.load(d_a, d_p, [&](int o) { return static_cast<const W*>(a_w_p2) + o * d_p; });
   };
   auto load_s = [&] {
     m_q.load(4 * DM, d_s, [&](int o) {
       const int m = o / DM;
-      const void* w = m == 0 ? a.w_q : m == 1 ? a.w_k : m == 2 ? a.w_v : a.w_n;
+      const void* w = m == 0 ? a_w_q : m == 1 ? a_w_k : m == 2 ? a_w_v : a_w_n;
       return static_cast<const W*>(w) + (o - m * DM) * d_s;
     });
-    m_ts.load(d_head, d_s, [&](int o) { return static_cast<const W*>(a.th1) + o * a.ld_th1; });
+    m_ts.load(d_head, d_s, [&](int o) { return static_cast<const W*>(a_th1) + o * a_ld_th1; });
   };
   auto load_c = [&] {
-    m_c.load(DM, DM, [&](int o) { return static_cast<const W*>(a.w_c) + o * DM; });
-    m_tc.load(d_head, DM, [&](int o) { return static_cast<const W*>(a.th1) + o * a.ld_th1 + d_s; });
+    m_c.load(DM, DM, [&](int o) { return static_cast<const W*>(a_w_c) + o * DM; });
+    m_tc.load(d_head, DM, [&](int o) { return static_cast<const W*>(a_th1) + o * a_ld_th1 + d_s; });
 #pragma unroll
-    for (int r = 0; r < R_TC; ++r) {
-      const int o = tid / PM + NTT / PM * r;
-      wnu[r] = o < d_head ? static_cast<const W*>(a.th1)[o * a.ld_th1 + d_s + DM] : W(0);
-      th2[r] = o < d_head ? static_cast<const W*>(a.th2)[o] : W(0);
+    for (int g = 0; g < G_TC; ++g) {
+      const int o = min(own(g), d_head - 1);
+      wnu[g] = static_cast<const W*>(a_th1)[o * a_ld_th1 + d_s + DM];
+      th2[g] = static_cast<const W*>(a_th2)[o];
     }
   };
   // the token's memory: S rows rg, rg + RP, ... (columns VE cq ..), or the wave's pairs
   const int cq = tid % CV, rg = tid / CV;
   const bool on = rg < DM;
-  ST* Sp = HIST ? nullptr : static_cast<ST*>(a.S) + t * DM * DM + VE * cq;
+  ST* Sp = HIST ? nullptr : static_cast<ST*>(a_S) + t * DM * DM + VE * cq;
   u32x4 sv[HIST ? 1 : CH];
   auto load_mem = [&](int i0) {
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
-      if (on) sv[c] = *reinterpret_cast<const u32x4*>(Sp + (rg + RP * (i0 + c)) * DM);
+    for (int c = 0; c < CH; ++c) sv[c] = *reinterpret_cast<const u32x4*>(Sp + (min(rg, DM - 1) + RP * (i0 + c)) * DM);
   };
-  float* H = HIST ? a.kv + t * a.L_R * 2 * DM : nullptr;
+  float* H = HIST ? a_kv + t * a_L_R * 2 * DM : nullptr;
   const int np = j - 1;                       // stored pairs
   const bool hl = lane * EPL < DM;
-  float hk[HIST ? HPW : 1][EPL], hv[HIST ? HPW : 1][EPL];
+  float hk[HIST ? HPW : 1][EPL], hv[HIST ? HPW : 1][EPL];   // the last pair stands in past np, unused
   float zv = 0.f;
-  if constexpr (HIST) {
-    if (mem) {
+  auto load_pairs = [&] {
 #pragma unroll
-      for (int u = 0; u < HPW; ++u) {
-        const int i = wave + NWT * u;
+    for (int u = 0; u < (HIST ? HPW : 0); ++u) {
+      const float* h = H + static_cast<size_t>(max(min(wave + NWT * u, np - 1), 0)) * 2 * DM + min(lane * EPL, DM - EPL);
 #pragma unroll
-        for (int x = 0; x < EPL; ++x) {
-          hk[u][x] = i < np && hl ? H[static_cast<size_t>(i) * 2 * DM + lane * EPL + x] : 0.f;
-          hv[u][x] = i < np && hl ? H[static_cast<size_t>(i) * 2 * DM + DM + lane * EPL + x] : 0.f;
-        }
+      for (int x = 0; x < EPL; ++x) {
+        hk[u][x] = h[x];
+        hv[u][x] = h[DM + x];
       }
     }
+  };
+  if constexpr (HIST) {
+    if (PRE && mem) load_pairs();
   } else if (ctx) {
     if constexpr (PRE && NR == CH) load_mem(0);
-    if (tid < DM) zv = a.zeta[t * DM + tid];
+    zv = a_zeta[t * DM + min(tid, DM - 1)];
   }
   if constexpr (PRE) {
     load_hu();
@@ -1169,7 +1206,7 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
   // (2) SiLU of the pre-activations, the local head's shares, the path encoder's hidden layer
   float p = pv[0];
 #pragma unroll
-  for (int z = 1; z < MAXSPLIT; ++z) p += pv[z];
+  for (int z = 1; z < MAXSPLIT; ++z) p += z < a_p_splits ? pv[z] : 0.f;
   if (tid < d_e) xs[tid] = siluf_(rs[0] * p);
   const float bsum = wave_sum(head ? ldf(&ps2) * siluf_(p) : 0.f);
   if (lane == 0) bpart[wave] = bsum;
@@ -1178,10 +1215,10 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
     float h = 0.f;
     if (tid < d_p) {
       const float dj = j >= 2 ? sqrtf(rs[1]) : 0.f;
-      const float gam = j >= 3 ? rs[2] / (dj * sqrtf(rs[3]) + a.eps) : 0.f;
-      const bool pos = !(a.abl & ABL_NO_POS);
-      const float xp[6] = {pos ? static_cast<float>(j) / static_cast<float>(a.L_R) : 0.f,
-                           pos ? static_cast<float>(a.L_R - j) / static_cast<float>(a.L_R) : 0.f,
+      const float gam = j >= 3 ? rs[2] / (dj * sqrtf(rs[3]) + a_eps) : 0.f;
+      const bool pos = !(a_abl & ABL_NO_POS);
+      const float xp[6] = {pos ? static_cast<float>(j) / static_cast<float>(a_L_R) : 0.f,
+                           pos ? static_cast<float>(a_L_R - j) / static_cast<float>(a_L_R) : 0.f,
                            pos ? dj : 0.f, pos ? gam : 0.f, pprev, mprev};
 #pragma unroll
       for (int k = 0; k < 6; ++k) h = fmaf(ldf(&p1[k]), xp[k], h);
@@ -1194,22 +1231,16 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
   __syncthreads();
 
   // (3) s = [z_h; z_a]
-  m_hu.dot(xs, d_h, [&](int, int o, float v) {
-    if (tid % 32 == 0) s[o] = v;
-  });
-  m_p2.dot(hp, d_a, [&](int, int o, float v) {
-    if (tid % 16 == 0) s[d_h + o] = a.abl & ABL_NO_AUX ? 0.f : v;
-  });
+  m_hu.dot(xs, d_h, d_e, [&](int, int o, float v) { s[o] = v; });
+  m_p2.dot(hp, d_a, d_p, [&](int, int o, float v) { s[d_h + o] = a_abl & ABL_NO_AUX ? 0.f : v; });
   if constexpr (!PRE) load_s();
   __syncthreads();
 
   // (4) phi(q), phi(k), v, W_n s and the s part of the history head
-  m_q.dot(s, 4 * DM, [&](int, int o, float v) {
-    if (tid % 8 == 0) pr[o / DM][o % DM] = o < 2 * DM ? phif_(v) : v;
+  m_q.dot(s, 4 * DM, d_s, [&](int, int o, float v) {
+    pr[o / DM][o % DM] = o < 2 * DM ? phif_(v) : v;
   });
-  m_ts.dot(s, d_head, [&](int, int o, float v) {
-    if (tid % 8 == 0) hs[o] = v;
-  });
+  m_ts.dot(s, d_head, d_s, [&](int, int o, float v) { hs[o] = v; });
   if constexpr (!PRE) load_c();
   __syncthreads();
 
@@ -1219,6 +1250,7 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
 #pragma unroll
     for (int x = 0; x < EPL; ++x) c[x] = 0.f;
     if (mem) {
+      if (!PRE) load_pairs();
 #pragma unroll
       for (int u = 0; u < HPW; ++u) {
         const int i = wave + NWT * u;
@@ -1227,7 +1259,7 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
 #pragma unroll
           for (int x = 0; x < EPL; ++x)
             if (hl) d = fmaf(pr[0][lane * EPL + x], hk[u][x], d);
-          const float al = a.hw[i] * wave_sum(d);
+          const float al = args.hw[i] * wave_sum(d);
           den += al;
 #pragma unroll
           for (int x = 0; x < EPL; ++x) c[x] = fmaf(al, hv[u][x], c[x]);
@@ -1240,11 +1272,11 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
 #pragma unroll
       for (int x = 0; x < EPL; ++x) red[wave][lane * EPL + x] = c[x];
   } else {
-    const float rho = 1.0f / (1.0f + expf(-a.eta));
+    const float rho = 1.0f / (1.0f + expf(-a_eta));
     float d = 0.f;
     if (mem && tid < DM) {
       d = pr[0][tid] * zv;
-      a.zeta[t * DM + tid] = fmaf(rho, zv, pr[1][tid]);
+      a_zeta[t * DM + tid] = fmaf(rho, zv, pr[1][tid]);
     }
     d = wave_sum(d);
     if (lane == 0) dpart[wave] = d;
@@ -1254,9 +1286,22 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
       vr[e] = pr[2][VE * cq + e];
       cacc[e] = 0.f;
     }
-    if (mem && on) {
+    auto store = [&](int r, const float* o) {
+      u32x4 w;
+      if constexpr (VE == 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(o[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          w[e] = static_cast<uint32_t>(f32_to_bf16(o[2 * e])) |
+                 (static_cast<uint32_t>(f32_to_bf16(o[2 * e + 1])) << 16);
+      }
+      *reinterpret_cast<u32x4*>(Sp + r * DM) = w;
+    };
+    if (ctx && on) {
       for (int i0 = 0; i0 < NR; i0 += CH) {
-        if (ctx && !(PRE && NR == CH)) load_mem(i0);
+        if (!(PRE && NR == CH)) load_mem(i0);
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
           const int r = rg + RP * (i0 + c);
@@ -1264,28 +1309,24 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
           float o[VE];
 #pragma unroll
           for (int e = 0; e < VE; ++e) {
-            float x = 0.f;
-            if (ctx) {
-              if constexpr (VE == 4)
-                x = __uint_as_float(sv[c][e]);
-              else
-                x = __uint_as_float(e & 1 ? sv[c][e >> 1] & 0xffff0000u : sv[c][e >> 1] << 16);
-            }
+            float x;
+            if constexpr (VE == 4)
+              x = __uint_as_float(sv[c][e]);
+            else
+              x = __uint_as_float(e & 1 ? sv[c][e >> 1] & 0xffff0000u : sv[c][e >> 1] << 16);
             cacc[e] = fmaf(qv, x, cacc[e]);
-            o[e] = ctx ? fmaf(rho, x, kv * vr[e]) : kv * vr[e];
+            o[e] = fmaf(rho, x, kv * vr[e]);
           }
-          u32x4 w;
-          if constexpr (VE == 4) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(o[e]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              w[e] = static_cast<uint32_t>(f32_to_bf16(o[2 * e])) |
-                     (static_cast<uint32_t>(f32_to_bf16(o[2 * e + 1])) << 16);
-          }
-          *reinterpret_cast<u32x4*>(Sp + r * DM) = w;
+          store(r, o);
         }
+      }
+    } else if (mem && on) {
+      for (int i = 0; i < NR; ++i) {
+        const int r = rg + RP * i;
+        float o[VE];
+#pragma unroll
+        for (int e = 0; e < VE; ++e) o[e] = pr[1][r] * vr[e];
+        store(r, o);
       }
     }
     if (on)
@@ -1299,25 +1340,23 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
     for (int g = 0; g < NRED; ++g) c += red[g][tid];
 #pragma unroll
     for (int w = 0; w < NWT; ++w) den += dpart[w];
-    c = ctx ? c / (den + a.eps) : 0.f;
+    c = ctx ? c / (den + a_eps) : 0.f;
     cv[tid] = c;
-    if (a.c_read && mem) a.c_read[t * DM + tid] = c;
+    if (a_c_read && mem) a_c_read[t * DM + tid] = c;
   }
   __syncthreads();
 
   // (6) W_c c beside W_n s for nu; the c part of the history head
-  float nn = 0.f, cc = 0.f, nc = 0.f, pre[R_TC];
-  m_c.dot(cv, DM, [&](int, int o, float v) {
+  float nn = 0.f, cc = 0.f, nc = 0.f, pre[G_TC];
+  m_c.dot(cv, DM, DM, [&](int, int o, float v) {
     const float n = pr[3][o];
-    if (tid % PM == 0) {
-      nn = fmaf(n, n, nn);
-      cc = fmaf(v, v, cc);
-      nc = fmaf(n, v, nc);
-    }
+    nn = fmaf(n, n, nn);
+    cc = fmaf(v, v, cc);
+    nc = fmaf(n, v, nc);
   });
 #pragma unroll
-  for (int r = 0; r < R_TC; ++r) pre[r] = 0.f;
-  m_tc.dot(cv, d_head, [&](int r, int o, float v) { pre[r] = v + hs[o]; });
+  for (int g = 0; g < G_TC; ++g) pre[g] = 0.f;
+  m_tc.dot(cv, d_head, DM, [&](int g, int o, float v) { pre[g] = v + hs[o]; });
   nn = wave_sum(nn);
   cc = wave_sum(cc);
   nc = wave_sum(nc);
@@ -1332,16 +1371,16 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
   for (int w = 0; w < NWT; ++w)
 #pragma unroll
     for (int e = 0; e < 3; ++e) tot[e] += npart[w][e];
-  const float nu = ctx ? 1.0f - tot[2] / (sqrtf(tot[0]) * sqrtf(tot[1]) + a.eps) : 0.f;
+  const float nu = ctx ? 1.0f - tot[2] / (sqrtf(tot[0]) * sqrtf(tot[1]) + a_eps) : 0.f;
   float av = 0.f;
 #pragma unroll
-  for (int r = 0; r < R_TC; ++r)   // rows past d_head have th2 = 0
-    av = fmaf(ldf(&th2[r]), siluf_(fmaf(ldf(&wnu[r]), nu, pre[r])), av);
-  av = wave_sum(tid % PM == 0 ? av : 0.f);
+  for (int g = 0; g < G_TC; ++g)
+    if (own(g) < d_head) av = fmaf(ldf(&th2[g]), siluf_(fmaf(ldf(&wnu[g]), nu, pre[g])), av);
+  av = wave_sum(av);
   if (lane == 0) apart[wave] = av;
   __syncthreads();
   if (tid == 0) {
-    const bool hist = !(a.abl & ABL_NO_HISTORY);
+    const bool hist = !(a_abl & ABL_NO_HISTORY);
     float aa = 0.f, b = 0.f;
 #pragma unroll
     for (int w = 0; w < NWT; ++w) {
@@ -1349,12 +1388,12 @@ __global__ __launch_bounds__(NTT, 2) void router_token_kernel(RouterTailArgs a) 
       b += bpart[w];
     }
     if (!hist) aa = 0.f;
-    const float ph = sigmoidf_(aa / a.T_hist);
-    a.p_hist[t] = hist ? ph : 1.0f;
-    a.m_hist[t] = hist ? mprev * ph : 1.0f;
+    const float ph = sigmoidf_(aa / a_T_hist);
+    a_p_hist[t] = hist ? ph : 1.0f;
+    a_m_hist[t] = hist ? mprev * ph : 1.0f;
     const float l = aa + b + beta;
-    a.logit[t] = l;
-    a.gate[t] = sigmoidf_(l);
+    a_logit[t] = l;
+    a_gate[t] = sigmoidf_(l);
   }
 }
 

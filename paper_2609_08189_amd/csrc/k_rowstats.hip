@@ -10,85 +10,102 @@
 // The transition sums are only formed where the paper defines them (j >= 2, j >= 3).
 #include "hero_device.h"
 #include "hero_kernels.h"
+#include "hero_rows.h"
 
 namespace hero {
 
-// One workgroup per token, its row split over the 4 waves (8 elements per lane per pass, up to
-// four passes kept in registers for the normalisation), the four sums reduced across the waves
-// through LDS.  Measured against four tokens per workgroup (one per wave): 26.8 against 28.4 us at
-// 4096 tokens of d = 4096, 7.2 against 13.6 us at 256 tokens, where a wave per row left most CUs idle.
 template <typename T>
-__global__ __launch_bounds__(256) void rowstats_row_kernel(const T* __restrict__ hbar,
-                                                           const T* __restrict__ prev1,
-                                                           const T* __restrict__ prev2,
-                                                           const T* __restrict__ norm_w, int d, int j,
-                                                           float eps_norm, float* __restrict__ rowstat,
+__global__ __launch_bounds__(256) void rowstats_row_kernel(const T* __restrict__ hbar, const T* __restrict__ prev1,
+                                                           const T* __restrict__ prev2, const T* __restrict__ norm_w,
+                                                           int d, int j, float eps_norm, float* __restrict__ rowstat,
                                                            T* __restrict__ u) {
-  __shared__ f32x4 part[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t row = static_cast<size_t>(blockIdx.x) * d;
-  constexpr int RC = 4;   // 8-element chunks per thread kept in registers (rows up to 8192)
-  Raw8<T> h[RC];
-  float ss = 0.f, dd = 0.f, dp = 0.f, pp = 0.f;
-  const bool resident = d <= RC * 8 * 256;
-  for (int c0 = 0; c0 < d; c0 += RC * 8 * 256) {
-    Raw8<T> a[RC], b[RC];
-#pragma unroll
-    for (int c = 0; c < RC; ++c) {
-      const int col = c0 + 8 * (tid + 256 * c);
-      if (col < d) {
-        h[c].load(hbar + row + col);
-        if (j >= 2) a[c].load(prev1 + row + col);
-        if (j >= 3) b[c].load(prev2 + row + col);
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < RC; ++c) {
-      const int col = c0 + 8 * (tid + 256 * c);
-      if (col >= d) continue;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float hv = h[c][i];
-        ss += hv * hv;
-        if (j >= 2) {
-          const float av = a[c][i];
-          const float dj = hv - av;
-          dd += dj * dj;
-          if (j >= 3) {
-            const float dq = av - b[c][i];
-            dp += dj * dq;
-            pp += dq * dq;
-          }
-        }
-      }
-    }
+  rowstats_row<T, 256>(static_cast<int>(blockIdx.x), hbar, prev1, prev2, norm_w, d, j, eps_norm, rowstat, u);
+}
+
+// ---------------------------------------------------------------------------
+// The head of a decode step's layer (at most 256 tokens, bf16): the router's pre-activation
+// product P = hbar [W_hd; psi_1]^T and the row pass read the same rows and nothing of each other,
+// so one launch holds both.  The product streams 4 MiB of weights for few rows: up to 64 tokens
+// here, workgroups of 16 columns x one of the kHeadSplits K-slices, then one workgroup per token
+// row (beyond, the 64 x 128 tiles of launch_router_gemm, whose fragments go through LDS).  Waves
+// are four blocks of 16 tokens by two halves of the K-slice, added through LDS; the fragments come
+// straight from memory, BS k-steps of 32 in one batch.  One 8B layer at 1 token: 10.4 us for the
+// tiles, the row pass beside them on a second stream, -> 4.5 us for both.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr int kHeadTokens = 64, kHeadSplits = 4, kHeadBatch = 16;
+
+__global__ __launch_bounds__(512) void decode_head_kernel(const bf16_t* __restrict__ hbar,
+                                                          const bf16_t* __restrict__ prev1,
+                                                          const bf16_t* __restrict__ prev2,
+                                                          const bf16_t* __restrict__ norm_w,
+                                                          const bf16_t* __restrict__ w_hd,
+                                                          const bf16_t* __restrict__ ps1, int T, int d, int d_e, int N,
+                                                          int j, float eps_norm, float* __restrict__ P,
+                                                          float* __restrict__ rowstat, bf16_t* __restrict__ u) {
+  constexpr int BS = kHeadBatch;
+  const int ncb = N / 16, ng = ncb * kHeadSplits;
+  const int b = static_cast<int>(blockIdx.x);
+  if (b >= ng) {
+    rowstats_row<bf16_t, 512>(b - ng, hbar, prev1, prev2, norm_w, d, j, eps_norm, rowstat, u);
+    return;
   }
-  ss = wave_sum(ss);
-  dd = wave_sum(dd);
-  dp = wave_sum(dp);
-  pp = wave_sum(pp);
-  if (lane == 0) part[wave] = f32x4{ss, dd, dp, pp};
+  __shared__ f32x4 red[4][kWave];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int rg = wave & 3, half = wave >> 2;
+  const int cb = b % ncb, sl = b / ncb;
+  const int kn = d / kHeadSplits / 2, k0 = sl * (d / kHeadSplits) + half * kn;
+  const int kq = 8 * (lane >> 4), n = 16 * cb + (lane & 15);
+  const bf16_t* brow = (n < d_e ? w_hd + static_cast<size_t>(n) * d : ps1 + static_cast<size_t>(n - d_e) * d) + k0 + kq;
+  const bf16_t* arow = hbar + static_cast<size_t>(min(16 * rg + (lane & 15), T - 1)) * d + k0 + kq;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (16 * rg < T)
+    for (int kb = 0; kb < kn; kb += 32 * BS) {
+      // steps past the slice load its last one again and are not used
+      bf16x8 fb[BS], fa[BS];
+#pragma unroll
+      for (int i = 0; i < BS; ++i) {
+        const int k = min(kb + 32 * i, kn - 32);
+        fb[i] = *reinterpret_cast<const bf16x8*>(brow + k);
+        fa[i] = *reinterpret_cast<const bf16x8*>(arow + k);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < BS; ++i)
+        if (kb + 32 * i < kn) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[i], acc, 0, 0, 0);
+    }
+  if (half == 1) red[rg][lane] = acc;
   __syncthreads();
-  const f32x4 tot = part[0] + part[1] + part[2] + part[3];
-  const float inv_rms = 1.0f / sqrtf(tot[0] / static_cast<float>(d) + eps_norm);
-  if (tid == 0) {
-    f32x4 r = {inv_rms, tot[1], tot[2], tot[3]};
-    *reinterpret_cast<f32x4*>(rowstat + 4 * static_cast<size_t>(blockIdx.x)) = r;
-  }
-  for (int c0 = 0; c0 < d; c0 += RC * 8 * 256) {
+  if (half == 1) return;
+  acc += red[rg][lane];
+  float* out = P + static_cast<size_t>(sl) * T * N + n;
 #pragma unroll
-    for (int c = 0; c < RC; ++c) {
-      const int col = c0 + 8 * (tid + 256 * c);
-      if (col >= d) continue;
-      if (!resident) h[c].load(hbar + row + col);
-      Raw8<T> w;
-      w.load(norm_w + col);
-      float o[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = h[c][i] * inv_rms * w[i];
-      st8(u + row + col, o);
-    }
+  for (int r = 0; r < 4; ++r) {
+    const int t = 16 * rg + 4 * (lane >> 4) + r;
+    if (t < T) out[static_cast<size_t>(t) * N] = acc[r];
   }
+}
+}  // namespace
+
+bool decode_head_fits(int dtype, int T, int d, int d_e, int N) {
+  return dtype == 1 && T <= kDecodeTokens && d % (64 * kHeadSplits) == 0 && d_e % 16 == 0 && N % 16 == 0 &&
+         router_gemm_splits(dtype, d, T, N) == kHeadSplits && (T <= kHeadTokens || decode_head_tiles_fit(N));
+}
+
+hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                              const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                              float eps_norm, float* P, float* rowstat, void* u, hipStream_t s) {
+  if (T <= 0) return hipSuccess;
+  if (T > kHeadTokens)
+    return launch_decode_head_tiles(hbar, prev1, prev2, norm_w, w_hd, ps1, T, d, d_e, d_head, j, eps_norm, P, rowstat,
+                                    u, s);
+  const int N = d_e + d_head;
+  decode_head_kernel<<<N / 16 * kHeadSplits + T, 512, 0, s>>>(
+      static_cast<const bf16_t*>(hbar), static_cast<const bf16_t*>(prev1), static_cast<const bf16_t*>(prev2),
+      static_cast<const bf16_t*>(norm_w), static_cast<const bf16_t*>(w_hd), static_cast<const bf16_t*>(ps1), T, d, d_e,
+      N, j, eps_norm, P, rowstat, static_cast<bf16_t*>(u));
+  return hipGetLastError();
 }
 
 hipError_t launch_rowstats(int dtype, const void* hbar, const void* prev1, const void* prev2,

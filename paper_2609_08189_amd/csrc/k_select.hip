@@ -21,13 +21,6 @@ namespace {
 constexpr int NT = 1024;
 constexpr int NW = NT / 64;
 
-// order-preserving image of an fp32 value (-0 and +0 map to the same key)
-__device__ __forceinline__ uint32_t okey(float f) {
-  uint32_t b = __float_as_uint(f);
-  if (b == 0x80000000u) b = 0u;
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
 __device__ __forceinline__ int lane_prefix(unsigned long long bal, int lane) {
   return __popcll(bal & ((1ull << lane) - 1ull));
 }
@@ -94,7 +87,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
       const uint32_t prefix = s_prefix;
       for_chunks<R>(T, [&](int r, int t) {
         if (t < T) {
-          const uint32_t key = okey(lg.at(a.logit, r, t));
+          const uint32_t key = order_key(lg.at(a.logit, r, t));
           if (shift == 24 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
             atomicAdd(&hist[(key >> shift) & 255u], 1u);
         }
@@ -137,7 +130,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     int run = 0;
     for_chunks<R>(T, [&](int r, int t) {
       if (run >= k) return;   // uniform: every thread holds the same run
-      const bool pred = t < T && okey(lg.at(a.logit, r, t)) == vstar;
+      const bool pred = t < T && order_key(lg.at(a.logit, r, t)) == vstar;
       const unsigned long long bal = __ballot(pred);
       if (lane == 0) wcount[wave] = __popcll(bal);
       __syncthreads();
@@ -164,7 +157,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     if (valid) {
       const float l = lg.at(a.logit, r, t);
       if (budget) {
-        const uint32_t key = okey(l);
+        const uint32_t key = order_key(l);
         const bool skip = a.n_skip > 0 && (key < vstar || (key == vstar && t <= tstar));
         ffn = !skip;
       } else {
@@ -299,7 +292,7 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
       uint32_t cnt = 0;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const uint32_t key = okey(v[r]);
+        const uint32_t key = order_key(v[r]);
         if (hi >= 32 || (key >> hi) == (prefix >> hi)) {
           const int dgt = static_cast<int>((key >> shift) & dmask);
           if (dgt == last) {
@@ -344,7 +337,7 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
     const int k = s_k;
     int neq = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) neq += okey(v[r]) == vstar ? 1 : 0;
+    for (int r = 0; r < R; ++r) neq += order_key(v[r]) == vstar ? 1 : 0;
     int tot;
     const int eq_before = block_exclusive_scan(neq, wsum, &tot);
     if (tid == 0) s_tstar = -1;
@@ -353,7 +346,7 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
       int seen = eq_before;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        if (okey(v[r]) == vstar) {
+        if (order_key(v[r]) == vstar) {
           ++seen;
           if (seen == k) s_tstar = t0 + r;
         }
@@ -373,7 +366,7 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
       const int t = t0 + r;
       bool ffn;
       if (budget) {
-        const uint32_t key = okey(v[r]);
+        const uint32_t key = order_key(v[r]);
         ffn = !(a.n_skip > 0 && (key < vstar || (key == vstar && t <= tstar)));
       } else {
         ffn = v[r] >= a.thr;

@@ -1,0 +1,46 @@
+"""A routed decode step's folded launches (row pass with the router's product; decision and adapter down-projection in
+the gate/up launch; adapter up-projection with the down product's reduction) at the edges of their layouts, against
+the oracle: token counts around the 16-, 32- and 64-row blocks, every narrow adapter rank, all tokens on one branch."""
+import numpy as np
+import pytest
+
+from paper_2609_08189_amd import synth
+from tests.parity import check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(T, d=256, d_ff=384, d_r=32, mode="budget", budget=0.3, beta=None, tiled=True):
+    from paper_2609_08189_amd.device import DeviceProblem
+    print(f"case T={T} d={d} d_ff={d_ff} d_r={d_r} mode={mode} budget={budget}", flush=True)
+    w = synth.Workload("decode_route", "bf16", d=d, d_ff=d_ff, d_r=d_r, L_R=8, d_m=32, T=T, mode=mode, budget=budget,
+                       bias="spread")
+    prob = synth.make_problem(w, seed=T, layer_j=3)
+    if beta is not None:
+        prob.beta = np.full(T, beta, np.float32)
+    dp = DeviceProblem(prob, tiled=tiled)
+    dp.run_layer(3)
+    check_layer(prob, dp.results(), 3)
+
+
+@pytest.mark.parametrize("mode", ["budget", "threshold"])
+@pytest.mark.parametrize("T", [1, 16, 17, 33, 64, 65, 129, 255, 256])
+def test_token_counts(T, mode):
+    _layer(T, mode=mode)
+
+
+@pytest.mark.parametrize("d_r", [64, 96, 128])
+@pytest.mark.parametrize("d,d_ff", [(256, 128), (1280, 1408), (2048, 4224)])
+def test_ranks_and_widths(d, d_ff, d_r):
+    _layer(100, d, d_ff, d_r, tiled=False)
+
+
+@pytest.mark.parametrize("T", [1, 70])
+@pytest.mark.parametrize("beta", [-50.0, 50.0])
+def test_threshold_one_branch(T, beta):
+    _layer(T, mode="threshold", beta=beta)
+
+
+@pytest.mark.parametrize("budget", [0.0, 1.0])
+def test_budget_one_branch(budget):
+    _layer(70, budget=budget)
