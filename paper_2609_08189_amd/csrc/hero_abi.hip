@@ -466,12 +466,12 @@ int run_layer(const LayerCall& c) {
   if (n_ffn_max > 0) {
     e = timed(HERO_K_FFN_GATE_UP, st, [&] {
       return launch_ffn_gateup(D.dtype, u, idx_ffn, counts, n_ffn_max, c.ffn->w_gate, c.ffn->w_up,
-                               c.ffn->w_gate_up_tiled, act, part, D.d, D.d_ff, st);
+                               c.ffn->w_gate_up_tiled, act, part, D.d, D.d_ff, c.rc->mode == HERO_MODE_BUDGET, st);
     });
     if (e != hipSuccess) return HERO_E_LAUNCH;
     e = timed(HERO_K_FFN_DOWN, st, [&] {
       return launch_ffn_down(D.dtype, act, idx_ffn, counts, n_ffn_max, c.ffn->w_down, c.ffn->w_down_tiled,
-                             c.hbar, gate, c.h_out, part, D.d, D.d_ff, st);
+                             c.hbar, gate, c.h_out, part, D.d, D.d_ff, c.rc->mode == HERO_MODE_BUDGET, st);
     });
     if (e != hipSuccess) return HERO_E_LAUNCH;
   }
@@ -913,12 +913,12 @@ int run_dense_ffn(const hero_dims& dm, int T, const void* hbar, void* h, const h
   if (e != hipSuccess) return HERO_E_LAUNCH;
   e = timed(HERO_K_FFN_GATE_UP, st, [&] {
     return launch_ffn_gateup(dm.dtype, u, nullptr, nullptr, T, f.w_gate, f.w_up, f.w_gate_up_tiled, act, part,
-                             dm.d, dm.d_ff, st);
+                             dm.d, dm.d_ff, true, st);
   });
   if (e != hipSuccess) return HERO_E_LAUNCH;
   e = timed(HERO_K_FFN_DOWN, st, [&] {
     return launch_ffn_down(dm.dtype, act, nullptr, nullptr, T, f.w_down, f.w_down_tiled, hbar, nullptr, h, part,
-                           dm.d, dm.d_ff, st);
+                           dm.d, dm.d_ff, true, st);
   });
   return e == hipSuccess ? HERO_OK : HERO_E_LAUNCH;
 }
@@ -1271,17 +1271,17 @@ int hero_routed_block_backward(const hero_dims* dims, int T, const void* hbar, c
   });
   if (err != hipSuccess) return HERO_E_LAUNCH;
   err = timed(HERO_K_BWD_FFN_E, s, [&] {
-    return launch_ffn_bwd_e(D.dtype, dh_out, idx_f, cnt, nf_max, ffn_t->w_down_t, e, D.d, D.d_ff, s);
+    return launch_ffn_bwd_e(D.dtype, dh_out, idx_f, cnt, nf_max, ffn_t->w_down_t, e, D.d, D.d_ff, budget, s);
   });
   if (err != hipSuccess) return HERO_E_LAUNCH;
   err = timed(HERO_K_BWD_FFN_GATE_UP, s, [&] {
     return launch_ffn_bwd_gateup(D.dtype, u, idx_f, cnt, nf_max, ffn->w_gate, ffn->w_up, e, gate, dgu,
-                                 const_cast<float*>(a.dgpart), D.d, D.d_ff, s);
+                                 const_cast<float*>(a.dgpart), D.d, D.d_ff, budget, s);
   });
   if (err != hipSuccess) return HERO_E_LAUNCH;
   err = timed(HERO_K_BWD_FFN_DU, s, [&] {
     return launch_ffn_bwd_du(D.dtype, dgu, cnt, nf_max, ffn_t->w_gate_up_t, const_cast<float*>(a.du_f), D.d,
-                             D.d_ff, s);
+                             D.d_ff, budget, s);
   });
   if (err != hipSuccess) return HERO_E_LAUNCH;
   err = timed(HERO_K_BWD_ADAPTER, s, [&] {

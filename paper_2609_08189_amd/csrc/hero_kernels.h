@@ -107,15 +107,17 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s);
 size_t ffn_part_floats(int dtype, int d, int d_ff, int T);
 // w_gate_up_tiled (may be null): W_g and W_u in the streaming order of launch_tile_ffn_weights,
 // read instead of w_gate, w_up by the products of at most 256 rows.
+// exact: n_max is the row count itself (budget routing); otherwise an upper bound of counts[0],
+// and the large products choose their tiles on the device.
 hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const int* counts,
                              int n_max, const void* w_gate, const void* w_up, const void* w_gate_up_tiled,
-                             void* act, float* part, int d, int d_ff, hipStream_t s);
+                             void* act, float* part, int d, int d_ff, bool exact, hipStream_t s);
 // FFN branch, down + scatter: h_out[t] = hbar[t] + g[t] * (W_d act[m]), t = idx_ffn[m].
 // w_down_tiled (may be null): W_d in the streaming order, read instead of w_down by the products
 // of at most 256 rows.
 hipError_t launch_ffn_down(int dtype, const void* act, const int* idx_ffn, const int* counts,
                            int n_max, const void* w_down, const void* w_down_tiled, const void* hbar,
-                           const float* gate, void* h_out, float* part, int d, int d_ff, hipStream_t s);
+                           const float* gate, void* h_out, float* part, int d, int d_ff, bool exact, hipStream_t s);
 // A routed decode step after the router, in three launches: the branch decision and the adapter's
 // down-projection beside the gate/up product; the down product; its reduction and scatter beside
 // the adapter's up-projection.  For bf16 calls of at most 256 tokens with a FFN row for certain or
@@ -187,16 +189,16 @@ hipError_t launch_adapter_transpose(int dtype, const void* w1, const void* w2, v
                                     int rpad, hipStream_t s);
 // e[m] = dL/dh[idx_ffn[m]] W_d (W_d^T given, [d_ff][d]), storage dtype, [n][d_ff]
 hipError_t launch_ffn_bwd_e(int dtype, const void* dh, const int* idx_ffn, const int* counts, int n_max,
-                            const void* w_down_t, void* e, int d, int d_ff, hipStream_t s);
+                            const void* w_down_t, void* e, int d, int d_ff, bool exact, hipStream_t s);
 // G, U recomputed from u[idx_ffn[m]]; dgu[m] = [dG | dU] (storage dtype, [n][2 d_ff]) and
 // dgpart[m][p] = the p-th share of <e_m, act_m> (swiglu_bwd_parts(dtype, d_ff) per row)
 int swiglu_bwd_parts(int dtype, int d_ff);
 hipError_t launch_ffn_bwd_gateup(int dtype, const void* u, const int* idx_ffn, const int* counts, int n_max,
                                  const void* w_gate, const void* w_up, const void* e, const float* gate,
-                                 void* dgu, float* dgpart, int d, int d_ff, hipStream_t s);
+                                 void* dgu, float* dgpart, int d, int d_ff, bool exact, hipStream_t s);
 // du[m] = dgu[m] [W_g; W_u] (([W_g; W_u])^T given, [d][2 d_ff]), fp32 [n][d]
 hipError_t launch_ffn_bwd_du(int dtype, const void* dgu, const int* counts, int n_max, const void* w_gate_up_t,
-                             float* du, int d, int d_ff, hipStream_t s);
+                             float* du, int d, int d_ff, bool exact, hipStream_t s);
 // part[z][m][n] (z < adapter_proj_splits, slices n_max d_r floats apart): K-slice partial sums
 // of rows[idx_ad[m]] W^T for W [d_r][d] (adapter_part_floats(dtype, d, d_r, n_max) floats)
 int adapter_proj_splits(int dtype, int d, int d_r);

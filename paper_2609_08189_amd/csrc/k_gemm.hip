@@ -245,74 +245,38 @@ constexpr int kCUs = 256;    // compute units of an MI355X
 // instruction classes of __builtin_amdgcn_sched_group_barrier
 constexpr int SG_MFMA = 0x008, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100;
 
-// An epilogue with a block() member takes each staged 32-row block of a wave tile whole,
-// instead of 8-column row pieces through emit8().
-template <class E, class = void>
-struct BlockEpilogue : std::false_type {};
-template <class E>
-struct BlockEpilogue<E, std::void_t<decltype(&E::block)>> : std::true_type {};
-// A two-product epilogue with kDualHook takes the gate/up accumulators of a finished wave tile
-// itself (the backward of the gated SwiGLU) instead of the forward's SiLU(gate) * up staging.
-template <class E, class = void>
-struct DualHook : std::false_type {};
-template <class E>
-struct DualHook<E, std::void_t<decltype(E::kDualHook)>> : std::true_type {};
-
 // An epilogue with kRows brings the row pass of a decode step along (EpiStoreF32Rows)
 template <class E, class = void>
 struct RowsHook : std::false_type {};
 template <class E>
 struct RowsHook<E, std::void_t<decltype(E::kRows)>> : std::true_type {};
 
-template <class C, class Epi>
-__device__ __forceinline__ void swiglu_bwd_tile(const Epi& epi, f32x16 (&acc)[C::TM][C::TN], unsigned char* smem, int m0,
-                                int nt, int wave, int wm, int wn, int M, int lane);
-
 // NS_: LDS stages of the k-loop; the loads of tile k + NS - 1 are in flight while tile k is
-// consumed (2 for the big products, more where streaming weights from HBM needs more bytes in
-// flight per CU).
-// MI_: the matrix instruction, v_mfma_f32_32x32x16_bf16 (32) or v_mfma_f32_16x16x32_bf16 (16).
-// Both run at the same nominal rate; on random data the 16 x 16 x 32 form sustains a markedly
-// higher clock under the board's power limit (2.20 against 1.83-1.91 PFLOP/s in a register-only
-// loop on all CUs), so the FFN products use it.
-template <int BM_, int BN_, int WM_, int WN_, bool DUAL_, int NS_ = 2, int MI_ = 32>
+// consumed (2 where the operands sit in L2, more where streaming weights from HBM needs more bytes
+// in flight per CU).
+template <int BM_, int BN_, int WM_, int WN_, int NS_ = 2>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-  static constexpr bool DUAL = DUAL_;
   static constexpr int NS = NS_;
-  static constexpr int MI = MI_;
-  static constexpr int NACC = MI * MI / 64;           // accumulator registers per MFMA tile
-  using Acc = typename std::conditional<MI == 32, f32x16, f32x4>::type;
-  static constexpr int KSTEP = MI == 32 ? 16 : 32;    // k per MFMA
+  static constexpr int KSTEP = 16;                    // k per MFMA
   static constexpr int NT = 64 * WM * WN;
   static constexpr int NW = WM * WN;
   static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int TM = WTM / MI, TN = WTN / MI;
+  static constexpr int TM = WTM / 32, TN = WTN / 32;
   static constexpr int STAGE = (BM + BN) * ROWB;
-  static constexpr int OUT_N = DUAL ? BN / 2 : BN;   // output columns per tile
-  static constexpr int ON = DUAL ? WTN / 2 : WTN;     // output columns per wave
-  static constexpr int OPAD = ON + 4;                 // fp32 staging row pitch (floats)
-  static constexpr int SPAD = ON + 8;                 // bf16 staging row pitch (elements)
-  static_assert(MI == 32 || MI == 16, "matrix instruction");
-  static_assert(WTM % MI == 0 && WTN % MI == 0, "wave tile must be whole MFMA tiles");
-  static_assert(!DUAL || TN % 2 == 0, "gate/up tiles come in pairs");
+  static constexpr int OUT_N = BN;                    // output columns per tile
+  static constexpr int OPAD = WTN + 4;                // fp32 staging row pitch (floats)
+  static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole MFMA tiles");
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "loader split");
-  static_assert(DUAL ? NW * WTM * SPAD * 2 <= 2 * STAGE : NW * MI * OPAD * 4 <= 2 * STAGE,
-                "epilogue staging must fit in the stages");
-  static_assert((MI * (ON / 8)) % 64 == 0, "epilogue pieces split evenly over the lanes");
+  static_assert(NW * 32 * OPAD * 4 <= 2 * STAGE, "epilogue staging must fit in the stages");
+  static_assert((32 * (WTN / 8)) % 64 == 0, "epilogue pieces split evenly over the lanes");
   static_assert(NS >= 2 && NS * STAGE <= 160 * 1024, "stages fit in LDS");
 };
 
 // Lane layout of the two matrix instructions (wave64).  Operands: lane l holds 8 consecutive k of
 // row (l mod MI) of its 16 x 32 (MI 16) or 32 x 16 (MI 32) block, at k-chunk l / MI.  Result:
-// element r of lane l is row frag_out_row(r, l), column (l mod MI) of the MI x MI tile.
-template <int MI>
-__device__ __forceinline__ int out_row(int r, int lane) {
-  if constexpr (MI == 32)
-    return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-  else
-    return 4 * (lane >> 4) + r;
-}
+// element r of lane l is row 4 (l / 16) + r (MI 16) or out_row32(r, l) (MI 32), column l mod MI.
+__device__ __forceinline__ int out_row32(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 template <int MI>
 __device__ __forceinline__ int in_chunk(int ks, int lane) {   // 16-byte chunk of a 128-byte row
   if constexpr (MI == 32)
@@ -342,7 +306,7 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
   constexpr int A_LD = C::BM / 8 / NW;  // wave-wide loads per k-tile, A
   constexpr int B_LD = C::BN / 8 / NW;
   constexpr int KS = BK / C::KSTEP;     // k-steps per k-tile
-  constexpr int MI = C::MI;
+  constexpr int MI = 32;
   constexpr int NM = C::TM * C::TN;     // MFMAs per k-step
   constexpr int NR = C::TM + C::TN;     // fragment reads per k-step
   constexpr int NL = A_LD + B_LD;       // stage loads per k-tile
@@ -401,18 +365,9 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
     const int blk = i * NW + wave;  // 8-row block, wave-uniform
     const int r = 8 * blk + rsub;
     const int ch = (lane & 7) ^ ((r >> 1) & 7);
-    const bf16_t* base;
-    int row;
-    if constexpr (C::DUAL) {
-      const int wb = (8 * blk) / C::WTN, q0 = (8 * blk) % C::WTN, h = C::WTN / 2;
-      const bool up = q0 >= h;
-      base = up ? B.b1 : B.b0;
-      row = nt * C::OUT_N + wb * h + (r % C::WTN) - (up ? h : 0);
-    } else {
-      const bool second = nt * C::BN + 8 * blk >= B.split;
-      base = second ? B.b1 : B.b0;
-      row = nt * C::BN + r - (second ? B.split : 0);
-    }
+    const bool second = nt * C::BN + 8 * blk >= B.split;
+    const bf16_t* base = second ? B.b1 : B.b0;
+    const int row = nt * C::BN + r - (second ? B.split : 0);
     b_base[i] = reinterpret_cast<const unsigned char*>(base);
     b_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(B.ld * 2) + ch * 16;
   }
@@ -427,13 +382,13 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
       load_lds16(b_base[i] + b_off[i] + kb, sa + C::BM * ROWB + (i * NW + wave) * 1024);
   };
 
-  typename C::Acc acc[C::TM][C::TN];
+  f32x16 acc[C::TM][C::TN];
 #pragma unroll
   for (int a = 0; a < C::TM; ++a)
 #pragma unroll
     for (int b = 0; b < C::TN; ++b)
 #pragma unroll
-      for (int r = 0; r < C::NACC; ++r) acc[a][b][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
   int fa_row[C::TM], fb_row[C::TN];
 #pragma unroll
@@ -517,362 +472,477 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if constexpr (DualHook<Epi>::value) {
-    static_assert(MI == 32, "the backward SwiGLU epilogue takes 32 x 32 accumulator tiles");
-    swiglu_bwd_tile<C>(epi, acc, smem, m0, nt, wave, wm, wn, M, lane);
-  } else if constexpr (C::DUAL) {
-    // the wave's finished tile, SiLU(gate) * up in bf16, staged at once
-    bf16_t* stg = reinterpret_cast<bf16_t*>(smem) + wave * (C::WTM * C::SPAD);
+  constexpr int CPR = C::WTN / 8;                 // 8-column pieces per staged row
+  constexpr int PPB = 32 * CPR / kWave;           // pieces per lane per 32-row block
+  // what the epilogue combines with (hbar rows) is fetched for the whole wave tile ahead of the
+  // staging, so those loads are in flight together
+  typename Epi::Pre pre[C::TM][PPB];
 #pragma unroll
-    for (int a = 0; a < C::TM; ++a)
+  for (int a = 0; a < C::TM; ++a)
 #pragma unroll
-      for (int r = 0; r < C::NACC; ++r) {
-        const int i = a * MI + out_row<MI>(r, lane);
+    for (int q = 0; q < PPB; ++q) {
+      const int e = lane + kWave * q;
+      const int m = m0 + wm * C::WTM + a * 32 + e / CPR;
+      pre[a][q] = epi.prep(min(m, M - 1), nt * C::OUT_N + wn * C::WTN + (e % CPR) * 8);
+    }
+  float* stg = reinterpret_cast<float*>(smem) + wave * (32 * C::OPAD);
 #pragma unroll
-        for (int b = 0; b < C::TN / 2; ++b) {
-          const float g = acc[a][b][r], u = acc[a][b + C::TN / 2][r];
-          stg[i * C::SPAD + b * MI + (lane & (MI - 1))] =
-              f32_to_bf16(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
-        }
-      }
-    constexpr int CPR = C::ON / 8;                 // 8-column pieces per row
-    constexpr int PPL = C::WTM * CPR / kWave;      // pieces per lane
+  for (int a = 0; a < C::TM; ++a) {
 #pragma unroll
-    for (int q = 0; q < PPL; ++q) {
+    for (int r = 0; r < 16; ++r) {
+      const int i = out_row32(r, lane);
+#pragma unroll
+      for (int b = 0; b < C::TN; ++b) stg[i * C::OPAD + b * 32 + (lane & 31)] = acc[a][b][r];
+    }
+#pragma unroll
+    for (int q = 0; q < PPB; ++q) {
       const int e = lane + kWave * q;
       const int i = e / CPR, c8 = (e % CPR) * 8;
-      const int m = m0 + wm * C::WTM + i;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(stg + i * C::SPAD + c8);
-      if (m < M) epi.emit_packed(m, nt * C::OUT_N + wn * C::ON + c8, v);
-    }
-  } else {
-    constexpr int CPR = C::ON / 8;                 // 8-column pieces per staged row
-    constexpr int PPB = MI * CPR / kWave;          // pieces per lane per MI-row block
-    // what the epilogue combines with (hbar rows) is fetched ahead of the staging, so those loads
-    // are in flight together: the whole wave tile with 32 x 32 tiles, 64 rows ahead with 16 x 16
-    // tiles (whose narrower blocks would otherwise hold twice the registers)
-    constexpr int AHEAD = MI == 32 ? C::TM : ((64 / MI) < C::TM ? (64 / MI) : C::TM);
-    typename Epi::Pre pre[C::TM][PPB];
-    auto fetch = [&](int a) {
-#pragma unroll
-      for (int q = 0; q < PPB; ++q) {
-        const int e = lane + kWave * q;
-        const int m = m0 + wm * C::WTM + a * MI + e / CPR;
-        pre[a][q] = epi.prep(min(m, M - 1), nt * C::OUT_N + wn * C::ON + (e % CPR) * 8);
-      }
-    };
-#pragma unroll
-    for (int a = 0; a < AHEAD; ++a) fetch(a);
-    float* stg = reinterpret_cast<float*>(smem) + wave * (MI * C::OPAD);
-#pragma unroll
-    for (int a = 0; a < C::TM; ++a) {
-      if (a + AHEAD < C::TM) fetch(a + AHEAD);
-#pragma unroll
-      for (int r = 0; r < C::NACC; ++r) {
-        const int i = out_row<MI>(r, lane);
-#pragma unroll
-        for (int b = 0; b < C::TN; ++b) stg[i * C::OPAD + b * MI + (lane & (MI - 1))] = acc[a][b][r];
-      }
-      if constexpr (BlockEpilogue<Epi>::value) {
-        static_assert(MI == 32, "block epilogues take 32-row blocks");
-        // the epilogue takes the whole staged 32-row block (any lane may read any element)
-        epi.block(stg, C::OPAD, C::ON, m0 + wm * C::WTM + a * 32, nt * C::OUT_N + wn * C::ON, M, lane);
-      } else {
-#pragma unroll
-        for (int q = 0; q < PPB; ++q) {
-          const int e = lane + kWave * q;
-          const int i = e / CPR, c8 = (e % CPR) * 8;
-          const int m = m0 + wm * C::WTM + a * MI + i;
-          if (m < M) epi.emit8(pre[a][q], m, nt * C::OUT_N + wn * C::ON + c8, stg + i * C::OPAD + c8);
-        }
-      }
+      const int m = m0 + wm * C::WTM + a * 32 + i;
+      if (m < M) epi.emit8(pre[a][q], m, nt * C::OUT_N + wn * C::WTN + c8, stg + i * C::OPAD + c8);
     }
   }
 }
 
-// Backward SwiGLU epilogue of one wave tile (EpiSwiGLUBwd on the MFMA path).  Lane (lane & 31)
-// holds column b 32 + (lane & 31) of gate tile b and of up tile b + TN/2, at rows
-// a 32 + 8 (r >> 2) + 4 (lane >> 5) + (r & 3) for accumulator element r.  The wave's own LDS
-// region (the stages are free once the k-loop has ended) holds in turn the rows' gates, the
-// per-lane shares of <e, act> (one lane then sums each row), and the bf16 staging of dG, then
-// dU, which leave as 16-byte row pieces.  A wave's LDS operations complete in order, so the
-// region needs no barrier between these uses.
+// ---------------------------------------------------------------------------
+// The large bf16 products: BM x 256 tiles (BM 256, 192 or 128) on v_mfma_f32_16x16x32_bf16, eight
+// waves, two per SIMD, each with two 16 HM-row by two 32-column blocks: rows from either half of
+// the A tile, columns from either half of the B tile (the gate/up product: W_g, then W_u).
+//   * A k-tile is four products of a half by a half.  Each half is read from LDS into registers
+//     one product ahead, so a half of a stage is free again half a k-tile after its k-tile began,
+//     and its loads for k-tile kt + 2 are issued then: they have one to one and a half k-tiles to
+//     land (half a k-tile to one with whole stages), and the waits leave 8 of them in flight.  Two
+//     barriers a k-tile.
+//   * The loads write the LDS that the fragment reads read, so the compiler keeps their order:
+//     they are written in the order they shall issue in, one between two MFMAs.  Issued as a burst
+//     ahead of the reads (the order of the source before), the same loop lost all of its gain.
+//   * The 16 x 16 x 32 instruction: at the same nominal rate as 32 x 32 x 16 it sustains a higher
+//     clock on random data under the board's power limit.
+// What bounds it is that limit: on zero operands the Llama-3.1-8B gate/up product (4096 rows) runs
+// at 1.84 PFLOP/s (the loop with whole stages: 1.57), on random ones at 1.44 (1.38); 20047 rows
+// 3510 -> 3390 us, its down product 1845 -> 1760 us, 2995 rows on 192-row tiles 550 -> 525 and
+// 265 -> 257 us.  Four waves of 128 x 128 (a third fewer LDS reads) reached 1.39.
+// Epilogues: the gate/up products finish in registers and stage bf16; the others stage 16-row
+// blocks in fp32 and take 8-column pieces (emit8) or the whole block (block).
+// A grid with gridDim.y = S > 1 splits K as mfma_gemm does.
+// ---------------------------------------------------------------------------
+
+// An epilogue with a block() member takes each staged block of 16 rows whole, instead of 8-column
+// row pieces through emit8().
+template <class E, class = void>
+struct BlockEpilogue : std::false_type {};
+template <class E>
+struct BlockEpilogue<E, std::void_t<decltype(&E::block)>> : std::true_type {};
+// A two-product epilogue with kDualHook takes the accumulators of a finished wave tile itself (the
+// backward of the gated SwiGLU) instead of the forward's SiLU(gate) * up staging.
+template <class E, class = void>
+struct DualHook : std::false_type {};
+template <class E>
+struct DualHook<E, std::void_t<decltype(E::kDualHook)>> : std::true_type {};
+
+template <int BM_, bool DUAL_>
+struct Phase {
+  static constexpr int WN = 4, NW = 8, NT = 512;
+  static constexpr int HB = 2;                  // 16-column fragments per wave and half
+  static constexpr int BM = BM_, BN = 256;
+  static constexpr bool DUAL = DUAL_;
+  static constexpr int HM = BM / 64;            // 16-row fragments per wave and half
+  static constexpr int STAGE = (BM + BN) * ROWB;
+  static constexpr int OUT_N = DUAL ? 128 : 256;
+  static constexpr int A_LD = BM / 8 / NW;      // 1 KiB stage loads per wave: A
+  static constexpr int A1 = BM / 16 / NW;       // ... of the first half alone
+  static constexpr int BH = 16 / NW;            // ... of half of B
+  static constexpr int L1 = A1 + BH, L2 = A_LD - A1 + BH;
+  static constexpr int SPLIT = A_LD % 2;        // loads of the second group that the first half needs too
+  static constexpr int ON = 32;                 // output columns per wave and half
+};
+
 template <class C, class Epi>
-__device__ __forceinline__ void swiglu_bwd_tile(const Epi& epi, f32x16 (&acc)[C::TM][C::TN], unsigned char* smem, int m0,
-                                int nt, int wave, int wm, int wn, int M, int lane) {
-  static_assert(C::DUAL, "gate/up tiles");
-  constexpr int TM = C::TM, TH = C::TN / 2, WTM = C::WTM;
-  constexpr int PP = 33;   // row pitch of the per-lane shares (floats): rows hit distinct banks
-  constexpr int RP = (WTM + WTM * PP) * 4, RS = WTM * C::SPAD * 2;
-  constexpr int REG = ((RP > RS ? RP : RS) + 15) / 16 * 16;
-  static_assert(C::NW * REG <= C::NS * C::STAGE, "backward staging fits in the stages");
-  unsigned char* reg = smem + wave * REG;
-  float* gl = reinterpret_cast<float*>(reg);
-  float* pr = gl + WTM;
-  const int rw = m0 + wm * WTM;                   // first row of the wave tile
-  const int col0 = nt * C::OUT_N + wn * C::ON;    // first output column of the wave
-  for (int i = lane; i < WTM; i += kWave) {
-    const int m = min(rw + i, M - 1);
-    const int t = epi.idx ? epi.idx[m] : m;
-    gl[i] = epi.gate ? epi.gate[t] : 1.0f;
-  }
-#pragma unroll
-  for (int a = 0; a < TM; ++a) {
-    // e at this lane's elements of the 32-row block, the loads in flight together: held as the
-    // loaded 16-bit words and widened at use (widening at the load let the compiler wait for each
-    // load in turn: 694 -> 798 us for the 8B layer's recompute)
-    bf16_t ev[16][TH];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = min(rw + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), M - 1);
-#pragma unroll
-      for (int b = 0; b < TH; ++b) ev[r][b] = epi.e[static_cast<size_t>(m) * epi.ld_e + col0 + b * 32 + (lane & 31)];
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const float gt = gl[i];
-      float sum = 0.f;
-#pragma unroll
-      for (int b = 0; b < TH; ++b) {
-        const float g = acc[a][b][r], u = acc[a][b + TH][r];
-        const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-g));
-        const float ee = bf16_to_f32(ev[r][b]);
-        const float dact = gt * ee;
-        sum += ee * (g * sg * u);
-        acc[a][b][r] = dact * u * sg * (1.0f + g * (1.0f - sg));   // dG
-        acc[a][b + TH][r] = dact * g * sg;                          // dU
-      }
-      pr[i * PP + (lane & 31)] = sum;
-    }
-  }
-  for (int i = lane; i < WTM; i += kWave) {
-    float v = 0.f;
-#pragma unroll 8
-    for (int c = 0; c < 32; ++c) v += pr[i * PP + c];
-    if (rw + i < M) epi.dgpart[static_cast<size_t>(rw + i) * epi.n_parts + col0 / C::ON] = v;
-  }
-  bf16_t* stg = reinterpret_cast<bf16_t*>(reg);
-  constexpr int CPR = C::ON / 8, PPL = WTM * CPR / kWave;
-  static_assert(WTM * CPR % kWave == 0, "pieces split evenly over the lanes");
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int i = a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-#pragma unroll
-        for (int b = 0; b < TH; ++b) stg[i * C::SPAD + b * 32 + (lane & 31)] = f32_to_bf16(acc[a][b + h * TH][r]);
-      }
-#pragma unroll
-    for (int q = 0; q < PPL; ++q) {
-      const int e = lane + kWave * q;
-      const int i = e / CPR, c8 = (e % CPR) * 8;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(stg + i * C::SPAD + c8);
-      if (rw + i < M)
-        *reinterpret_cast<u32x4*>(epi.dgu + static_cast<size_t>(rw + i) * epi.ld_dgu + h * epi.d_ff + col0 + c8) = v;
-    }
-  }
-}
+__device__ __forceinline__ void swiglu_bwd_tile(const Epi& epi, f32x4 (&acc)[2 * C::HM][4], unsigned char* smem, int m0,
+                                                int nt, int wave, int wm, int wn, int M, int lane);
 
-// ---------------------------------------------------------------------------
-// Persistent gate/up product.  The plain kernel ends every tile with an epilogue during
-// which the CU does no MFMA work, and all CUs reach it together, once per round of tiles.
-// Here one workgroup per CU walks the tiles its XCD owns (the same grouped order and
-// XCD ranges as mfma_gemm, workgroup q of an XCD taking every nq-th tile of the range);
-// a finished tile is staged as bf16 SiLU(gate) * up in a third LDS region and written
-// out at the start of the next tile's first k-tile, after its loads are in flight, so the
-// stores overlap that tile's MFMAs.  Each wave stages and stores only its own block, so the
-// staging region needs no barrier.  Results are identical to mfma_gemm's.
-// ---------------------------------------------------------------------------
-template <class C>
-__global__ __launch_bounds__(C::NT) void gateup_persist(ARows<bf16_t> A, BRows<bf16_t> B,
-                                                       EpiSwiGLU<bf16_t> epi,
-                                                       const int* __restrict__ m_count, int M_fixed,
-                                                       int K, int mt_max, int n_tiles) {
-  static_assert(C::DUAL, "gate/up only");
-  constexpr int NW = C::NW;
-  constexpr int A_LD = C::BM / 8 / NW;
-  constexpr int B_LD = C::BN / 8 / NW;
-  constexpr int KS = BK / C::KSTEP;
-  constexpr int MI = C::MI;
-  constexpr int NM = C::TM * C::TN;
-  constexpr int NR = C::TM + C::TN;
-  constexpr int NL = A_LD + B_LD;
-  constexpr int OUT_W = C::WTM * C::ON;            // staged bf16 elements per wave
-  constexpr int CPR = C::ON / 8;                   // 16-byte pieces per staged row
-  constexpr int PPL = C::WTM * CPR / kWave;        // pieces per lane
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * C::STAGE + NW * OUT_W * 2];
-  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3, nq = gridDim.x >> 3;
-  const int M = m_count ? *m_count : M_fixed;
-  const int mt_act = min(mt_max, (M + C::BM - 1) / C::BM);   // row tiles that exist
-  const int total = mt_act * n_tiles;
-  const int per = (total + 7) >> 3;                           // tiles per XCD
+template <class C, class Epi>
+__device__ __forceinline__ void phase_tile(const ARows<bf16_t>& A, const BRows<bf16_t>& B, const Epi& epi, int M,
+                                           int M_max, int K, int n_tiles, unsigned char* smem) {
+  constexpr int BM = C::BM, HM = C::HM, HB = C::HB, NW = C::NW, BH = C::BH;
+  const int mt_max = (M_max + BM - 1) / BM;
+  const int mt_act = min(mt_max, (M + BM - 1) / BM);
+  const int per = (mt_act * n_tiles + 7) >> 3;
+  const int q = blockIdx.x >> 3;
+  if (q >= per) return;
+  const int tile = (blockIdx.x & 7) * per + q;
+  if (tile >= mt_act * n_tiles) return;
+  const int grp = tile / (GROUP_M * n_tiles), rem = tile % (GROUP_M * n_tiles);
+  const int gsz = min(GROUP_M, mt_act - grp * GROUP_M);
+  const int mt = grp * GROUP_M + rem % gsz, nt = rem / gsz;
+  const int m0 = mt * BM;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN;
   const int rsub = lane >> 3;
-  bf16_t* ostg = reinterpret_cast<bf16_t*>(smem + 2 * C::STAGE) + wave * OUT_W;
-  const int nk = K / BK;
 
-  int fa_row[C::TM], fb_row[C::TN];
+  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A.base);
+  uint32_t a_off[C::A_LD], b_off[2 * BH];
 #pragma unroll
-  for (int a = 0; a < C::TM; ++a) fa_row[a] = wm * C::WTM + a * MI + (lane & (MI - 1));
+  for (int i = 0; i < C::A_LD; ++i) {
+    const int r = 8 * (i * NW + wave) + rsub;
+    const int ch = (lane & 7) ^ ((r >> 1) & 7);
+    const int m = min(m0 + r, M - 1);
+    const int row = A.idx ? A.idx[m] : m;
+    a_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(A.ld * 2) + ch * 16;
+  }
+  const unsigned char* b_base[2 * BH];
 #pragma unroll
-  for (int b = 0; b < C::TN; ++b) fb_row[b] = C::BM + wn * C::WTN + b * MI + (lane & (MI - 1));
-  bf16x8 fa[2][C::TM], fb[2][C::TN];
-  typename C::Acc acc[C::TM][C::TN];
-  auto read_frags = [&](int buf, const unsigned char* st, int ks) {
-    const int c = in_chunk<MI>(ks, lane);
+  for (int i = 0; i < 2 * BH; ++i) {
+    const int blk = 8 * (i * NW + wave);   // first of eight rows, wave-uniform
+    const int r = blk + rsub;
+    const int ch = (lane & 7) ^ ((r >> 1) & 7);
+    const bool second = C::DUAL ? blk >= 128 : nt * 256 + blk >= B.split;
+    const int row = C::DUAL ? nt * 128 + (r & 127) : nt * 256 + r - (second ? B.split : 0);
+    b_base[i] = reinterpret_cast<const unsigned char*>(second ? B.b1 : B.b0);
+    b_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(B.ld * 2) + ch * 16;
+  }
+  // split K: workgroup y covers k-tiles [y nkt / S, (y + 1) nkt / S), at least two
+  const int nkt = K / BK;
+  const int kt0 = static_cast<int>(blockIdx.y) * nkt / static_cast<int>(gridDim.y);
+  const int nk = (static_cast<int>(blockIdx.y) + 1) * nkt / static_cast<int>(gridDim.y) - kt0;
 #pragma unroll
-    for (int a = 0; a < C::TM; ++a) fa[buf][a] = *reinterpret_cast<const bf16x8*>(st + swz(fa_row[a], c));
+  for (int i = 0; i < C::A_LD; ++i) a_off[i] += kt0 * ROWB;
 #pragma unroll
-    for (int b = 0; b < C::TN; ++b) fb[buf][b] = *reinterpret_cast<const bf16x8*>(st + swz(fb_row[b], c));
+  for (int i = 0; i < 2 * BH; ++i) b_off[i] += kt0 * ROWB;
+  auto ldA = [&](int i, int stage, uint32_t kb) {
+    load_lds16((a_base + kb) + a_off[i], smem + stage * C::STAGE + (i * NW + wave) * 1024);
   };
-  auto mfmas = [&](int buf) {
-#pragma unroll
-    for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-      for (int b = 0; b < C::TN; ++b)
-        acc[a][b] = mfma_op(fa[buf][a], fb[buf][b], acc[a][b]);
+  auto ldB = [&](int i, int stage, uint32_t kb) {
+    load_lds16((b_base[i] + kb) + b_off[i], smem + stage * C::STAGE + BM * ROWB + (i * NW + wave) * 1024);
   };
-  auto interleave = [&](auto nl_, auto nr_) {
-    constexpr int nl = decltype(nl_)::value, nr = decltype(nr_)::value;
+  // group 1: the first half of A and B; group 2: the rest (the piece of A that both halves share first)
+  auto ld1 = [&](int i, int kt) { i < C::A1 ? ldA(i, kt & 1, kt * ROWB) : ldB(i - C::A1, kt & 1, kt * ROWB); };
+  auto ld2 = [&](int i, int kt) {
+    i < C::A_LD - C::A1 ? ldA(C::A1 + i, kt & 1, kt * ROWB) : ldB(BH + i - (C::A_LD - C::A1), kt & 1, kt * ROWB);
+  };
+
+  f32x4 acc[2 * HM][2 * HB];
 #pragma unroll
-    for (int i = 0; i < NM; ++i) {
+  for (int a = 0; a < 2 * HM; ++a)
+#pragma unroll
+    for (int b = 0; b < 2 * HB; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int l15 = lane & 15;
+  bf16x8 fa0[HM][2], fa1[HM][2], fb0[HB][2], fb1[HB][2];
+  // fragment addresses: the chunk swizzle only depends on the lane (the blocks start at multiples of
+  // 16 rows), so a fragment is a constant away from one of four addresses in the stage
+  uint32_t offA[2], offB[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    offA[ks] = swz(wm * (BM / 4) + l15, in_chunk<16>(ks, lane));
+    offB[ks] = BM * ROWB + swz(wn * 16 * HB + l15, in_chunk<16>(ks, lane));
+  }
+  auto rdA = [&](bf16x8 (&f)[HM][2], const unsigned char* st, int half, int i) {
+    const int ks = i / HM, a = i % HM;
+    f[a][ks] = *reinterpret_cast<const bf16x8*>(st + offA[ks] + (half * (BM / 2) + 16 * a) * ROWB);
+  };
+  auto rdB = [&](bf16x8 (&f)[HB][2], const unsigned char* st, int half, int i) {
+    const int ks = i / HB, b = i % HB;
+    f[b][ks] = *reinterpret_cast<const bf16x8*>(st + offB[ks] + (half * 128 + 16 * b) * ROWB);
+  };
+  auto mm = [&](const bf16x8 (&fa)[HM][2], const bf16x8 (&fb)[HB][2], int ha, int hb) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int a = 0; a < HM; ++a)
+#pragma unroll
+        for (int b = 0; b < HB; ++b)
+          acc[ha * HM + a][hb * HB + b] = mfma_op(fa[a][ks], fb[b][ks], acc[ha * HM + a][hb * HB + b]);
+  };
+  // The memory operations of a phase in program order: a stage load after every EV-th fragment read (the
+  // compiler keeps their order, as the loads write the LDS that the reads read), and the
+  // schedule: one of them after each MFMA.
+  auto mem = [&](auto nr_, auto nl_, auto ev_, auto rd, auto ld) {
+    constexpr int nr = decltype(nr_)::value, nl = decltype(nl_)::value, ev = decltype(ev_)::value;
+    int l = 0;
+#pragma unroll
+    for (int i = 0; i < nr; ++i) {
+      rd(i);
+      if (i % ev == ev - 1 && l < nl) ld(l++);
+    }
+#pragma unroll
+    for (int i = 0; i < nl; ++i)
+      if (i >= l) ld(i);
+  };
+  auto weave = [&](auto nm_, auto nr_, auto nl_, auto ev_) {
+    constexpr int nm = decltype(nm_)::value, nl = decltype(nl_)::value, nr = decltype(nr_)::value,
+                  ev = decltype(ev_)::value;
+    int r = 0, l = 0;
+#pragma unroll
+    for (int i = 0; i < nm; ++i) {
       __builtin_amdgcn_sched_group_barrier(SG_MFMA, 1, 0);
-      if (i < nl) __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, 1, 0);
-      if (i < nr) __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
-    }
-    if constexpr (nl > NM) __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, nl - NM, 0);
-    if constexpr (nr > NM) __builtin_amdgcn_sched_group_barrier(SG_DS_READ, nr - NM, 0);
-  };
-  // write this wave's staged block of the tile at (m0, nt) to act
-  auto store_staged = [&](int m0, int nt) {
-#pragma unroll
-    for (int p = 0; p < PPL; ++p) {
-      const int e = lane + kWave * p;
-      const int i = e / CPR, c8 = (e % CPR) * 8;
-      const int m = m0 + wm * C::WTM + i;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(ostg + i * C::ON + c8);
-      if (m < M) epi.emit_packed(m, nt * C::OUT_N + wn * C::ON + c8, v);
-    }
-  };
-
-  int prev_m0 = -1, prev_nt = 0;
-  for (int li = q; li < per; li += nq) {
-    const int tile = xcd * per + li;
-    if (tile >= total) break;
-    const int grp = tile / (GROUP_M * n_tiles), rem = tile % (GROUP_M * n_tiles);
-    const int gsz = min(GROUP_M, mt_act - grp * GROUP_M);
-    const int mt = grp * GROUP_M + rem % gsz, nt = rem / gsz;
-    const int m0 = mt * C::BM;
-
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A.base);
-    uint32_t a_off[A_LD];
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-      const int r = 8 * (i * NW + wave) + rsub;
-      const int ch = (lane & 7) ^ ((r >> 1) & 7);
-      const int m = min(m0 + r, M - 1);
-      const int row = A.idx ? A.idx[m] : m;
-      a_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(A.ld * 2) + ch * 16;
-    }
-    const unsigned char* b_base[B_LD];
-    uint32_t b_off[B_LD];
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) {
-      const int blk = i * NW + wave;
-      const int r = 8 * blk + rsub;
-      const int ch = (lane & 7) ^ ((r >> 1) & 7);
-      const int wb = (8 * blk) / C::WTN, q0 = (8 * blk) % C::WTN, h = C::WTN / 2;
-      const bool up = q0 >= h;
-      b_base[i] = reinterpret_cast<const unsigned char*>(up ? B.b1 : B.b0);
-      const int row = nt * C::OUT_N + wb * h + (r % C::WTN) - (up ? h : 0);
-      b_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(B.ld * 2) + ch * 16;
-    }
-    auto issue = [&](int stage, int k0) {
-      unsigned char* sa = smem + stage * C::STAGE;
-      const uint32_t kb = static_cast<uint32_t>(k0) * 2;
-#pragma unroll
-      for (int i = 0; i < A_LD; ++i) load_lds16(a_base + a_off[i] + kb, sa + (i * NW + wave) * 1024);
-#pragma unroll
-      for (int i = 0; i < B_LD; ++i)
-        load_lds16(b_base[i] + b_off[i] + kb, sa + C::BM * ROWB + (i * NW + wave) * 1024);
-    };
-
-#pragma unroll
-    for (int a = 0; a < C::TM; ++a)
-#pragma unroll
-      for (int b = 0; b < C::TN; ++b)
-#pragma unroll
-        for (int r = 0; r < C::NACC; ++r) acc[a][b][r] = 0.f;
-
-    // every wave is past the previous tile's last barrier: the stages are free
-    issue(0, 0);
-    if (nk > 1) issue(1, BK);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    // the previous tile's results leave while this tile computes
-    if (prev_m0 >= 0) store_staged(prev_m0, prev_nt);
-    read_frags(0, smem, 0);
-    // one k-tile; the modes are straight-line code as in mfma_gemm (2: the loads of tile kt + 2
-    // and the first fragments of tile kt + 1 interleave with the last k-step; 1: no tile left to
-    // load; 0: the last tile)
-    auto ktile = [&](int kt, auto mode_) {
-      constexpr int mode = decltype(mode_)::value;
-      const unsigned char* st = smem + (kt & 1) * C::STAGE;
-#pragma unroll
-      for (int ks = 0; ks < KS - 1; ++ks) {
-        read_frags((ks + 1) & 1, st, ks + 1);
-        mfmas(ks & 1);
-        interleave(std::integral_constant<int, 0>(), std::integral_constant<int, NR>());
-        __builtin_amdgcn_sched_barrier(0);
+      if (r < nr) {
+        __builtin_amdgcn_sched_group_barrier(SG_DS_READ, 1, 0);
+        ++r;
+        if (r % ev == 0 && l < nl) {
+          __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, 1, 0);
+          ++l;
+        }
+      } else if (l < nl) {
+        __builtin_amdgcn_sched_group_barrier(SG_VMEM_READ, 1, 0);
+        ++l;
       }
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      __syncthreads();
-      if constexpr (mode == 2) issue(kt & 1, (kt + 2) * BK);
-      if constexpr (mode >= 1) read_frags(KS & 1, smem + ((kt + 1) & 1) * C::STAGE, 0);
-      mfmas((KS - 1) & 1);
-      interleave(std::integral_constant<int, mode == 2 ? NL : 0>(),
-                 std::integral_constant<int, mode >= 1 ? NR : 0>());
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#define IC(n) std::integral_constant<int, (n)>()
+  constexpr int L1 = C::L1, L2 = C::L2, SP = C::SPLIT, NM = 2 * HM * HB;
+  // MODE 2: tile kt + 2 is loaded; 1: the last but one; 0: the last
+  auto ktile = [&](int kt, auto mode_) {
+    constexpr int mode = decltype(mode_)::value;
+    const unsigned char* st = smem + (kt & 1) * C::STAGE;
+    const unsigned char* nx = smem + ((kt + 1) & 1) * C::STAGE;
+    wait_vm_lgkm<mode == 0 ? 0 : L1 + L2>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    mem(IC(2 * HB + 2 * HM), IC(mode == 2 ? L1 : 0), IC(2),
+        [&](int i) { i < 2 * HB ? rdB(fb1, st, 1, i) : rdA(fa1, st, 1, i - 2 * HB); }, [&](int i) { ld1(i, kt + 2); });
+    mm(fa0, fb0, 0, 0);
+    weave(IC(NM), IC(2 * HB + 2 * HM), IC(mode == 2 ? L1 : 0), IC(2));
+    mm(fa0, fb1, 0, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (mode != 0) {
+      wait_vm_lgkm<(mode == 2 ? L1 + L2 : L2) - SP>();
+      __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
+      mem(IC(2 * HM), IC(mode == 2 ? L2 : 0), IC(1), [&](int i) { rdA(fa0, nx, 0, i); }, [&](int i) { ld2(i, kt + 2); });
+    }
+    mm(fa1, fb0, 1, 0);
+    weave(IC(NM), IC(mode ? 2 * HM : 0), IC(mode == 2 ? L2 : 0), IC(1));
+    if constexpr (mode != 0)
+#pragma unroll
+      for (int i = 0; i < 2 * HB; ++i) rdB(fb0, nx, 0, i);
+    mm(fa1, fb1, 1, 1);
+    weave(IC(NM), IC(mode ? 2 * HB : 0), IC(0), IC(1));
+  };
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int i = 0; i < L1; ++i) ld1(i, t);
+#pragma unroll
+    for (int i = 0; i < L2; ++i) ld2(i, t);
+  }
+  wait_vm_lgkm<L1 + 2 * L2 - SP>();
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int i = 0; i < 2 * HM; ++i) rdA(fa0, smem, 0, i);
+#pragma unroll
+  for (int i = 0; i < 2 * HB; ++i) rdB(fb0, smem, 0, i);
+  int kt = 0;
+  for (; kt + 2 < nk; ++kt) ktile(kt, IC(2));
+  ktile(kt, IC(1));
+  ktile(kt + 1, IC(0));
+#undef IC
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+
+  if constexpr (DualHook<Epi>::value) {
+    swiglu_bwd_tile<C>(epi, acc, smem, m0, nt, wave, wm, wn, M, lane);
+  } else if constexpr (C::DUAL) {
+    // rows of half h: m0 + h BM/2 + wm BM/4 + ..; the wave's 32 columns of act, gate in acc[.][0..1], up in [2..3]
+    constexpr int ON = 16 * HB, SP2 = ON + 8, CPR = ON / 8;
+    bf16_t* stg = reinterpret_cast<bf16_t*>(smem) + wave * (32 * HM * SP2);
+#pragma unroll
+    for (int a = 0; a < 2 * HM; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int b = 0; b < HB; ++b) {
+          const float g = acc[a][b][r], u = acc[a][HB + b][r];
+          stg[(16 * a + 4 * (lane >> 4) + r) * SP2 + 16 * b + l15] =
+              f32_to_bf16(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
+        }
+#pragma unroll
+    for (int p = 0; p < 2 * HM * 16 * CPR / kWave; ++p) {
+      const int e = lane + kWave * p, i = e / CPR, c8 = (e % CPR) * 8;
+      const int h = i / (16 * HM), m = m0 + h * (BM / 2) + wm * (BM / 4) + i - h * 16 * HM;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(stg + i * SP2 + c8);
+      if (m < M) epi.emit_packed(m, nt * 128 + wn * ON + c8, v);
+    }
+  } else {
+    // per half of B: 32 columns; 16-row blocks staged as fp32
+    constexpr int ON = 16 * HB, OP = 2 * ON + 4, CPR = ON / 4, PP = 16 * CPR / kWave;
+    float* stg = reinterpret_cast<float*>(smem) + wave * (16 * OP);
+    typename Epi::Pre pre[2 * HM][PP];
+    // rows of fragment a, columns of the staged pair of 32-column blocks
+    auto row_of = [&](int a, int i) { return m0 + (a / HM) * (BM / 2) + wm * (BM / 4) + 16 * (a % HM) + i; };
+    auto col_of = [&](int c8) { return nt * 256 + (c8 / ON) * 128 + wn * ON + c8 % ON; };
+    auto fetch = [&](int a) {
+#pragma unroll
+      for (int p = 0; p < PP; ++p) {
+        const int e = lane + kWave * p;
+        pre[a][p] = epi.prep(min(row_of(a, e / CPR), M - 1), col_of((e % CPR) * 8));
+      }
     };
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) ktile(kt, std::integral_constant<int, 2>());
-    for (; kt + 1 < nk; ++kt) ktile(kt, std::integral_constant<int, 1>());
-    if (kt < nk) ktile(kt, std::integral_constant<int, 0>());
-    // stage SiLU(gate) * up of this wave's block (its previous contents were stored above)
+    // what the epilogue combines with (hbar rows) is fetched four fragments ahead of the staging
+    constexpr int AHEAD = 4;
 #pragma unroll
-    for (int a = 0; a < C::TM; ++a)
+    for (int a = 0; a < AHEAD; ++a) fetch(a);
 #pragma unroll
-      for (int r = 0; r < C::NACC; ++r) {
-        const int i = a * MI + out_row<MI>(r, lane);
+    for (int a = 0; a < 2 * HM; ++a) {
+      if (a + AHEAD < 2 * HM) fetch(a + AHEAD);
 #pragma unroll
-        for (int b = 0; b < C::TN / 2; ++b) {
-          const float g = acc[a][b][r], u = acc[a][b + C::TN / 2][r];
-          ostg[i * C::ON + b * MI + (lane & (MI - 1))] = f32_to_bf16(g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u);
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int b = 0; b < 2 * HB; ++b) stg[(4 * (lane >> 4) + r) * OP + 16 * b + l15] = acc[a][b][r];
+      if constexpr (BlockEpilogue<Epi>::value) {
+        epi.block(stg, OP, ON, row_of(a, 0), col_of(0), M, lane);
+        epi.block(stg + ON, OP, ON, row_of(a, 0), col_of(ON), M, lane);
+      } else {
+#pragma unroll
+        for (int p = 0; p < PP; ++p) {
+          const int e = lane + kWave * p, i = e / CPR, c8 = (e % CPR) * 8;
+          const int m = row_of(a, i);
+          if (m < M) epi.emit8(pre[a][p], m, col_of(c8), stg + i * OP + c8);
         }
       }
-    prev_m0 = m0;
-    prev_nt = nt;
+    }
   }
-  if (prev_m0 >= 0) store_staged(prev_m0, prev_nt);
 }
 
-// Persistent launch: one workgroup per CU (a multiple of 8 workgroups so that each XCD holds
-// the same number), each XCD owning a contiguous range of the grouped tile order.
-template <class C>
-hipError_t run_persist(ARows<bf16_t> A, BRows<bf16_t> B, EpiSwiGLU<bf16_t> epi, const int* m_count,
-                       int M_max, int N_out, int K, hipStream_t s) {
-  const int mt_max = (M_max + C::BM - 1) / C::BM;
-  const int n_tiles = N_out / C::OUT_N;
-  const int total = mt_max * n_tiles;
-  if (total == 0) return hipSuccess;
-  const int nq = std::min((total + 7) / 8, kCUs / 8);   // workgroups per XCD
-  gateup_persist<C><<<8 * nq, C::NT, 0, s>>>(A, B, epi, m_count, M_max, K, mt_max, n_tiles);
+
+template <class C, class Epi>
+__global__ __launch_bounds__(512, 2) void phase_gemm(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi,
+                                                     const int* __restrict__ m_count, int M_max, int K, int n_tiles) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * C::STAGE];
+  phase_tile<C>(A, B, epi, m_count ? *m_count : M_max, M_max, K, n_tiles, smem);
+}
+
+// Tile height for M rows: the launch's time in rounds of workgroups over the CUs, times the
+// relative duration of a round (measured on the Llama-3.1-8B gate/up and down shapes at 0.4k to 20k
+// rows: 54-57, 78 and 97 us for 128-, 192- and 256-row tiles at K = 4096; 187, 258 and 345 at
+// 14336).  The smaller tiles move more bytes per product and only pay while their finer rounds
+// leave fewer CUs idle, so beyond two (128) and eight (192) rounds they are not considered.
+__host__ __device__ inline int phase_rows(int M, int n_tiles) {
+  auto tiles = [&](int BM) { return (M + BM - 1) / BM * n_tiles; };
+  auto cost = [&](int BM, int w) { return (tiles(BM) + kCUs - 1) / kCUs * w; };
+  int best = 256, c = cost(256, 125);
+  if (tiles(192) <= 8 * kCUs && cost(192, 100) < c) {
+    best = 192;
+    c = cost(192, 100);
+  }
+  if (tiles(128) <= 2 * kCUs && cost(128, 75) < c) best = 128;
+  return best;
+}
+
+// Threshold routing: the host only knows an upper bound of the row count, so the workgroups choose
+// the tile height themselves from the count on the device.
+template <bool DUAL, class Epi>
+__global__ __launch_bounds__(512, 2) void phase_gemm_any(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi,
+                                                         const int* __restrict__ m_count, int M_max, int K,
+                                                         int n_tiles) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * Phase<256, DUAL>::STAGE];
+  const int M = min(*m_count, M_max);
+  const int bm = phase_rows(M, n_tiles);
+  if (bm == 256)
+    phase_tile<Phase<256, DUAL>>(A, B, epi, M, M_max, K, n_tiles, smem);
+  else if (bm == 192)
+    phase_tile<Phase<192, DUAL>>(A, B, epi, M, M_max, K, n_tiles, smem);
+  else
+    phase_tile<Phase<128, DUAL>>(A, B, epi, M, M_max, K, n_tiles, smem);
+}
+
+// exact: M_max is the row count (m_count, if given, holds at most that)
+template <bool DUAL, class Epi>
+hipError_t run_phase(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_count, int M_max, int N_out, int K,
+                     hipStream_t s, bool exact = true) {
+  const int n_tiles = N_out / Phase<256, DUAL>::OUT_N;
+  if (M_max <= 0 || n_tiles <= 0) return hipSuccess;
+  const auto blocks = [&](int BM) { return ((M_max + BM - 1) / BM * n_tiles + 7) / 8 * 8; };
+  if (!exact && m_count) {
+    // enough for any choice at any count up to M_max
+    const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 2 * kCUs)});
+    phase_gemm_any<DUAL, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
+    return hipGetLastError();
+  }
+  switch (phase_rows(M_max, n_tiles)) {
+    case 256: phase_gemm<Phase<256, DUAL>, Epi><<<blocks(256), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
+    case 192: phase_gemm<Phase<192, DUAL>, Epi><<<blocks(192), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
+    default: phase_gemm<Phase<128, DUAL>, Epi><<<blocks(128), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
+  }
   return hipGetLastError();
+}
+
+// Backward SwiGLU epilogue of one wave tile (EpiSwiGLUBwd on the MFMA path).  Lane l holds columns
+// l & 15 (+ 16) of the wave's 32, gate in acc[a][0..1] and up in acc[a][2..3], at rows
+// 16 a + 4 (l >> 4) + r of the wave's rows.  e is loaded two fragments of rows ahead, held as 16-bit
+// words and widened at use (widening at the load let the compiler wait for each load in turn); a
+// row's share of <e, act> is a sum over 16 lanes.  dG and dU of one half of the rows at a time are
+// staged in the wave's own LDS region, whose operations complete in order, and leave as 16-byte
+// row pieces.
+template <class C, class Epi>
+__device__ __forceinline__ void swiglu_bwd_tile(const Epi& epi, f32x4 (&acc)[2 * C::HM][4], unsigned char* smem, int m0,
+                                                int nt, int wave, int wm, int wn, int M, int lane) {
+  static_assert(C::DUAL, "gate/up tiles");
+  constexpr int HM = C::HM, NA = 2 * HM, HR = 16 * HM, SPAD = C::ON + 8, CPR = C::ON / 8;
+  static_assert(C::NW * (2 * HR * SPAD * 2 + 2 * HR * 4) <= 2 * C::STAGE, "backward staging fits in the stages");
+  bf16_t* sg = reinterpret_cast<bf16_t*>(smem) + wave * 2 * HR * SPAD;
+  bf16_t* su = sg + HR * SPAD;
+  float* gl = reinterpret_cast<float*>(smem + C::NW * 2 * HR * SPAD * 2) + wave * 2 * HR;
+  const int col0 = nt * C::OUT_N + wn * C::ON, l15 = lane & 15, g4 = 4 * (lane >> 4);
+  auto row_of = [&](int h, int i) { return m0 + h * (C::BM / 2) + wm * (C::BM / 4) + i; };   // row i of half h
+  for (int i = lane; i < 2 * HR; i += kWave) {
+    const int m = min(row_of(i / HR, i % HR), M - 1);
+    const int t = epi.idx ? epi.idx[m] : m;
+    gl[i] = epi.gate ? epi.gate[t] : 1.0f;
+  }
+  constexpr int AHEAD = 2;
+  bf16_t ev[AHEAD + 1][4][2];
+  auto fetch = [&](int a) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = min(row_of(a / HM, 16 * (a % HM) + g4 + r), M - 1);
+      const bf16_t* e = epi.e + static_cast<size_t>(m) * epi.ld_e + col0 + l15;
+      ev[a % (AHEAD + 1)][r][0] = e[0];
+      ev[a % (AHEAD + 1)][r][1] = e[16];
+    }
+  };
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a) fetch(a);
+#pragma unroll
+  for (int a = 0; a < NA; ++a) {
+    const int h = a / HM;
+    if (a + AHEAD < NA) fetch(a + AHEAD);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = 16 * (a % HM) + g4 + r;
+      const float gt = gl[h * HR + i];
+      float sum = 0.f;
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const float g = acc[a][b][r], u = acc[a][2 + b][r];
+        const float sg_ = __builtin_amdgcn_rcpf(1.0f + __expf(-g));
+        const float ee = bf16_to_f32(ev[a % (AHEAD + 1)][r][b]);
+        const float dact = gt * ee;
+        sum += ee * (g * sg_ * u);
+        sg[i * SPAD + 16 * b + l15] = f32_to_bf16(dact * u * sg_ * (1.0f + g * (1.0f - sg_)));
+        su[i * SPAD + 16 * b + l15] = f32_to_bf16(dact * g * sg_);
+      }
+      sum = group_sum<16>(sum);
+      const int m = row_of(h, i);
+      if (l15 == 0 && m < M) epi.dgpart[static_cast<size_t>(m) * epi.n_parts + col0 / C::ON] = sum;
+      __builtin_amdgcn_sched_barrier(0);   // one row at a time: the accumulators leave few registers
+    }
+    if (a % HM == HM - 1) {
+#pragma unroll
+      for (int p = 0; p < HR * CPR / kWave; ++p) {
+        const int e = lane + kWave * p, i = e / CPR, c8 = (e % CPR) * 8;
+        const u32x4 vg = *reinterpret_cast<const u32x4*>(sg + i * SPAD + c8);
+        const u32x4 vu = *reinterpret_cast<const u32x4*>(su + i * SPAD + c8);
+        const int m = row_of(h, i);
+        if (m < M) {
+          bf16_t* o = epi.dgu + static_cast<size_t>(m) * epi.ld_dgu + col0 + c8;
+          *reinterpret_cast<u32x4*>(o) = vg;
+          *reinterpret_cast<u32x4*>(o + epi.d_ff) = vu;
+        }
+      }
+    }
+  }
 }
 
 template <class C, class Epi>
@@ -1366,33 +1436,6 @@ hipError_t run_skinny(ARows<bf16_t> A, const bf16_t* b0, const bf16_t* b1, int l
   return hipGetLastError();
 }
 
-// Time of a launch in units of one round of 192-row tiles: CU rounds times the relative
-// duration of a round.  A 256-row tile moves fewer bytes through L2 per FLOP, so its round
-// takes ~1.23x (not 256/192 = 1.33x) a 192-row round on the FFN products (measured on the
-// Llama-3.1-8B gate/up and down shapes at 3k-20k rows).
-double tile_cost(int M, int BM, int n_tiles) {
-  const int tiles = (M + BM - 1) / BM * n_tiles;
-  return static_cast<double>((tiles + kCUs - 1) / kCUs) * (BM == 256 ? 1.23 : 1.0);
-}
-
-// Big-tile launch: 256 or 192 rows per tile, whichever finishes in fewer CU-rounds.  The FFN
-// products run the 16 x 16 x 32 instruction (MI = 16); other users keep 32 x 32 x 16 tiles.
-template <int BN, bool DUAL, class Epi, int MI = 32>
-hipError_t run_big(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_count, int M_max,
-                   int N_out, int K, hipStream_t s) {
-  using T256 = Tile<256, BN, 2, 4, DUAL, 2, MI>;
-  using T192 = Tile<192, BN, 2, 4, DUAL, 2, MI>;
-  const int n_tiles = N_out / T256::OUT_N;
-  if (tile_cost(M_max, 192, n_tiles) < tile_cost(M_max, 256, n_tiles)) {
-    if constexpr (DUAL) {
-      // more tiles than CUs: the persistent kernel hides each tile's epilogue behind the next
-      if ((M_max + 191) / 192 * n_tiles > kCUs) return run_persist<T192>(A, B, epi, m_count, M_max, N_out, K, s);
-    }
-    return run_tile<T192>(A, B, epi, m_count, M_max, N_out, K, s);
-  }
-  return run_tile<T256>(A, B, epi, m_count, M_max, N_out, K, s);
-}
-
 // ---------------------------------------------------------------------------
 // fp32 GEMM on the fp32 matrix cores (v_mfma_f32_16x16x4f32: products and sums in fp32)
 //
@@ -1724,13 +1767,11 @@ int adapter_groups_rows(int K, int n_max) {
 }
 
 // router pre-activations: 128-row tiles over all 8 waves, K split four ways
-using TileRouter = Tile<128, 256, 2, 4, false>;
-using TileRouterNarrow = Tile<128, 128, 2, 4, false>;
+using TileRouter = Tile<128, 256, 2, 4>;
+using TileRouterNarrow = Tile<128, 128, 2, 4>;
 // few tokens (a decode batch): 64-row tiles of 4 waves, four times the workgroups; each streams
 // a quarter of K, with three k-tiles in flight
-using TileRouterSmall = Tile<64, 128, 1, 4, false, 4>;
-// many tokens: 256 x 256 tiles on v_mfma_f32_16x16x32_bf16
-using TileRouterBig = Tile<256, 256, 2, 4, false, 2, 16>;
+using TileRouterSmall = Tile<64, 128, 1, 4, 4>;
 
 }  // namespace
 
@@ -1776,8 +1817,7 @@ hipError_t launch_router_gemm(int dtype, const void* hbar, const void* w_hd, con
       return run_tile<TileRouterSmall>(A, B, epi, nullptr, T, N, d, s, splits);
     // a full round or more of tiles: the FFN products' 256 x 256 tiles on the 16 x 16 x 32
     // instruction (32768 tokens: 256 tiles, no K split)
-    if (splits == 1 && T >= 16384 && N % TileRouterBig::OUT_N == 0)
-      return run_tile<TileRouterBig>(A, B, epi, nullptr, T, N, d, s);
+    if (splits == 1 && T >= 16384 && N % 256 == 0) return run_phase<false>(A, B, epi, nullptr, T, N, d, s);
     if (N % TileRouter::OUT_N == 0) return run_tile<TileRouter>(A, B, epi, nullptr, T, N, d, s, splits);
     return run_tile<TileRouterNarrow>(A, B, epi, nullptr, T, N, d, s, splits);
   }
@@ -1794,8 +1834,8 @@ namespace {
 // the launch within one round of workgroups), the slices write fp32 partial sums, and a pass
 // over them adds the S slices in a fixed order and finishes the epilogue.
 // ---------------------------------------------------------------------------
-using TileSplitGU = Tile<192, 256, 2, 4, false>;    // [W_g; W_u] as one 2 d_ff-row operand
-using TileSplitDown = Tile<192, 128, 2, 4, false, 4>;
+using TileSplitGU = Tile<192, 256, 2, 4>;    // [W_g; W_u] as one 2 d_ff-row operand
+using TileSplitDown = Tile<192, 128, 2, 4, 4>;
 constexpr int kMaxSplitGU = 8, kMaxSplitDown = 16;
 
 // At most 256 rows (a decode batch): the skinny products.  Gate/up: one workgroup per CU, each
@@ -2033,7 +2073,7 @@ hipError_t launch_tile_ffn_weights(const void* w0, const void* w1, int N, int K,
 
 hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const int* counts,
                              int n_max, const void* w_gate, const void* w_up, const void* w_gate_up_tiled,
-                             void* act, float* part, int d, int d_ff, hipStream_t s) {
+                             void* act, float* part, int d, int d_ff, bool exact, hipStream_t s) {
   if (n_max <= 0) return hipSuccess;
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(u), idx_ffn, d};
@@ -2054,8 +2094,7 @@ hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const
       return hipGetLastError();
     }
     BRows<bf16_t> B{static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up), INT_MAX, d};
-    return run_big<256, true, EpiSwiGLU<bf16_t>, 16>(A, B, EpiSwiGLU<bf16_t>{static_cast<bf16_t*>(act), d_ff},
-                                                     counts, n_max, d_ff, d, s);
+    return run_phase<true>(A, B, EpiSwiGLU<bf16_t>{static_cast<bf16_t*>(act), d_ff}, counts, n_max, d_ff, d, s, exact);
   }
   ARows<float> A{static_cast<const float*>(u), idx_ffn, d};
   BRows<float> B{static_cast<const float*>(w_gate), static_cast<const float*>(w_up), INT_MAX, d};
@@ -2065,7 +2104,7 @@ hipError_t launch_ffn_gateup(int dtype, const void* u, const int* idx_ffn, const
 
 hipError_t launch_ffn_down(int dtype, const void* act, const int* idx_ffn, const int* counts,
                            int n_max, const void* w_down, const void* w_down_tiled, const void* hbar,
-                           const float* gate, void* h_out, float* part, int d, int d_ff, hipStream_t s) {
+                           const float* gate, void* h_out, float* part, int d, int d_ff, bool exact, hipStream_t s) {
   if (n_max <= 0) return hipSuccess;
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(act), nullptr, d_ff};
@@ -2088,7 +2127,7 @@ hipError_t launch_ffn_down(int dtype, const void* act, const int* idx_ffn, const
     }
     EpiScatter<bf16_t, false> epi{idx_ffn, static_cast<const bf16_t*>(hbar), gate,
                                   static_cast<bf16_t*>(h_out), d};
-    return run_big<256, false, EpiScatter<bf16_t, false>, 16>(A, B, epi, counts, n_max, d, d_ff, s);
+    return run_phase<false>(A, B, epi, counts, n_max, d, d_ff, s, exact);
   }
   ARows<float> A{static_cast<const float*>(act), nullptr, d_ff};
   BRows<float> B{static_cast<const float*>(w_down), nullptr, INT_MAX, d_ff};
@@ -2121,15 +2160,15 @@ struct EpiQKV {
   __device__ __forceinline__ Pre prep(int, int) const { return {}; }
   __device__ __forceinline__ void store(int, int, float) const {}
   __device__ __forceinline__ void emit8(const Pre&, int, int, const float*) const {}
-  // a staged block of 32 token rows x `on` columns (one head's half: 64 | 128) starting at
-  // row mb, column nb
+  // a staged block of 16 token rows x `on` columns of one head (on | 128) starting at row mb,
+  // column nb
   __device__ __forceinline__ void block(const float* stg, int opad, int on, int mb, int nb, int M,
                                         int lane) const {
     const int head = nb / kHeadDim, c0 = nb % kHeadDim;
     if (head < nh + nkv) {
       // q or k: 8-column row pieces, turned by the rotary table
       const int cpr = on / 8;
-      for (int e = lane; e < 32 * cpr; e += kWave) {
+      for (int e = lane; e < 16 * cpr; e += kWave) {
         const int i = e / cpr, c8 = (e % cpr) * 8;
         const int m = mb + i;
         if (m >= M) continue;
@@ -2155,25 +2194,23 @@ struct EpiQKV {
       // p with bits 2 and 3 swapped: 0-3, 8-11, 4-7, 12-15): a piece is one column over the
       // 8 positions 16G + 4X + {0..3} and 16G + 8 + 4X + {0..3} of the block, one 16-byte run
       const int vh = head - nh - nkv;
-      for (int e = lane; e < 4 * on; e += kWave) {
-        const int col = e % on, rg = e / on;
-        const int G = rg >> 1, X = rg & 1;
-        const int m16 = mb + 16 * G;
-        if (m16 >= M) continue;
-        const int b = m16 / seq, p16 = m16 - b * seq;
+      for (int e = lane; e < 2 * on; e += kWave) {
+        const int col = e % on, X = e / on;
+        if (mb >= M) continue;
+        const int b = mb / seq, p16 = mb - b * seq;
         bf16_t* row = vt + ((static_cast<size_t>(b) * nkv + vh) * kHeadDim + c0 + col) * seq_pad;
-        if (m16 + 15 < M && p16 + 15 < seq && (p16 & 15) == 0) {
+        if (mb + 15 < M && p16 + 15 < seq && (p16 & 15) == 0) {
           u32x4 w;
 #pragma unroll
           for (int x = 0; x < 4; ++x) {
-            const int r0 = 16 * G + (x < 2 ? 4 * X + 2 * x : 8 + 4 * X + 2 * (x - 2));
+            const int r0 = x < 2 ? 4 * X + 2 * x : 8 + 4 * X + 2 * (x - 2);
             w[x] = static_cast<uint32_t>(f32_to_bf16(stg[r0 * opad + col])) |
                    (static_cast<uint32_t>(f32_to_bf16(stg[(r0 + 1) * opad + col])) << 16);
           }
           *reinterpret_cast<u32x4*>(row + p16 + 8 * X) = w;
         } else {
           for (int x = 0; x < 8; ++x) {
-            const int r = 16 * G + (x < 4 ? 4 * X + x : 8 + 4 * X + x - 4);
+            const int r = x < 4 ? 4 * X + x : 8 + 4 * X + x - 4;
             const int mm = mb + r;
             if (mm >= M) continue;
             const int bx = mm / seq, px = mm - bx * seq;
@@ -2212,7 +2249,7 @@ hipError_t launch_attn_qkv(const void* x, const void* w_qkv, int T, int d, int s
   BRows<bf16_t> B{static_cast<const bf16_t*>(w_qkv), nullptr, INT_MAX, d};
   EpiQKV epi{static_cast<bf16_t*>(q), static_cast<bf16_t*>(k), static_cast<bf16_t*>(vt),
              reinterpret_cast<const float2*>(rope_cs), seq, seq_pad, nh, nkv};
-  return run_big<256, false>(A, B, epi, nullptr, T, (nh + 2 * nkv) * kHeadDim, d, s);
+  return run_phase<false>(A, B, epi, nullptr, T, (nh + 2 * nkv) * kHeadDim, d, s);
 }
 
 hipError_t launch_attn_out(const void* o, const void* w_o, const void* h, void* hbar, int T, int d, int nh,
@@ -2222,7 +2259,7 @@ hipError_t launch_attn_out(const void* o, const void* w_o, const void* h, void* 
   ARows<bf16_t> A{static_cast<const bf16_t*>(o), nullptr, K};
   BRows<bf16_t> B{static_cast<const bf16_t*>(w_o), nullptr, INT_MAX, K};
   EpiScatter<bf16_t, false> epi{nullptr, static_cast<const bf16_t*>(h), nullptr, static_cast<bf16_t*>(hbar), d};
-  return run_big<256, false>(A, B, epi, nullptr, T, d, K, s);
+  return run_phase<false>(A, B, epi, nullptr, T, d, K, s);
 }
 
 // Wide adapters (ranks above 128, in steps of 128: the paper's d_r = 896).  The down-projection
@@ -2230,7 +2267,7 @@ hipError_t launch_attn_out(const void* o, const void* w_o, const void* h, void* 
 // hid = bf16(SiLU(sum of the partials)), and the up-projection is a GEMM whose epilogue scatters
 // hbar + (1 - g) (W_2 hid) into the adapter rows.
 constexpr int WIDE_SPLIT = 4;
-using TileWide = Tile<128, 128, 2, 4, false>;
+using TileWide = Tile<128, 128, 2, 4>;
 
 bool adapter_wide(int d_r) { return d_r > 128; }
 
@@ -2443,21 +2480,17 @@ hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s) {
 //   du   = [dG dU] [W_g; W_u]     B = [W_g; W_u]^T [d][2 d_ff]
 // and the adapter's: z = u[idx] W_1^T, e_a = dL/dh[idx] W_2 (B = W_2^T), du = dz W_1 (B = W_1^T).
 // ---------------------------------------------------------------------------
-namespace {
-using TileBwdGU = Tile<192, 256, 2, 4, true>;
-}
-
-int swiglu_bwd_parts(int dtype, int d_ff) { return dtype == 1 ? d_ff / TileBwdGU::ON : d_ff; }
+int swiglu_bwd_parts(int dtype, int d_ff) { return dtype == 1 ? d_ff / Phase<256, true>::ON : d_ff; }
 
 hipError_t launch_ffn_bwd_e(int dtype, const void* dh, const int* idx_ffn, const int* counts, int n_max,
-                            const void* w_down_t, void* e, int d, int d_ff, hipStream_t s) {
+                            const void* w_down_t, void* e, int d, int d_ff, bool exact, hipStream_t s) {
   if (n_max <= 0) return hipSuccess;
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(dh), idx_ffn, d};
     BRows<bf16_t> B{static_cast<const bf16_t*>(w_down_t), nullptr, INT_MAX, d};
     EpiStore<bf16_t> epi{static_cast<bf16_t*>(e), d_ff};
-    return d_ff % 256 == 0 ? run_big<256, false>(A, B, epi, counts, n_max, d_ff, d, s)
-                           : run_big<128, false>(A, B, epi, counts, n_max, d_ff, d, s);
+    return d_ff % 256 == 0 ? run_phase<false>(A, B, epi, counts, n_max, d_ff, d, s, exact)
+                           : run_tile<Tile<256, 128, 2, 4>>(A, B, epi, counts, n_max, d_ff, d, s);
   }
   ARows<float> A{static_cast<const float*>(dh), idx_ffn, d};
   BRows<float> B{static_cast<const float*>(w_down_t), nullptr, INT_MAX, d};
@@ -2466,14 +2499,14 @@ hipError_t launch_ffn_bwd_e(int dtype, const void* dh, const int* idx_ffn, const
 
 hipError_t launch_ffn_bwd_gateup(int dtype, const void* u, const int* idx_ffn, const int* counts, int n_max,
                                  const void* w_gate, const void* w_up, const void* e, const float* gate,
-                                 void* dgu, float* dgpart, int d, int d_ff, hipStream_t s) {
+                                 void* dgu, float* dgpart, int d, int d_ff, bool exact, hipStream_t s) {
   if (n_max <= 0) return hipSuccess;
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(u), idx_ffn, d};
     BRows<bf16_t> B{static_cast<const bf16_t*>(w_gate), static_cast<const bf16_t*>(w_up), INT_MAX, d};
     EpiSwiGLUBwd<bf16_t> epi{static_cast<const bf16_t*>(e), d_ff, idx_ffn, gate, static_cast<bf16_t*>(dgu),
                              2 * d_ff, d_ff, dgpart, swiglu_bwd_parts(1, d_ff)};
-    return run_tile<TileBwdGU>(A, B, epi, counts, n_max, d_ff, d, s);
+    return run_phase<true>(A, B, epi, counts, n_max, d_ff, d, s, exact);
   }
   ARows<float> A{static_cast<const float*>(u), idx_ffn, d};
   BRows<float> B{static_cast<const float*>(w_gate), static_cast<const float*>(w_up), INT_MAX, d};
@@ -2483,13 +2516,13 @@ hipError_t launch_ffn_bwd_gateup(int dtype, const void* u, const int* idx_ffn, c
 }
 
 hipError_t launch_ffn_bwd_du(int dtype, const void* dgu, const int* counts, int n_max, const void* w_gate_up_t,
-                             float* du, int d, int d_ff, hipStream_t s) {
+                             float* du, int d, int d_ff, bool exact, hipStream_t s) {
   if (n_max <= 0) return hipSuccess;
   const int K = 2 * d_ff;
   if (dtype == 1) {
     ARows<bf16_t> A{static_cast<const bf16_t*>(dgu), nullptr, K};
     BRows<bf16_t> B{static_cast<const bf16_t*>(w_gate_up_t), nullptr, INT_MAX, K};
-    return run_big<256, false>(A, B, EpiStoreF32{du, d, 0}, counts, n_max, d, K, s);
+    return run_phase<false>(A, B, EpiStoreF32{du, d, 0}, counts, n_max, d, K, s, exact);
   }
   ARows<float> A{static_cast<const float*>(dgu), nullptr, K};
   BRows<float> B{static_cast<const float*>(w_gate_up_t), nullptr, INT_MAX, K};
