@@ -817,7 +817,7 @@ __global__ __launch_bounds__(512, 2) void phase_gemm(ARows<bf16_t> A, BRows<bf16
 // relative duration of a round (measured on the Llama-3.1-8B gate/up and down shapes at 0.4k to 20k
 // rows: 54-57, 78 and 97 us for 128-, 192- and 256-row tiles at K = 4096; 187, 258 and 345 at
 // 14336).  The smaller tiles move more bytes per product and only pay while their finer rounds
-// leave fewer CUs idle, so beyond two (128) and eight (192) rounds they are not considered.
+// leave fewer CUs idle, so beyond four (128) and eight (192) rounds they are not considered.
 __host__ __device__ inline int phase_rows(int M, int n_tiles) {
   auto tiles = [&](int BM) { return (M + BM - 1) / BM * n_tiles; };
   auto cost = [&](int BM, int w) { return (tiles(BM) + kCUs - 1) / kCUs * w; };
@@ -826,7 +826,7 @@ __host__ __device__ inline int phase_rows(int M, int n_tiles) {
     best = 192;
     c = cost(192, 100);
   }
-  if (tiles(128) <= 2 * kCUs && cost(128, 75) < c) best = 128;
+  if (tiles(128) <= 4 * kCUs && cost(128, 75) < c) best = 128;
   return best;
 }
 
@@ -856,7 +856,7 @@ hipError_t run_phase(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_cou
   const auto blocks = [&](int BM) { return ((M_max + BM - 1) / BM * n_tiles + 7) / 8 * 8; };
   if (!exact && m_count) {
     // enough for any choice at any count up to M_max
-    const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 2 * kCUs)});
+    const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 4 * kCUs)});
     phase_gemm_any<DUAL, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
     return hipGetLastError();
   }
@@ -865,6 +865,17 @@ hipError_t run_phase(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_cou
     case 192: phase_gemm<Phase<192, DUAL>, Epi><<<blocks(192), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
     default: phase_gemm<Phase<128, DUAL>, Epi><<<blocks(128), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
   }
+  return hipGetLastError();
+}
+
+// K split S ways over 128-row tiles, for products of too few tiles to fill the CUs
+template <class Epi>
+hipError_t run_phase_split(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_count, int M_max, int N_out, int K,
+                           int S, hipStream_t s) {
+  using C = Phase<128, false>;
+  const int n_tiles = N_out / C::OUT_N;
+  const dim3 grid(((M_max + 127) / 128 * n_tiles + 7) / 8 * 8, S);
+  phase_gemm<C, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
   return hipGetLastError();
 }
 
@@ -1835,7 +1846,6 @@ namespace {
 // over them adds the S slices in a fixed order and finishes the epilogue.
 // ---------------------------------------------------------------------------
 using TileSplitGU = Tile<192, 256, 2, 4>;    // [W_g; W_u] as one 2 d_ff-row operand
-using TileSplitDown = Tile<192, 128, 2, 4, 4>;
 constexpr int kMaxSplitGU = 8, kMaxSplitDown = 16;
 
 // At most 256 rows (a decode batch): the skinny products.  Gate/up: one workgroup per CU, each
@@ -1929,9 +1939,17 @@ int gateup_split(int n, int d, int d_ff) {
   return split_ways((n + TileSplitGU::BM - 1) / TileSplitGU::BM * (2 * d_ff / TileSplitGU::OUT_N),
                     d / BK, kMaxSplitGU);
 }
+// K-slices that the workspace holds for the down product of n rows (192 x 128 tiles: the layout that
+// the workspace size and the no-allocation limit are stated for)
+int down_split_space(int n, int d, int d_ff) {
+  return split_ways((n + 191) / 192 * (d / 128), d_ff / BK, kMaxSplitDown);
+}
+// ... and that its 128 x 256 tiles take: the most that fit one round of workgroups, of at least two
+// k-tiles.  8B shape, 390 of at most 640 rows: 85 us in two slices of 192 x 128 tiles, 57 in three.
 int down_split(int n, int d, int d_ff) {
-  return split_ways((n + TileSplitDown::BM - 1) / TileSplitDown::BM * (d / TileSplitDown::OUT_N),
-                    d_ff / BK, kMaxSplitDown);
+  const int S = split_ways((n + 127) / 128 * (d / 256), d_ff / BK / 2, kMaxSplitDown);
+  const size_t space = ffn_part_floats(1, d, d_ff, n) / (static_cast<size_t>(n) * d);
+  return std::max(1, std::min(S, static_cast<int>(std::min<size_t>(space, kMaxSplitDown))));
 }
 
 // act[m][c] = bf16(SiLU(g) u) with g, u the sums over z < S of P[z][m][c] and P[z][m][d_ff + c];
@@ -2054,7 +2072,7 @@ size_t ffn_part_floats(int dtype, int d, int d_ff, int T) {
   if (skinny_down_fits(ns, d, d_ff)) most = static_cast<size_t>(skinny_down_splits(d, d_ff)) * ns * d;
   for (int mt = 1; (mt - 1) * TileSplitGU::BM < T; ++mt) {
     const int n = std::min(mt * TileSplitGU::BM, T);
-    const int sg = gateup_split(n, d, d_ff), sd = down_split(n, d, d_ff);
+    const int sg = gateup_split(n, d, d_ff), sd = down_split_space(n, d, d_ff);
     if (sg > 1) most = std::max(most, static_cast<size_t>(sg) * n * 2 * d_ff);
     if (sd > 1) most = std::max(most, static_cast<size_t>(sd) * n * d);
     if (sg == 1 && sd == 1) break;   // both counts only grow from here
@@ -2116,8 +2134,7 @@ hipError_t launch_ffn_down(int dtype, const void* act, const int* idx_ffn, const
       hipError_t e = skinny ? skinny_down(A, static_cast<const bf16_t*>(w_down),
                                           static_cast<const bf16_t*>(w_down_tiled), part, stride, counts,
                                           n_max, d, d_ff, S, s)
-                            : run_tile<TileSplitDown>(A, B, EpiStoreF32{part, d, stride}, counts, n_max, d,
-                                                      d_ff, s, S);
+                            : run_phase_split(A, B, EpiStoreF32{part, d, stride}, counts, n_max, d, d_ff, S, s);
       if (e != hipSuccess) return e;
       const size_t n8 = static_cast<size_t>(n_max) * (d / 8);
       scatter_reduce<<<static_cast<unsigned>((n8 + 255) / 256), 256, 0, s>>>(

@@ -1014,12 +1014,12 @@ constexpr int NWT = NTT / kWave;
 constexpr int kTokenMaxS = 64;           // widths the thread layout covers: d_s, d_h, d_a
 constexpr int kTokenMaxP = 128;          // d_p
 constexpr int kHistMax = 64;             // stored pairs
-// Most tokens of a call: one round of workgroups with bf16 weights, eight with fp32, whose three
+// Most tokens of a call: three rounds of workgroups with bf16 weights, eight with fp32, whose three
 // kernels are VALU chains.  Measured against the three kernels, a layer of d = 4096, d_ff = 14336,
-// d_m = 128 (bf16): 126 -> 117 us at 1 token, 186 -> 174 at 256, 223 -> 225 at 400, 365 -> 388 at
-// 1024; depth-history memory 156 -> 137 at 48.  fp32, four layers of d = 256, d_m = 32:
-// 426 -> 208 us at 300 tokens, 614 -> 569 at 2048, 818 -> 989 at 4096.
-constexpr int kTokenRowsBf16 = 256, kTokenRowsF32 = 2048;
+// d_m = 128 (bf16): 187 -> 178 us at 300 tokens, 214 -> 205 at 512, 311 -> 307 at 768, 328 -> 330 at
+// 1024; d_m = 256 at 512 tokens 256 -> 246, depth-history memory 208 -> 198.  fp32, four layers of
+// d = 256, d_m = 32: 426 -> 208 us at 300 tokens, 614 -> 569 at 2048, 818 -> 989 at 4096.
+constexpr int kTokenRowsBf16 = 768, kTokenRowsF32 = 2048;
 
 template <typename W, int PI, int R>
 struct TokenMat {

@@ -33,7 +33,7 @@ def test_memory_forms(dtype, d_m, state, history, j):
     _layer(BASE.replace(dtype=dtype, d_m=d_m, state_dtype=state), j, history)
 
 
-@pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 256), ("bf16", 257), ("f32", 2048), ("f32", 2049)])
+@pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 768), ("bf16", 769), ("f32", 2048), ("f32", 2049)])
 def test_token_limit_and_narrow_router(dtype, T):
     _layer(BASE.replace(dtype=dtype, T=T, d_m=32, **NARROW), 5)
 
