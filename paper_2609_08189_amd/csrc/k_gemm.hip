@@ -38,6 +38,10 @@ struct ARows {
   const T* base;
   const int* idx;  // null: identity
   int ld;
+  // products of two terms (an epilogue with kTwoTerm): the operand from k-tile `turn` on, where B
+  // starts over
+  const T* base2 = nullptr;
+  int turn = 0;
   __device__ __forceinline__ const T* row(int m) const {
     return base + static_cast<size_t>(idx ? idx[m] : m) * ld;
   }
@@ -540,6 +544,12 @@ struct DualHook : std::false_type {};
 template <class E>
 struct DualHook<E, std::void_t<decltype(E::kDualHook)>> : std::true_type {};
 
+// An epilogue with kTwoTerm ends a product of two terms, A B^T + A2 B^T (ARows::base2)
+template <class E, class = void>
+struct TwoTerm : std::false_type {};
+template <class E>
+struct TwoTerm<E, std::void_t<decltype(E::kTwoTerm)>> : std::true_type {};
+
 template <int BM_, bool DUAL_>
 struct Phase {
   static constexpr int WN = 4, NW = 8, NT = 512;
@@ -606,20 +616,24 @@ __device__ __forceinline__ void phase_tile(const ARows<bf16_t>& A, const BRows<b
   const int nkt = K / BK;
   const int kt0 = static_cast<int>(blockIdx.y) * nkt / static_cast<int>(gridDim.y);
   const int nk = (static_cast<int>(blockIdx.y) + 1) * nkt / static_cast<int>(gridDim.y) - kt0;
-#pragma unroll
-  for (int i = 0; i < C::A_LD; ++i) a_off[i] += kt0 * ROWB;
-#pragma unroll
-  for (int i = 0; i < 2 * BH; ++i) b_off[i] += kt0 * ROWB;
-  auto ldA = [&](int i, int stage, uint32_t kb) {
-    load_lds16((a_base + kb) + a_off[i], smem + stage * C::STAGE + (i * NW + wave) * 1024);
+  const unsigned char* a_base2 = reinterpret_cast<const unsigned char*>(A.base2);
+  // i-th load of the wave, k-tile kt of the slice
+  auto ldA = [&](int i, int kt) {
+    const int k = kt0 + kt;
+    const bool two = TwoTerm<Epi>::value && k >= A.turn;
+    const unsigned char* base = (two ? a_base2 : a_base) + static_cast<uint32_t>(two ? k - A.turn : k) * ROWB;
+    load_lds16(base + a_off[i], smem + (kt & 1) * C::STAGE + (i * NW + wave) * 1024);
   };
-  auto ldB = [&](int i, int stage, uint32_t kb) {
-    load_lds16((b_base[i] + kb) + b_off[i], smem + stage * C::STAGE + BM * ROWB + (i * NW + wave) * 1024);
+  auto ldB = [&](int i, int kt) {
+    const int k = kt0 + kt;
+    const bool two = TwoTerm<Epi>::value && k >= A.turn;
+    const unsigned char* base = b_base[i] + static_cast<uint32_t>(two ? k - A.turn : k) * ROWB;
+    load_lds16(base + b_off[i], smem + (kt & 1) * C::STAGE + BM * ROWB + (i * NW + wave) * 1024);
   };
   // group 1: the first half of A and B; group 2: the rest (the piece of A that both halves share first)
-  auto ld1 = [&](int i, int kt) { i < C::A1 ? ldA(i, kt & 1, kt * ROWB) : ldB(i - C::A1, kt & 1, kt * ROWB); };
+  auto ld1 = [&](int i, int kt) { i < C::A1 ? ldA(i, kt) : ldB(i - C::A1, kt); };
   auto ld2 = [&](int i, int kt) {
-    i < C::A_LD - C::A1 ? ldA(C::A1 + i, kt & 1, kt * ROWB) : ldB(BH + i - (C::A_LD - C::A1), kt & 1, kt * ROWB);
+    i < C::A_LD - C::A1 ? ldA(C::A1 + i, kt) : ldB(BH + i - (C::A_LD - C::A1), kt);
   };
 
   f32x4 acc[2 * HM][2 * HB];
@@ -779,8 +793,8 @@ __device__ __forceinline__ void phase_tile(const ARows<bf16_t>& A, const BRows<b
         pre[a][p] = epi.prep(min(row_of(a, e / CPR), M - 1), col_of((e % CPR) * 8));
       }
     };
-    // what the epilogue combines with (hbar rows) is fetched four fragments ahead of the staging
-    constexpr int AHEAD = 4;
+    // what the epilogue combines with (hbar rows) is fetched some fragments ahead of the staging
+    constexpr int AHEAD = TwoTerm<Epi>::value ? 2 : 4;
 #pragma unroll
     for (int a = 0; a < AHEAD; ++a) fetch(a);
 #pragma unroll
@@ -2604,32 +2618,92 @@ struct EpiAccF32 {  // C[m][n] += acc
 };
 }  // namespace
 
+// The router's backward, its two large products.  dP enters as two bf16 terms, hi + lo, in one
+// product each, so that the fp32 result is touched once.
 namespace {
-struct EpiAccF32Mfma {  // C[m][n] += acc on the MFMA path (each element owned by one lane)
+struct EpiStoreF32Two : EpiStoreF32 {
+  static constexpr bool kTwoTerm = true;
+};
+
+// dhbar[t][n] += acc + the row's RMSNorm and transition terms, c_norm hbar + ddelta with
+// ddelta = c1 delta_j + c2 delta_{j-1} (rowcoef), so that this is the only pass over dhbar
+struct EpiRouterDh {
+  static constexpr bool kTwoTerm = true;
   float* out;
   int ld;
-  struct Pre {};
-  __device__ __forceinline__ Pre prep(int, int) const { return {}; }
-  __device__ __forceinline__ void emit8(const Pre&, int m, int n, const float* v) const {
-    float* o = out + static_cast<size_t>(m) * ld + n;
-    f32x4 a = *reinterpret_cast<const f32x4*>(o), b = *reinterpret_cast<const f32x4*>(o + 4);
+  const float* coef;                   // [T][8]
+  const bf16_t *h0, *h1, *h2;          // hbar_j, hbar_{j-1} (or null), hbar_{j-2} (or null)
+  struct Pre {
+    f32x4 o[2];
+    u32x4 x, y, z;
+    f32x4 c;
+  };
+  __device__ __forceinline__ Pre prep(int m, int n) const {
+    Pre p;
+    const size_t e = static_cast<size_t>(m) * ld + n;
+    p.o[0] = *reinterpret_cast<const f32x4*>(out + e);
+    p.o[1] = *reinterpret_cast<const f32x4*>(out + e + 4);
+    p.c = *reinterpret_cast<const f32x4*>(coef + 8 * static_cast<size_t>(m));
+    p.x = *reinterpret_cast<const u32x4*>(h0 + e);
+    p.y = h1 ? *reinterpret_cast<const u32x4*>(h1 + e) : p.x;
+    p.z = h2 ? *reinterpret_cast<const u32x4*>(h2 + e) : p.y;
+    return p;
+  }
+  __device__ __forceinline__ void emit8(const Pre& p, int m, int n, const float* v) const {
+    float r[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      a[i] += v[i];
-      b[i] += v[4 + i];
+    for (int k = 0; k < 8; ++k) {
+      const auto at = [k](const u32x4& w) {
+        return __uint_as_float(k & 1 ? w[k >> 1] & 0xffff0000u : w[k >> 1] << 16);
+      };
+      const float x = at(p.x), y = at(p.y), z = at(p.z);
+      r[k] = p.o[k >> 2][k & 3] + v[k] + (p.c[0] * x + (p.c[1] * (x - y) + p.c[2] * (y - z)));
     }
-    *reinterpret_cast<f32x4*>(o) = a;
-    *reinterpret_cast<f32x4*>(o + 4) = b;
+    float* o = out + static_cast<size_t>(m) * ld + n;
+    *reinterpret_cast<f32x4*>(o) = *reinterpret_cast<const f32x4*>(r);
+    *reinterpret_cast<f32x4*>(o + 4) = *reinterpret_cast<const f32x4*>(r + 4);
   }
 };
+
+// C0 rows [0, m0), then C1: C[m][n] += sum over z < S of part[z][m][n], four columns a thread
+__global__ __launch_bounds__(256) void acc_slices_kernel(const float* __restrict__ part, int S, int M, int N, int m0,
+                                                        float* __restrict__ C0, float* __restrict__ C1) {
+  const size_t e = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) * 4, n = static_cast<size_t>(M) * N;
+  if (e >= n) return;
+  f32x4 v = *reinterpret_cast<const f32x4*>(part + e);
+  for (int z = 1; z < S; ++z) v += *reinterpret_cast<const f32x4*>(part + z * n + e);
+  const size_t split = static_cast<size_t>(m0) * N;
+  f32x4* c = reinterpret_cast<f32x4*>(e < split ? C0 + e : C1 + (e - split));
+  *c += v;
+}
 }  // namespace
 
-hipError_t launch_gemm_nt_acc_bf16(const void* A, int lda, int M, const void* B, int ldb, int N, int K, float* C,
-                                   int ldc, hipStream_t s) {
-  if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-  ARows<bf16_t> a{static_cast<const bf16_t*>(A), nullptr, lda};
-  BRows<bf16_t> b{static_cast<const bf16_t*>(B), nullptr, INT_MAX, ldb};
-  return run_tile<TileWide>(a, b, EpiAccF32Mfma{C, ldc}, nullptr, M, N, K, s);
+int router_bwd_dw_slices(int NP, int d, int kp) {
+  const int tiles = (NP + 127) / 128 * (d / 256);
+  return std::max(1, std::min({8, kCUs / std::max(tiles, 1), kp / BK}));
+}
+
+hipError_t launch_router_bwd_dw(const void* hi, const void* lo, int kp, int d_e, int NP, const void* hT, int d,
+                                float* part, float* w_hd, float* ps1, hipStream_t s) {
+  ARows<bf16_t> A{static_cast<const bf16_t*>(hi), nullptr, kp, static_cast<const bf16_t*>(lo), kp / BK};
+  BRows<bf16_t> B{static_cast<const bf16_t*>(hT), nullptr, INT_MAX, kp};
+  const int S = router_bwd_dw_slices(NP, d, kp);
+  EpiStoreF32Two epi{{part, d, static_cast<size_t>(NP) * d}};
+  const hipError_t e = run_phase_split(A, B, epi, nullptr, NP, d, 2 * kp, S, s);
+  if (e != hipSuccess) return e;
+  const size_t n4 = static_cast<size_t>(NP) * d / 4;
+  acc_slices_kernel<<<static_cast<unsigned>((n4 + 255) / 256), 256, 0, s>>>(part, S, NP, d, d_e, w_hd, ps1);
+  return hipGetLastError();
+}
+
+hipError_t launch_router_bwd_dh(const void* hi, const void* lo, int T, int NP, const void* wT, int d,
+                                const float* coef, const void* hbar, const void* prev1, const void* prev2,
+                                float* dhbar, hipStream_t s) {
+  ARows<bf16_t> A{static_cast<const bf16_t*>(hi), nullptr, NP, static_cast<const bf16_t*>(lo), NP / BK};
+  BRows<bf16_t> B{static_cast<const bf16_t*>(wT), nullptr, INT_MAX, NP};
+  EpiRouterDh epi{dhbar, d, coef, static_cast<const bf16_t*>(hbar), static_cast<const bf16_t*>(prev1),
+                  static_cast<const bf16_t*>(prev2)};
+  return run_phase<false>(A, B, epi, nullptr, T, d, 2 * NP, s);
 }
 
 hipError_t launch_gemm_acc_f32(const float* A, int lda, int M, const float* B, int ldb, int N, int K, float* C,

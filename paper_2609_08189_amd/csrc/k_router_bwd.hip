@@ -1317,7 +1317,8 @@ __device__ __forceinline__ void rows_rmw8(float* p, const float* v) {
   q[0] = u0;
   q[1] = u1;
 }
-template <typename T>
+// SELF: dhbar_j's terms here (fp32 storage; with bf16 they ride on the product that adds into it)
+template <typename T, bool SELF>
 __global__ __launch_bounds__(256) void router_bwd_rows(RouterBwdArgs a) {
   const int t = blockIdx.x, j = a.j, d = a.d;
   const float* rc = a.rowcoef + static_cast<size_t>(t) * 8;
@@ -1340,7 +1341,7 @@ __global__ __launch_bounds__(256) void router_bwd_rows(RouterBwdArgs a) {
       g1[k] = gp - gj;
       g2[k] = -gp;
     }
-    rows_rmw8(a.dhbar + row + i, g0);
+    if (SELF) rows_rmw8(a.dhbar + row + i, g0);
     if (j >= 2) rows_rmw8(a.dhbar1 + row + i, g1);
     if (j >= 3) rows_rmw8(a.dhbar2 + row + i, g2);
   }
@@ -1804,10 +1805,10 @@ hipError_t launch_router_bwd_chain(const RouterBwdArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_router_bwd_rows(const RouterBwdArgs& a, hipStream_t s) {
-  if (a.dtype == 1)
-    router_bwd_rows<bf16_t><<<a.T, 256, 0, s>>>(a);
-  else
-    router_bwd_rows<float><<<a.T, 256, 0, s>>>(a);
+  if (a.dtype != 1)
+    router_bwd_rows<float, true><<<a.T, 256, 0, s>>>(a);
+  else if (a.j >= 2)
+    router_bwd_rows<bf16_t, false><<<a.T, 256, 0, s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   router_bwd_deta<<<1, RB_DETA_NT, 0, s>>>(a.rho_part, a.T, a.rho, a.deta);
