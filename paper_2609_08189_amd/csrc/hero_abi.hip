@@ -326,13 +326,15 @@ int run_layer(const LayerCall& c) {
   hipError_t e = hipSuccess;
   const void* prev1 = c.j >= 2 ? c.prev1 : nullptr;
   const void* prev2 = c.j >= 3 ? c.prev2 : nullptr;
-  if (decode_head_fits(D.dtype, T, D.d, D.d_e, D.d_e + D.d_head)) {
+  const bool f32_head = f32_head_fits(D.dtype, T, D.d_e + D.d_head);
+  if (f32_head || decode_head_fits(D.dtype, T, D.d, D.d_e, D.d_e + D.d_head)) {
     // few tokens: the row pass and the router's product in one launch, timed as the product
     e = timed(HERO_K_ROWSTATS, st, nothing);
     if (e == hipSuccess)
       e = timed(HERO_K_ROUTER_GEMM, st, [&] {
-        return launch_decode_head(c.hbar, prev1, prev2, c.ffn->norm_w, c.rt->w_hd, c.rt->ps1, T, D.d, D.d_e, D.d_head,
-                                  c.j, D.eps_norm, P, rowstat, u, st);
+        return (f32_head ? launch_f32_head : launch_decode_head)(
+            c.hbar, prev1, prev2, c.ffn->norm_w, c.rt->w_hd, c.rt->ps1, T, D.d, D.d_e, D.d_head, c.j, D.eps_norm, P,
+            rowstat, u, st);
       });
     if (e != hipSuccess) return HERO_E_LAUNCH;
   } else {
@@ -443,17 +445,21 @@ int run_layer(const LayerCall& c) {
   void* act = ws + L.act;
   float* part = reinterpret_cast<float*>(ws + L.part);
   float* part_ad = reinterpret_cast<float*>(ws + L.part_ad);
-  if (decode_route_fits(D.dtype, T, n_ffn_max, D.d, D.d_ff, D.d_r)) {
+  const bool f32_route = f32_route_fits(D.dtype, T, n_ffn_max, n_ad_max, D.d, D.d_ff, D.d_r);
+  if (f32_route || decode_route_fits(D.dtype, T, n_ffn_max, D.d, D.d_ff, D.d_r)) {
     // a decode step: the decision and the adapter's down-projection inside the gate/up launch, the
     // adapter's up-projection with the down product's reduction (timed as the adapter's up)
     const DecodeRoute r{sa, n_ffn_max, n_ad_max, D.d, D.d_ff, D.d_r, u, c.hbar, c.ffn->w_gate, c.ffn->w_up,
                         c.ffn->w_gate_up_tiled, c.ffn->w_down, c.ffn->w_down_tiled, c.ad->w1, c.ad->w2, gate, act,
                         c.h_out, part, part_ad};
     e = timed(HERO_K_SELECT, st, nothing);
-    if (e == hipSuccess) e = timed(HERO_K_FFN_GATE_UP, st, [&] { return launch_route_gateup(r, st); });
-    if (e == hipSuccess) e = timed(HERO_K_FFN_DOWN, st, [&] { return launch_route_down(r, st); });
+    if (e == hipSuccess)
+      e = timed(HERO_K_FFN_GATE_UP, st, [&] { return f32_route ? launch_f32_route_in(r, st) : launch_route_gateup(r, st); });
+    if (e == hipSuccess)
+      e = timed(HERO_K_FFN_DOWN, st, [&] { return f32_route ? launch_f32_route_out(r, st) : launch_route_down(r, st); });
     if (e == hipSuccess) e = timed(HERO_K_ADAPTER_DOWN, st, nothing);
-    if (e == hipSuccess) e = timed(HERO_K_ADAPTER_UP, st, [&] { return launch_route_finish(r, st); });
+    if (e == hipSuccess)
+      e = timed(HERO_K_ADAPTER_UP, st, [&] { return f32_route ? hipSuccess : launch_route_finish(r, st); });
     return e == hipSuccess ? HERO_OK : HERO_E_LAUNCH;
   }
   e = timed(HERO_K_SELECT, st, [&] { return launch_select(sa, st); });

@@ -32,6 +32,11 @@ bool decode_head_tiles_fit(int N);
 hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                                     const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
                                     float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);
+// ... and for fp32 calls whose product has few tiles
+bool f32_head_fits(int dtype, int T, int N);
+hipError_t launch_f32_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                           const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                           float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);
 hipError_t launch_router_gemm(int dtype, const void* hbar, const void* w_hd, const void* ps1,
                               int T, int d, int d_e, int d_head, float* P, hipStream_t s);
 
@@ -135,6 +140,11 @@ bool decode_route_fits(int dtype, int T, int n_ffn_max, int d, int d_ff, int d_r
 hipError_t launch_route_gateup(const DecodeRoute& r, hipStream_t s);
 hipError_t launch_route_down(const DecodeRoute& r, hipStream_t s);
 hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s);
+// The same in two launches for fp32 calls of at most 256 tokens whose products have few tiles: decision,
+// gate/up and the adapter's down-projection; down and the adapter's up-projection
+bool f32_route_fits(int dtype, int T, int n_ffn_max, int n_ad_max, int d, int d_ff, int d_r);
+hipError_t launch_f32_route_in(const DecodeRoute& r, hipStream_t s);
+hipError_t launch_f32_route_out(const DecodeRoute& r, hipStream_t s);
 // The frozen FFN weights in the decode products' streaming order (bf16): W [N][K] becomes
 // [K/64][N/16][G][16][64], i.e. 16 x 64 tiles of 2 KiB, k-tile by k-tile, each k-tile's row of
 // 16-row blocks contiguous, with G = 2 matrices alternating tile by tile (W_g then W_u) or G = 1 (W_d).

@@ -1021,8 +1021,9 @@ struct RouteFinish {
 // The branch decision of select_kernel for T <= 256 tokens by one wave: lane l holds tokens
 // l, l + 64, ...  The n_skip-th smallest key is found bit by bit over ballots, its ties by token
 // index.  list receives the FFN tokens in ascending order (256 ints); write: the outputs of
-// SelectArgs too.  Returns the FFN count.
-__device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* list, bool write) {
+// SelectArgs too; adapters (may be null): the other tokens, also ascending.  Returns the FFN count.
+__device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* list, bool write,
+                                           int* adapters = nullptr) {
   constexpr int Q = kRouteTokens / kWave;
   float l[Q];
   uint32_t key[Q];
@@ -1083,6 +1084,7 @@ __device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* l
     const bool f = (ffn >> lane) & 1ull;
     const int pf = nf + __popcll(ffn & below), pa = na + __popcll(ad & below);
     if (f) list[pf] = t;
+    if (adapters && !f && t < a.T) adapters[pa] = t;
     if (write && t < a.T) {
       a.mask[t] = f ? 1 : 0;
       if (f)
@@ -1491,15 +1493,13 @@ __device__ __forceinline__ f32x4 f32_frag(const float* row, int k, int K) {
 }
 
 template <bool DUAL, int R, bool VEC, class Epi>
-__global__ __launch_bounds__(256) void f32_gemm(ARows<float> A, BRows<float> B, Epi epi,
-                                               const int* __restrict__ m_count, int M_fixed,
-                                               int N, int K) {
+__device__ __forceinline__ void f32_tile(const ARows<float>& A, const BRows<float>& B, const Epi& epi, int M, int N,
+                                         int K, int bm, int bn) {
   constexpr int BT = 16 * R;                   // rows and columns of the tile
   constexpr int U = R == 1 ? 8 : 4;            // k-steps per batch of loads
   constexpr int RP = BT + 1;
   __shared__ float red[DUAL ? 2 : 1][4][BT][RP];
-  const int M = m_count ? *m_count : M_fixed;
-  const int m0 = blockIdx.x * BT, n0 = blockIdx.y * BT;
+  const int m0 = bm * BT, n0 = bn * BT;
   if (m0 >= M) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -1574,6 +1574,95 @@ __global__ __launch_bounds__(256) void f32_gemm(ARows<float> A, BRows<float> B, 
   }
 }
 
+template <bool DUAL, int R, bool VEC, class Epi>
+__global__ __launch_bounds__(256) void f32_gemm(ARows<float> A, BRows<float> B, Epi epi,
+                                               const int* __restrict__ m_count, int M_fixed,
+                                               int N, int K) {
+  f32_tile<DUAL, R, VEC>(A, B, epi, m_count ? *m_count : M_fixed, N, K, static_cast<int>(blockIdx.x),
+                         static_cast<int>(blockIdx.y));
+}
+
+// Products of few tiles are bound by their launches and load latencies, so two that do not depend on
+// each other share one: the row pass beside the router's product, the adapter's beside the FFN's
+// (f32_pair), whose first launch also decides the branches, a wave of every workgroup for itself.
+// The 4-layer stack of d = 256 at 64 tokens: 147 us with a launch each, 105 so; 2 layers of d = 2048
+// at 20 tokens 407 -> 181.
+template <bool VEC>
+__global__ __launch_bounds__(256) void f32_head(ARows<float> A, BRows<float> B, EpiStoreF32 epi, int T, int N, int K,
+                                               int mt, int tiles, const float* __restrict__ prev1,
+                                               const float* __restrict__ prev2, const float* __restrict__ norm_w,
+                                               int j, float eps_norm, float* __restrict__ rowstat,
+                                               float* __restrict__ u) {
+  const int b = static_cast<int>(blockIdx.x);
+  if (b >= tiles)
+    rowstats_row<float, 256>(b - tiles, A.base, prev1, prev2, norm_w, K, j, eps_norm, rowstat, u);
+  else
+    f32_tile<false, 1, VEC>(A, B, epi, T, N, K, b % mt, b / mt);
+}
+
+template <class Epi>
+struct F32Job {
+  ARows<float> A;
+  BRows<float> B;
+  Epi epi;
+  int M_max, N, K;
+  bool vec() const {
+    const auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
+    return K % 4 == 0 && A.ld % 4 == 0 && B.ld % 4 == 0 && al(A.base) && al(B.b0) && al(B.b1);
+  }
+  __host__ __device__ int mt() const { return (M_max + 15) / 16; }
+  int tiles() const { return mt() * ((N + 15) / 16); }
+};
+
+// ROUTE: the row lists are decided here (at most kRouteTokens tokens); else sel.counts holds the
+// row counts: [0] of the first job, [1] of the second
+template <bool DUAL, bool V0, bool V1, bool ROUTE, class E0, class E1>
+__global__ __launch_bounds__(256) void f32_pair(F32Job<E0> j0, F32Job<E1> j1, int tiles0, SelectArgs sel) {
+  const int b = static_cast<int>(blockIdx.x);
+  int nf, na;
+  if constexpr (ROUTE) {
+    __shared__ int lists[2][kRouteTokens];
+    __shared__ int s_nf;
+    if (threadIdx.x < kWave) {
+      const int n = select_wave(sel, static_cast<int>(threadIdx.x), lists[0], b == 0, lists[1]);
+      if (threadIdx.x == 0) s_nf = n;
+    }
+    __syncthreads();
+    nf = s_nf;
+    na = sel.T - nf;
+    j0.A.idx = lists[0];
+    j1.A.idx = lists[1];
+  } else {
+    nf = sel.counts[0];
+    na = sel.counts[1];
+  }
+  if (b < tiles0)
+    f32_tile<DUAL, 1, V0>(j0.A, j0.B, j0.epi, nf, j0.N, j0.K, b % j0.mt(), b / j0.mt());
+  else
+    f32_tile<false, 1, V1>(j1.A, j1.B, j1.epi, na, j1.N, j1.K, (b - tiles0) % j1.mt(), (b - tiles0) / j1.mt());
+}
+
+template <bool DUAL, bool ROUTE, class E0, class E1>
+hipError_t run_f32_pair(const F32Job<E0>& j0, const F32Job<E1>& j1, const SelectArgs& sel, hipStream_t s) {
+  const int t0 = j0.tiles(), blocks = t0 + j1.tiles();
+  if (blocks <= 0) return hipSuccess;
+  const bool v0 = j0.vec(), v1 = j1.vec();
+  if (v0 && v1)
+    f32_pair<DUAL, true, true, ROUTE><<<blocks, 256, 0, s>>>(j0, j1, t0, sel);
+  else if (v0)
+    f32_pair<DUAL, true, false, ROUTE><<<blocks, 256, 0, s>>>(j0, j1, t0, sel);
+  else if (v1)
+    f32_pair<DUAL, false, true, ROUTE><<<blocks, 256, 0, s>>>(j0, j1, t0, sel);
+  else
+    f32_pair<DUAL, false, false, ROUTE><<<blocks, 256, 0, s>>>(j0, j1, t0, sel);
+  return hipGetLastError();
+}
+
+// 32 x 32 tiles halve the operand bytes per product once they fill the CUs
+bool f32_tiles_large(int M, int N) {
+  return static_cast<long long>((M + 31) / 32) * ((N + 31) / 32) >= 2 * kCUs;
+}
+
 template <bool DUAL, int R, class Epi>
 hipError_t run_f32_r(ARows<float> A, BRows<float> B, Epi epi, const int* m_count, int M_max, int N,
                      int K, bool vec, hipStream_t s) {
@@ -1589,11 +1678,8 @@ template <bool DUAL, class Epi>
 hipError_t run_f32(ARows<float> A, BRows<float> B, Epi epi, const int* m_count, int M_max, int N,
                    int K, hipStream_t s) {
   if (M_max <= 0 || N <= 0) return hipSuccess;
-  const auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-  const bool vec = K % 4 == 0 && A.ld % 4 == 0 && B.ld % 4 == 0 && al(A.base) && al(B.b0) && al(B.b1);
-  // 32 x 32 tiles halve the operand bytes per product once they fill the CUs
-  const long long t32 = static_cast<long long>((M_max + 31) / 32) * ((N + 31) / 32);
-  if (t32 >= 2 * kCUs) return run_f32_r<DUAL, 2>(A, B, epi, m_count, M_max, N, K, vec, s);
+  const bool vec = F32Job<Epi>{A, B, epi, M_max, N, K}.vec();
+  if (f32_tiles_large(M_max, N)) return run_f32_r<DUAL, 2>(A, B, epi, m_count, M_max, N, K, vec, s);
   return run_f32_r<DUAL, 1>(A, B, epi, m_count, M_max, N, K, vec, s);
 }
 
@@ -1827,6 +1913,28 @@ hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const v
   BRows<bf16_t> B{static_cast<const bf16_t*>(w_hd), static_cast<const bf16_t*>(ps1), d_e, d};
   const dim3 grid(tiles + (T + splits - 1) / splits, splits);
   mfma_gemm<C, EpiStoreF32Rows><<<grid, C::NT, 0, s>>>(A, B, epi, nullptr, T, d, mt, nt);
+  return hipGetLastError();
+}
+
+bool f32_head_fits(int dtype, int T, int N) { return dtype != 1 && !f32_tiles_large(T, N); }
+
+hipError_t launch_f32_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
+                           const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
+                           float eps_norm, float* P, float* rowstat, void* u, hipStream_t s) {
+  const int N = d_e + d_head;
+  const F32Job<EpiStoreF32> g{{static_cast<const float*>(hbar), nullptr, d},
+                              {static_cast<const float*>(w_hd), static_cast<const float*>(ps1), d_e, d},
+                              {P, N, static_cast<size_t>(T) * N}, T, N, d};
+  const int tiles = g.tiles();
+  const auto run = [&](auto kernel) {
+    kernel<<<tiles + T, 256, 0, s>>>(g.A, g.B, g.epi, T, N, d, g.mt(), tiles, static_cast<const float*>(prev1),
+                                     static_cast<const float*>(prev2), static_cast<const float*>(norm_w), j, eps_norm,
+                                     rowstat, static_cast<float*>(u));
+  };
+  if (g.vec())
+    run(f32_head<true>);
+  else
+    run(f32_head<false>);
   return hipGetLastError();
 }
 
@@ -2426,6 +2534,35 @@ hipError_t launch_adapter_up(int dtype, const float* part, const int* idx_ad, co
 bool decode_route_fits(int dtype, int T, int n_ffn_max, int d, int d_ff, int d_r) {
   return dtype == 1 && T <= kRouteTokens && n_ffn_max > 0 && !adapter_wide(d_r) && d % 256 == 0 &&
          skinny_gateup_fits(n_ffn_max, d, d_ff) && skinny_down_fits(n_ffn_max, d, d_ff);
+}
+
+// fp32, few tiles in each product: the decision rides with the first pair as long as one wave holds
+// the tokens
+bool f32_route_fits(int dtype, int T, int n_ffn_max, int n_ad_max, int d, int d_ff, int d_r) {
+  return dtype != 1 && T <= kRouteTokens && !f32_tiles_large(n_ffn_max, d_ff) && !f32_tiles_large(n_ffn_max, d) &&
+         !f32_tiles_large(n_ad_max, d_r) && !f32_tiles_large(n_ad_max, d);
+}
+
+hipError_t launch_f32_route_in(const DecodeRoute& r, hipStream_t s) {
+  const float* u = static_cast<const float*>(r.u);
+  const F32Job<EpiSwiGLU<float>> f{{u, nullptr, r.d},
+                                   {static_cast<const float*>(r.w_gate), static_cast<const float*>(r.w_up), INT_MAX, r.d},
+                                   {static_cast<float*>(r.act), r.d_ff}, r.n_ffn_max, r.d_ff, r.d};
+  const F32Job<EpiSiLU<float>> a{{u, nullptr, r.d}, {static_cast<const float*>(r.w1), nullptr, INT_MAX, r.d},
+                                 {r.part_ad, r.d_r}, r.n_ad_max, r.d_r, r.d};
+  return run_f32_pair<true, true>(f, a, r.sel, s);
+}
+
+hipError_t launch_f32_route_out(const DecodeRoute& r, hipStream_t s) {
+  const float* hb = static_cast<const float*>(r.hbar);
+  float* out = static_cast<float*>(r.h_out);
+  const F32Job<EpiScatter<float, false>> f{{static_cast<const float*>(r.act), nullptr, r.d_ff},
+                                           {static_cast<const float*>(r.w_down), nullptr, INT_MAX, r.d_ff},
+                                           {r.sel.idx_ffn, hb, r.gate, out, r.d}, r.n_ffn_max, r.d, r.d_ff};
+  const F32Job<EpiScatter<float, true>> a{{r.part_ad, nullptr, r.d_r},
+                                          {static_cast<const float*>(r.w2), nullptr, INT_MAX, r.d_r},
+                                          {r.sel.idx_ad, hb, r.gate, out, r.d}, r.n_ad_max, r.d, r.d_r};
+  return run_f32_pair<false, false>(f, a, r.sel, s);
 }
 
 namespace {

@@ -19,3 +19,18 @@ def test_f32_layer_products(T, d, d_ff, d_r):
     dp = DeviceProblem(prob)
     dp.run_layer(3)
     check_layer(prob, dp.results(), 3)
+
+
+@pytest.mark.parametrize("mode,budget", [("budget", 0.0), ("budget", 0.3), ("budget", 1.0), ("threshold", 0.0)])
+@pytest.mark.parametrize("T,d_ff,d_r", [(1, 40, 16), (16, 41, 17), (65, 688, 5), (255, 48, 16), (256, 160, 15), (257, 48, 16)])
+def test_f32_shared_launches(T, d_ff, d_r, mode, budget):
+    """Calls of at most 256 tokens decide the branches inside the first of two shared launches: both branches, one
+    only, row pitches with and without 16-byte loads in either product, and the first size past them."""
+    from paper_2609_08189_amd.device import DeviceProblem
+    print(f"case T={T} d_ff={d_ff} d_r={d_r} mode={mode} budget={budget}", flush=True)
+    w = synth.Workload("f32_pairs", "f32", d=128, d_ff=d_ff, d_r=d_r, L_R=4, d_m=32, T=T, mode=mode, budget=budget,
+                       bias="spread")
+    prob = synth.make_problem(w, seed=T, layer_j=3)
+    dp = DeviceProblem(prob)
+    dp.run_layer(3)
+    check_layer(prob, dp.results(), 3)

@@ -1,7 +1,7 @@
 """The large bf16 products on each tile height (128, 192 and 256 rows), chosen on the host (budget mode: the row
 count is known) and on the device (threshold mode): forward and backward of a routed layer against the oracle, with
-row counts off the tiles.  22 column tiles of the gate/up product: 10 to 11 row tiles of 128, 8 of 192 and 16 of 192,
-and 9 of 256 finish in the fewest rounds of 256 workgroups."""
+row counts off the tiles.  22 column tiles of the gate/up product: 11 row tiles of 128, 8 and 16 of 192 and 9 of 256
+finish in the fewest rounds of 256 workgroups; from 257 to 1001 rows the down product's 128-row tiles split K."""
 import pytest
 
 from paper_2609_08189_amd import synth
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("mode", ["budget", "threshold"])
-@pytest.mark.parametrize("T", [1365, 1501, 2203, 3001])
+@pytest.mark.parametrize("T", [257, 639, 1001, 1365, 1501, 2203, 3001])
 def test_layer(T, mode):
     from paper_2609_08189_amd.device import DeviceProblem
     print(f"case T={T} mode={mode}", flush=True)
