@@ -11,7 +11,7 @@
 // chunks keeps both index lists in ascending token order.
 // One workgroup of 1024 threads does the whole layer: the work is ~10 bytes per
 // token and the cost is latency, so each thread keeps its tokens' logits in registers
-// (up to 32 chunks of 1024 tokens) for the six passes instead of reading them again.
+// (up to 32768 tokens) for the six passes instead of reading them again.
 #include "hero_device.h"
 #include "hero_kernels.h"
 
@@ -25,7 +25,7 @@ __device__ __forceinline__ int lane_prefix(unsigned long long bal, int lane) {
   return __popcll(bal & ((1ull << lane) - 1ull));
 }
 
-// R > 0: token t = tid + NT r (r < R) keeps its logit in a register for all passes (T <= NT R);
+// R == 1: token t = tid keeps its logit in a register for all passes (T <= NT);
 // R == 0: every pass reads the logits again (any T).
 template <int R>
 struct Logits {
@@ -204,13 +204,14 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Large batches: thread i owns the contiguous run of R tokens [i R, (i + 1) R).  The radix
+// More than 1024 tokens: thread i owns the contiguous run of R tokens [i R, (i + 1) R).  The radix
 // select takes 11-bit digits (three passes), and each thread adds its run's digits to the LDS
 // histogram run-length encoded: the logits of an untrained router cluster, so the leading
 // digits of a run are mostly equal and one atomic add covers many tokens.  The tie rank and the
 // compaction each need one block-wide scan of per-thread counts (every thread then writes its
 // own run in token order), instead of a barrier pair per 1024-token chunk.  Same decisions,
-// index lists, counts and lambda as select_kernel (the result is unique).
+// index lists, counts and lambda as select_kernel (the result is unique).  Against select_kernel on
+// chunks of 1024: 16.7 -> 12.5 us at 4096 tokens (budget), 6.3 -> 5.3 us at 2777 (threshold).
 // ---------------------------------------------------------------------------
 
 // exclusive prefix over the block of one int per thread; *total receives the block sum
@@ -240,6 +241,7 @@ template <int R>
 __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
   static_assert(R % 4 == 0, "runs are read as float4");
   constexpr int DB = 11, NB = 1 << DB;          // digit bits and histogram bins
+  static_assert(NB == 2 * NT, "two bins per thread");
   __shared__ uint32_t hist[NB];
   __shared__ int wsum[NW];
   __shared__ float wmin[NW];
@@ -306,29 +308,14 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
       }
       if (cnt) atomicAdd(&hist[last], cnt);
       __syncthreads();
-      if (wave == 0) {
-        // lane l owns bins [32 l, 32 l + 32); inclusive scan of their sums across the wave
-        uint32_t sum = 0;
-        for (int i = 0; i < NB / 64; ++i) sum += hist[(NB / 64) * lane + i];
-        uint32_t incl = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const uint32_t u = __shfl_up(incl, off, 64);
-          if (lane >= off) incl += u;
-        }
-        const int k = s_k;
-        uint32_t before = incl - sum;
-        if (static_cast<int>(before) < k && k <= static_cast<int>(incl)) {
-          int dgt = (NB / 64) * lane;
-          for (int i = 0; i < NB / 64; ++i) {
-            const uint32_t h = hist[dgt];
-            if (static_cast<int>(before + h) >= k) break;
-            before += h;
-            ++dgt;
-          }
-          s_prefix = prefix | (static_cast<uint32_t>(dgt) << shift);
-          s_k = k - static_cast<int>(before);
-        }
+      // thread i owns bins 2 i and 2 i + 1
+      const int k = s_k, h0 = static_cast<int>(hist[2 * tid]), h1 = static_cast<int>(hist[2 * tid + 1]);
+      int tot;
+      const int before = block_exclusive_scan(h0 + h1, wsum, &tot);
+      if (before < k && k <= before + h0 + h1) {
+        const int second = k > before + h0 ? 1 : 0;
+        s_prefix = prefix | (static_cast<uint32_t>(2 * tid + second) << shift);
+        s_k = k - before - (second ? h0 : 0);
       }
       __syncthreads();
     }
@@ -426,25 +413,17 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
 }  // namespace
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
-  const int chunks = (a.T + NT - 1) / NT;
-  // large batches: contiguous runs per thread (one scan per phase instead of a barrier pair per
-  // chunk; up to 32768 tokens)
-  if (a.T > 8 * NT && a.T <= 16 * NT) {
-    select_run_kernel<16><<<1, NT, 0, s>>>(a);
-    return hipGetLastError();
-  }
-  if (a.T > 16 * NT && a.T <= 32 * NT) {
-    select_run_kernel<32><<<1, NT, 0, s>>>(a);
-    return hipGetLastError();
-  }
-  if (chunks <= 1)
+  // above 1024 tokens contiguous runs per thread; runs past 32 tokens would spill
+  if (a.T <= NT)
     select_kernel<1><<<1, NT, 0, s>>>(a);
-  else if (chunks <= 4)
-    select_kernel<4><<<1, NT, 0, s>>>(a);
-  else if (chunks <= 8)
-    select_kernel<8><<<1, NT, 0, s>>>(a);
-  else if (chunks <= 32)
-    select_kernel<32><<<1, NT, 0, s>>>(a);
+  else if (a.T <= 4 * NT)
+    select_run_kernel<4><<<1, NT, 0, s>>>(a);
+  else if (a.T <= 8 * NT)
+    select_run_kernel<8><<<1, NT, 0, s>>>(a);
+  else if (a.T <= 16 * NT)
+    select_run_kernel<16><<<1, NT, 0, s>>>(a);
+  else if (a.T <= 32 * NT)
+    select_run_kernel<32><<<1, NT, 0, s>>>(a);
   else
     select_kernel<0><<<1, NT, 0, s>>>(a);
   return hipGetLastError();
