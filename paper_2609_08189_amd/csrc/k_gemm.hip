@@ -6,10 +6,12 @@
 //   adapter down             hid = SiLU(u W_1^T)                      (Sec. 3.1, adapter)
 //   adapter up + scatter     h_out[t] = hbar[t] + (1 - g_t) (hid W_2^T)
 //
-// bf16 path: v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  A and B are both
+// bf16 path: MFMA with fp32 accumulation, three kernels.  phase_gemm (16x16x32) takes
+// the large products, mfma_gemm (32x32x16) the smaller tiles of the router, the wide
+// adapters and few rows with K split, skinny_gemm the decode steps.  A and B are both
 // K-contiguous ("x W^T" with nn.Linear weights).  A k-tile of 64 elements
 // (128 bytes per row) of A and B is staged through LDS, double buffered, with
-// the 16-byte chunks of each row XOR-swizzled by (row & 7) so that the 32-row
+// the 16-byte chunks of each row XOR-swizzled by (row / 2) & 7 so that the
 // fragment reads of one MFMA hit distinct banks.  A rows may be gathered through
 // an index list whose length lives on the device (tiles past it exit at once).
 // Workgroups are mapped to tiles so that each XCD (8 per MI355X, round-robin
@@ -211,10 +213,9 @@ struct EpiScatter {
 // bf16 MFMA GEMM
 //
 // One workgroup of WM x WN waves computes a BM x BN tile; each wave owns a
-// (BM/WM) x (BN/WN) block of 32 x 32 MFMA tiles with fp32 accumulators.  The big
-// products run 8 waves (two per SIMD) on a 256 x 256 (or 192 x 256) tile, so that one
-// wave's MFMAs cover the other's waits.  K advances in 64-deep tiles through two
-// LDS stages:
+// (BM/WM) x (BN/WN) block of 32 x 32 MFMA tiles with fp32 accumulators.  The larger
+// tiles run 8 waves (two per SIMD), so that one wave's MFMAs cover the other's waits.
+// K advances in 64-deep tiles through two LDS stages (more where a tile names them):
 //   * each stage is filled by wave-wide global_load_lds_dwordx4: one instruction
 //     moves 64 x 16 bytes into a contiguous 1 KiB of LDS, i.e. eight 128-byte
 //     tile rows; lane L lands in row 8b + L/8 at physical chunk L%8 and so loads
@@ -229,10 +230,9 @@ struct EpiScatter {
 //     MFMA of that last k-step, together with the first fragment reads of tile k+1.
 // A grid with gridDim.y = S > 1 splits K: workgroup y covers k-tiles [y n / S, (y + 1) n / S)
 // of the n = K / 64 and its epilogue writes partial sums to a slice of its own (router
-// pre-activations; FFN products with few rows).
-// Epilogues: the gate/up product stages its finished bf16 tile in LDS at once and
-// writes 16-byte row pieces; the others first fetch what they combine with (hbar
-// rows) for the whole wave tile, then stage fp32 results in 32-row blocks.
+// pre-activations; gate/up with few rows).
+// Epilogues first fetch what they combine with (hbar rows) for the whole wave tile,
+// then stage fp32 results in 32-row blocks.
 // ---------------------------------------------------------------------------
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -1948,8 +1948,8 @@ hipError_t launch_router_gemm(int dtype, const void* hbar, const void* w_hd, con
     const int splits = router_gemm_splits(dtype, d, T, N);
     if (T <= 1024 && N % TileRouterSmall::OUT_N == 0)
       return run_tile<TileRouterSmall>(A, B, epi, nullptr, T, N, d, s, splits);
-    // a full round or more of tiles: the FFN products' 256 x 256 tiles on the 16 x 16 x 32
-    // instruction (32768 tokens: 256 tiles, no K split)
+    // a full round or more of tiles: the FFN products' core (32768 tokens: 256 tiles of 256 x 256,
+    // no K split)
     if (splits == 1 && T >= 16384 && N % 256 == 0) return run_phase<false>(A, B, epi, nullptr, T, N, d, s);
     if (N % TileRouter::OUT_N == 0) return run_tile<TileRouter>(A, B, epi, nullptr, T, N, d, s, splits);
     return run_tile<TileRouterNarrow>(A, B, epi, nullptr, T, N, d, s, splits);
