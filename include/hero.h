@@ -249,7 +249,8 @@ typedef enum hero_kernel {
  * Measurement hook.  While attached, every launch of `kernel` is bracketed by
  * hipEventRecord(start_events[i]) and hipEventRecord(stop_events[i]) on the
  * call's stream, with i cycling over the n_slots caller-created hipEvent_t
- * handles (passed as void*).  n_slots = 0 detaches.  The registry is process
+ * handles (passed as void*).  A kernel that shares another's launch (calls of few
+ * tokens) records an empty interval.  n_slots = 0 detaches.  The registry is process
  * global and must not be changed while routed calls are being enqueued.
  */
 int hero_kernel_timer(int kernel, void *const *start_events, void *const *stop_events, int n_slots);
