@@ -5,16 +5,23 @@
 
 namespace hero {
 
-// One workgroup of NT threads per token, its row split over the waves (8 elements per lane per
-// pass, up to 8192 elements kept in registers for the normalisation), the four sums reduced across the waves
+// 256 threads per token, its row split over their four waves (8 elements per lane per pass, up to
+// 8192 elements kept in registers for the normalisation), the four sums reduced across the waves
 // through LDS.  Measured against four tokens per workgroup (one per wave): 26.8 against 28.4 us at
 // 4096 tokens of d = 4096, 7.2 against 13.6 us at 256 tokens, where a wave per row left most CUs idle.
-template <typename T, int NT>
-__device__ __forceinline__ void rowstats_row(int t, const T* __restrict__ hbar, const T* __restrict__ prev1,
+// A workgroup of 256 G threads takes the G tokens from t on (past the last of T: the last again,
+// nothing stored); the threads of a token and so the order of its sums are the same for every G.
+template <typename T, int G = 1>
+__device__ __forceinline__ void rowstats_row(int t, int T_rows, const T* __restrict__ hbar, const T* __restrict__ prev1,
                                              const T* __restrict__ prev2, const T* __restrict__ norm_w, int d, int j,
                                              float eps_norm, float* __restrict__ rowstat, T* __restrict__ u) {
-  __shared__ f32x4 part[NT / 64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int NT = 256;
+  __shared__ f32x4 parts[G][NT / 64];
+  const int grp = G == 1 ? 0 : static_cast<int>(threadIdx.x) / NT;
+  const bool own = t + grp < T_rows;
+  t = min(t + grp, T_rows - 1);
+  f32x4* part = parts[grp];
+  const int tid = G == 1 ? threadIdx.x : threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
   const size_t row = static_cast<size_t>(t) * d;
   constexpr int RC = 1024 / NT;   // 8-element chunks per thread kept in registers (rows up to 8192)
   Raw8<T> h[RC];
@@ -62,6 +69,7 @@ __device__ __forceinline__ void rowstats_row(int t, const T* __restrict__ hbar, 
 #pragma unroll
   for (int w = 1; w < NT / 64; ++w) tot += part[w];
   const float inv_rms = 1.0f / sqrtf(tot[0] / static_cast<float>(d) + eps_norm);
+  if (!own) return;
   if (tid == 0) {
     f32x4 r = {inv_rms, tot[1], tot[2], tot[3]};
     *reinterpret_cast<f32x4*>(rowstat + 4 * static_cast<size_t>(t)) = r;

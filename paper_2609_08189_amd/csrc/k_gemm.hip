@@ -316,11 +316,12 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
   constexpr int NL = A_LD + B_LD;       // stage loads per k-tile
   __shared__ __attribute__((aligned(1024))) unsigned char smem[C::NS * C::STAGE];
   if constexpr (RowsHook<Epi>::value) {
+    static_assert(C::NT == 256, "the row pass takes 256 threads a token");
     if (static_cast<int>(blockIdx.x) >= epi.tile_blocks) {
       const int t = (static_cast<int>(blockIdx.x) - epi.tile_blocks) * static_cast<int>(gridDim.y) +
                     static_cast<int>(blockIdx.y);
       if (t < epi.T)
-        rowstats_row<bf16_t, C::NT>(t, epi.hbar, epi.prev1, epi.prev2, epi.norm_w, epi.d, epi.j, epi.eps_norm,
+        rowstats_row<bf16_t>(t, epi.T, epi.hbar, epi.prev1, epi.prev2, epi.norm_w, epi.d, epi.j, epi.eps_norm,
                                     epi.rowstat, epi.u);
       return;
     }
@@ -1595,7 +1596,7 @@ __global__ __launch_bounds__(256) void f32_head(ARows<float> A, BRows<float> B, 
                                                float* __restrict__ u) {
   const int b = static_cast<int>(blockIdx.x);
   if (b >= tiles)
-    rowstats_row<float, 256>(b - tiles, A.base, prev1, prev2, norm_w, K, j, eps_norm, rowstat, u);
+    rowstats_row<float>(b - tiles, T, A.base, prev1, prev2, norm_w, K, j, eps_norm, rowstat, u);
   else
     f32_tile<false, 1, VEC>(A, B, epi, T, N, K, b % mt, b / mt);
 }

@@ -19,15 +19,16 @@ __global__ __launch_bounds__(256) void rowstats_row_kernel(const T* __restrict__
                                                            const T* __restrict__ prev2, const T* __restrict__ norm_w,
                                                            int d, int j, float eps_norm, float* __restrict__ rowstat,
                                                            T* __restrict__ u) {
-  rowstats_row<T, 256>(static_cast<int>(blockIdx.x), hbar, prev1, prev2, norm_w, d, j, eps_norm, rowstat, u);
+  rowstats_row<T>(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), hbar, prev1, prev2, norm_w, d, j, eps_norm,
+                  rowstat, u);
 }
 
 // ---------------------------------------------------------------------------
 // The head of a decode step's layer (at most 256 tokens, bf16): the router's pre-activation
 // product P = hbar [W_hd; psi_1]^T and the row pass read the same rows and nothing of each other,
 // so one launch holds both.  The product streams 4 MiB of weights for few rows: up to 64 tokens
-// here, workgroups of 16 columns x one of the kHeadSplits K-slices, then one workgroup per token
-// row (beyond, the 64 x 128 tiles of launch_router_gemm, whose fragments go through LDS).  Waves
+// here, workgroups of 16 columns x one of the kHeadSplits K-slices, then one workgroup per two token
+// rows (beyond, the 64 x 128 tiles of launch_router_gemm, whose fragments go through LDS).  Waves
 // are four blocks of 16 tokens by two halves of the K-slice, added through LDS; the fragments come
 // straight from memory, BS k-steps of 32 in one batch.  One 8B layer at 1 token: 10.4 us for the
 // tiles, the row pass beside them on a second stream, -> 4.5 us for both.
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(512) void decode_head_kernel(const bf16_t* __restri
   const int ncb = N / 16, ng = ncb * kHeadSplits;
   const int b = static_cast<int>(blockIdx.x);
   if (b >= ng) {
-    rowstats_row<bf16_t, 512>(b - ng, hbar, prev1, prev2, norm_w, d, j, eps_norm, rowstat, u);
+    rowstats_row<bf16_t, 2>(2 * (b - ng), T, hbar, prev1, prev2, norm_w, d, j, eps_norm, rowstat, u);
     return;
   }
   __shared__ f32x4 red[4][kWave];
@@ -101,7 +102,7 @@ hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* p
     return launch_decode_head_tiles(hbar, prev1, prev2, norm_w, w_hd, ps1, T, d, d_e, d_head, j, eps_norm, P, rowstat,
                                     u, s);
   const int N = d_e + d_head;
-  decode_head_kernel<<<N / 16 * kHeadSplits + T, 512, 0, s>>>(
+  decode_head_kernel<<<N / 16 * kHeadSplits + (T + 1) / 2, 512, 0, s>>>(
       static_cast<const bf16_t*>(hbar), static_cast<const bf16_t*>(prev1), static_cast<const bf16_t*>(prev2),
       static_cast<const bf16_t*>(norm_w), static_cast<const bf16_t*>(w_hd), static_cast<const bf16_t*>(ps1), T, d, d_e,
       N, j, eps_norm, P, rowstat, static_cast<bf16_t*>(u));

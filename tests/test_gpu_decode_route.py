@@ -44,3 +44,22 @@ def test_threshold_one_branch(T, beta):
 @pytest.mark.parametrize("budget", [0.0, 1.0])
 def test_budget_one_branch(budget):
     _layer(70, budget=budget)
+
+
+@pytest.mark.parametrize("T", [47, 64, 65, 256])
+def test_row_pass_is_the_prefills(T):
+    """A token's normalised row u (the first region of the workspace) has the same bits in a decode step, where the row
+    pass shares the router product's launch, as in a call of 300 tokens with a row pass of its own."""
+    import torch
+    from paper_2609_08189_amd.device import DeviceProblem
+    d = 4096
+    u = []
+    for n in (T, 300):
+        w = synth.Workload("row_pass", "bf16", d=d, d_ff=128, d_r=32, L_R=8, d_m=32, T=n, mode="budget", budget=0.3)
+        dp = DeviceProblem(synth.make_problem(w, seed=5, layer_j=3))
+        rows = torch.randn(300, d, generator=torch.Generator().manual_seed(9)).to(torch.bfloat16).cuda()
+        dp.hbar.copy_(rows[:n])
+        dp.run_layer(3)
+        torch.cuda.synchronize()
+        u.append(dp.ws[:T * d * 2].view(torch.int16).clone())
+    assert torch.equal(*u)
