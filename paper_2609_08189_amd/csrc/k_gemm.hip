@@ -18,7 +18,8 @@
 // dispatch) owns a contiguous run of a grouped tile order: the tiles it runs at
 // once share a few row panels and a few weight panels in its L2.
 //
-// f32 path: small tiles on the fp32 matrix cores with full bounds checks (narrow shapes).
+// f32 path: small tiles on the fp32 matrix cores, 64 x 64 VALU tiles for the largest products, with
+// full bounds checks.
 #include <limits.h>
 
 #include <algorithm>
@@ -1476,7 +1477,9 @@ hipError_t run_skinny(ARows<bf16_t> A, const bf16_t* b0, const bf16_t* b1, int l
 // dependent loads, not by the arithmetic: a 64 x 64 LDS tile on the VALU walked K = 688 in 43
 // dependent steps on 4 workgroups at 64 rows.  Measured against it: the 4-layer stack of
 // d = 256, d_ff = 688 at 64 tokens 1318 -> 508 us, 2 layers of d = 2048, d_ff = 5632 at 20 tokens
-// 3460 -> 407 us and at 2048 tokens 6489 -> 4540 us, so it serves every size.
+// 3460 -> 407 us and at 2048 tokens 6489 -> 4540 us.  Without LDS each tile reads its operands anew,
+// so once the 64 x 64 tiles fill the chip several times over they are the faster ones
+// (f32_valu_gemm).
 // ---------------------------------------------------------------------------
 
 // elements k .. k + 3 of a row, zero past K; VEC: K and both row pitches are multiples of four
@@ -1675,10 +1678,95 @@ hipError_t run_f32_r(ARows<float> A, BRows<float> B, Epi epi, const int* m_count
   return hipGetLastError();
 }
 
+// Large fp32 products: 64 x 64 tiles through LDS on the VALU, 4 x 4 outputs per thread, full bounds
+// checks.  The VALU's rate bounds it (64 TFLOP/s at 2990 rows of d = 2048, d_ff = 5632).
+template <bool DUAL, class Epi>
+__global__ __launch_bounds__(256) void f32_valu_gemm(ARows<float> A, BRows<float> B, Epi epi,
+                                                    const int* __restrict__ m_count, int M_fixed,
+                                                    int N, int K) {
+  __shared__ float As[16][68];
+  __shared__ float Bs[16][68];
+  __shared__ float Us[DUAL ? 16 : 1][68];
+  const int M = m_count ? *m_count : M_fixed;
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+  if (m0 >= M) return;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  float acc[4][4], acu[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = acu[i][j] = 0.f;
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    for (int e = threadIdx.x; e < 64 * 16; e += 256) {
+      const int r = e >> 4, kk = e & 15, k = k0 + kk;
+      const int m = m0 + r, n = n0 + r;
+      As[kk][r] = (m < M && k < K) ? A.row(m)[k] : 0.f;
+      if (DUAL) {
+        Bs[kk][r] = (n < N && k < K) ? B.gate_row(n)[k] : 0.f;
+        Us[kk][r] = (n < N && k < K) ? B.up_row(n)[k] : 0.f;
+      } else {
+        Bs[kk][r] = (n < N && k < K) ? B.row(n)[k] : 0.f;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+      float a[4], b[4], u[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        a[i] = As[kk][ty * 4 + i];
+        b[i] = Bs[kk][tx * 4 + i];
+        if (DUAL) u[i] = Us[kk][tx * 4 + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+          if (DUAL) acu[i][j] = fmaf(a[i], u[j], acu[i][j]);
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int m = m0 + ty * 4 + i;
+    if (m >= M) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int n = n0 + tx * 4 + j;
+      if (n >= N) continue;
+      if constexpr (DUAL) {
+        epi.store2(m, n, acc[i][j], acu[i][j]);
+      } else {
+        epi.store(m, n, acc[i][j]);
+      }
+    }
+  }
+}
+
+// Where the VALU tiles are the faster ones, by the row bound M, columns N and depth K (matrix cores
+// against VALU, us): eight or more of them per CU over 2048 rows for two products in one (2990 rows,
+// d = 2048, d_ff = 5632: 2567 / 2147; d = 1024, d_ff = 2816: 642 / 596; but 1495 rows of the former
+// 1307 / 1320), over 4096 rows for one (its down product of 5980 rows 2829 / 2710, of 11960
+// 5840 / 4953; d = 1024, 5980 rows, six per CU: 736 / 777), two per CU for the adapters' few k-steps
+// (K = 64, 2212 rows, 2048 columns: 50 / 35; 1106 rows, 1024 columns: 20 / 23).
+bool f32_valu_fits(bool dual, int M, int N, int K) {
+  const long long tiles = static_cast<long long>((M + 63) / 64) * ((N + 63) / 64);
+  if ((M + 63) / 64 > 65535) return false;   // grid limit
+  if (K <= 64) return tiles >= 2 * kCUs;
+  return tiles >= 8 * kCUs && M >= (dual ? 2048 : 4096);
+}
+
 template <bool DUAL, class Epi>
 hipError_t run_f32(ARows<float> A, BRows<float> B, Epi epi, const int* m_count, int M_max, int N,
                    int K, hipStream_t s) {
   if (M_max <= 0 || N <= 0) return hipSuccess;
+  if (f32_valu_fits(DUAL, M_max, N, K)) {
+    const dim3 grid((N + 63) / 64, (M_max + 63) / 64);
+    f32_valu_gemm<DUAL, Epi><<<grid, 256, 0, s>>>(A, B, epi, m_count, M_max, N, K);
+    return hipGetLastError();
+  }
   const bool vec = F32Job<Epi>{A, B, epi, M_max, N, K}.vec();
   if (f32_tiles_large(M_max, N)) return run_f32_r<DUAL, 2>(A, B, epi, m_count, M_max, N, K, vec, s);
   return run_f32_r<DUAL, 1>(A, B, epi, m_count, M_max, N, K, vec, s);
