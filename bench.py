@@ -570,14 +570,17 @@ def router_backward_work(w, j, c_given=False):
     small = 2 * T * (4 * dm * w.d_s + dm * dm + w.d_head * d_x + 2 * w.d_head + 6 * w.d_p + w.d_a * w.d_p
                      + w.d_h * w.d_e)
     n_prev = min(j - 1, 2)
+    # bf16: the row's own terms (its states read again) ride on the product that adds into dL/dhbar
+    own = 1 if w.dtype == "bf16" else 0
     return {
         "router_bwd_gemm": dict(flops=2 * T * d * NP, bytes=T * d * es + NP * d * es + splits * T * NP * 4),
         "router_bwd_token": dict(flops=0, bytes=T * ((3 if j > 1 else 2) * dm * dm * 4 + (1 + n_prev) * d * es
                                                      + splits * NP * 4 + (2 * NP + vec + 8) * 4
                                                      + (dm * 4 if c_given and j > 1 else 0))),
         "router_bwd_products": dict(flops=4 * T * NP * d + small, bytes=(2 * NP + vec) * T * 4 + T * d * (es + 4)
-                                    + 2 * T * d * 4),
-        "router_bwd_rows": dict(flops=0, bytes=T * d * ((1 + n_prev) * es + 2 * (1 + n_prev) * 4)),
+                                    + 2 * T * d * 4 + own * T * (1 + n_prev) * d * es),
+        "router_bwd_rows": dict(flops=0, bytes=T * d * ((1 + n_prev) * es + 2 * (1 + n_prev - own) * 4)
+                                if n_prev or not own else 0),
     }
 
 
@@ -645,8 +648,10 @@ def bench_router_backward(args, w):
     bounds = [t_start] + marks + [t_stop]
     step_ms = sorted(ev.elapsed_ms(a, b) for a, b in zip(bounds[:-1], bounds[1:]))
     dom_ms = sum(ev.elapsed_ms(a, b) for a, b in zip(ks, ke)) / K
-    if dom == "router_bwd_products":      # fp32 products on the vector ALUs
-        achieved, peak, unit, bound = works[dom]["flops"] / (dom_ms * 1e-3) * 1e-12, PEAK_F32_TFLOPS, "TFLOP/s", "alu"
+    if dom == "router_bwd_products":
+        achieved, peak, unit, bound = ((works[dom]["flops"] / (dom_ms * 1e-3) * 1e-12,)
+                                       + ((PEAK_BF16_TFLOPS, "TFLOP/s", "mfma") if w.dtype == "bf16"
+                                          else (PEAK_F32_TFLOPS, "TFLOP/s", "alu")))
         wpl = f"4 T (d_e + d_head) d FLOP (dW_hd, dpsi_1 and dP [W_hd; psi_1]) + the small weights' products"
     elif works[dom]["flops"]:
         achieved, peak, unit, bound = (works[dom]["flops"] / (dom_ms * 1e-3) * 1e-12,

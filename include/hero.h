@@ -240,8 +240,10 @@ typedef enum hero_kernel {
   /* backward of the router at one routed layer (hero_router_backward) */
   HERO_K_ROUTER_BWD_GEMM = 22,     /* P = hbar [W_hd; psi_1]^T recomputed                         */
   HERO_K_ROUTER_BWD_TOKEN = 23,    /* the router's forward recomputed and reversed, per token     */
-  HERO_K_ROUTER_BWD_PRODUCTS = 24, /* weight gradients (tokens as K) and dP [W_hd; psi_1]         */
-  HERO_K_ROUTER_BWD_ROWS = 25,     /* RMSNorm and transition terms of dL/dhbar; dL/deta           */
+  HERO_K_ROUTER_BWD_PRODUCTS = 24, /* weight gradients (tokens as K) and dP [W_hd; psi_1]; bf16
+                                      models: with the row's own terms of dL/dhbar               */
+  HERO_K_ROUTER_BWD_ROWS = 25,     /* RMSNorm and transition terms of dL/dhbar (bf16 models: of
+                                      the two earlier states' gradients only); dL/deta           */
   HERO_K_COUNT = 26
 } hero_kernel;
 
@@ -250,7 +252,9 @@ typedef enum hero_kernel {
  * hipEventRecord(start_events[i]) and hipEventRecord(stop_events[i]) on the
  * call's stream, with i cycling over the n_slots caller-created hipEvent_t
  * handles (passed as void*).  A kernel that shares another's launch (calls of few
- * tokens) records an empty interval.  n_slots = 0 detaches.  The registry is process
+ * tokens) records an empty interval.
+ * While kernel 24 or 25 is attached the router backward's weight gradients, which otherwise run
+ * on beside kernel 25, end inside 24's interval.  n_slots = 0 detaches.  The registry is process
  * global and must not be changed while routed calls are being enqueued.
  */
 int hero_kernel_timer(int kernel, void *const *start_events, void *const *stop_events, int n_slots);

@@ -1617,6 +1617,18 @@ int hero_router_backward(const hero_dims* dims, int j, int T, const void* hbar, 
     });
   if (e != hipSuccess) return HERO_E_LAUNCH;
   const Side* sd = D.dtype == HERO_BF16 ? side_of_current_device() : nullptr;
+  // the weight gradients run on beside the row pass, except while a timer is attached to either
+  // group: then each interval holds its own work and nothing else
+  const bool measured = g_timer[HERO_K_ROUTER_BWD_PRODUCTS].n > 0 || g_timer[HERO_K_ROUTER_BWD_ROWS].n > 0;
+  bool joined = sd == nullptr;
+  const auto join_side = [&](hipError_t x) {
+    // joined even after a failed launch, so that the side stream holds nothing of this call
+    if (joined) return x;
+    joined = true;
+    const hipError_t y = hipEventRecord(sd->join, sd->s);
+    const hipError_t z = y == hipSuccess ? hipStreamWaitEvent(s, sd->join, 0) : y;
+    return x == hipSuccess ? z : x;
+  };
   e = timed(HERO_K_ROUTER_BWD_PRODUCTS, s, [&] {
     // the weight gradients: products with the tokens as K (every operand token-contiguous)
     float* tn_part = reinterpret_cast<float*>(ws + L.tn_part);
@@ -1665,14 +1677,9 @@ int hero_router_backward(const hero_dims* dims, int j, int T, const void* hbar, 
       if (x == hipSuccess) x = hero::launch_gemm_acc_f32(a.dP, NP, T, wT, NP, D.d, NP, dhbar, D.d, s);
       if (x == hipSuccess) x = hero::launch_small_products(sp, nsp, T, T, sp_part, L.sp_floats, s);
     }
-    return x;
+    return measured ? join_side(x) : x;
   });
   if (e == hipSuccess) e = timed(HERO_K_ROUTER_BWD_ROWS, s, [&] { return hero::launch_router_bwd_rows(a, s); });
-  if (sd) {
-    // joined even after a failed launch, so that the side stream holds nothing of this call
-    const hipError_t y = hipEventRecord(sd->join, sd->s);
-    const hipError_t z = y == hipSuccess ? hipStreamWaitEvent(s, sd->join, 0) : y;
-    if (e == hipSuccess) e = z;
-  }
+  e = join_side(e);
   return e == hipSuccess ? HERO_OK : HERO_E_LAUNCH;
 }

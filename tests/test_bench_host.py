@@ -160,3 +160,14 @@ def test_router_backward_work_counts():
     assert 4 * 4096 * 512 * 4096 < wk["router_bwd_products"]["flops"] < 1.1 * 4 * 4096 * 512 * 4096
     assert wk["router_bwd_token"]["bytes"] > 4096 * 3 * 128 * 128 * 4
     assert bench.router_backward_work(w, 1)["router_bwd_token"]["bytes"] < wk["router_bwd_token"]["bytes"]
+
+
+def test_router_backward_rows_touch_dhbar_once():
+    """bf16: the row's own gradient is added by the product's epilogue, so the row pass reads and writes the earlier
+    states' gradients only (none at j = 1); fp32: all of them."""
+    from paper_2609_08189_amd import synth
+    w = synth.WORKLOADS["llama31_8b_layer"]
+    row = w.T * w.d
+    assert bench.router_backward_work(w, 17)["router_bwd_rows"]["bytes"] == row * (3 * 2 + 2 * 2 * 4)
+    assert bench.router_backward_work(w, 1)["router_bwd_rows"]["bytes"] == 0
+    assert bench.router_backward_work(w.replace(dtype="f32"), 1)["router_bwd_rows"]["bytes"] == row * (4 + 2 * 4)

@@ -176,3 +176,50 @@ def test_router_backward_first_layer_without_state():
         np.testing.assert_array_equal(a["grads"][k], b["grads"][k])
     del dp
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("timed", [False, True])
+def test_timed_products_hold_the_weight_gradients(timed, tmp_path):
+    """While a timer is attached to the products the weight gradients, which otherwise run beside the row pass, end
+    before it, so that each interval holds its own work: read from the order of the captured call's kernels."""
+    import re
+    import torch
+    from bench import HipEvents
+    from paper_2609_08189_amd import hero as H
+    from paper_2609_08189_amd.device import DeviceProblem, DeviceRouterBackward
+    w, j = BF16, 3
+    prob = synth.make_problem(w, seed=4, layer_j=j)
+    rng = np.random.default_rng(4)
+    f = lambda *s: rng.standard_normal(s).astype(np.float32)   # noqa: E731
+    T, dm = w.T, w.d_m
+    dp = DeviceProblem(prob, stats=False)
+    rb = DeviceRouterBackward(dp, j, f(T), f(T, dm, dm), f(T, dm), f(T), f(T))
+    rb.run()
+    torch.cuda.synchronize()
+    ev = HipEvents()
+    a, b = ev.create(1), ev.create(1)
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    g.enable_debug_mode()
+    if timed:
+        H.hero_kernel_timer(H.HERO_K["router_bwd_products"], a, b)
+    try:
+        with torch.cuda.graph(g):
+            rb.run()
+    finally:
+        H.hero_kernel_timer(H.HERO_K["router_bwd_products"], [], [])
+    dot = tmp_path / "call.dot"
+    g.debug_dump(str(dot))
+    ev.destroy(a + b)
+    text = dot.read_text()
+    edges = re.findall(r'"(\w+)"\s*->\s*"(\w+)"', text)
+    names = dict(re.findall(r'"(\w+)"\s*\[[^\]]*?label="([^"]*)"', text, re.S))
+    find = lambda k: [n for n, label in names.items() if k in label]   # noqa: E731
+    rows, wgrad = find("router_bwd_rows"), find("acc_slices")
+    assert len(rows) == 1 and len(wgrad) == 1, names
+    before, todo = set(), list(rows)
+    while todo:
+        n = todo.pop()
+        new = [x for x, y in edges if y == n and x not in before]
+        before.update(new)
+        todo += new
+    assert (wgrad[0] in before) == timed
