@@ -153,6 +153,8 @@ def cpu_baseline(prob, gpu_stats, j, target_s=12.0, max_tokens=None):
 # committed rocprofv3 FETCH_SIZE / WRITE_SIZE summaries, per workload
 # a call of at most this many tokens is a decode step: timed as HIP-graph replays by default
 DECODE_TOKENS = 256
+# a call of at most this many tokens runs the three router kernels as one
+ROUTER_TOKENS = {"bf16": 768, "f32": 2048}
 COUNTERS_MD = {
     "llama31_8b_layer": os.path.join(ROOT, "profiles", "routed_layer_llama31_8b_hbm_counters.md"),
     "llama31_8b_stack": os.path.join(ROOT, "profiles", "routed_stack_llama31_8b_hbm_counters.md"),
@@ -361,10 +363,11 @@ def bench_decoder(args, w):
         H.hero_kernel_timer(H.HERO_K[name], [], [])
         ms = sum(ev.elapsed_ms(x, y) for x, y in zip(a, b)) / K         # per step
         n = launches[name]
-        wk = works.get(name)
-        per[name] = {"ms_per_step": round(ms, 3), "launches": n, "us": round(1000 * ms / n, 2),
-                     "tflops": round(wk["flops"] / (ms * 1e-3) * 1e-12, 1) if wk and wk["flops"] else None,
-                     "gbs": round(wk["bytes"] / (ms * 1e-3) * 1e-9, 1) if wk else None}
+        # a launch that several kernels share says nothing about one of them
+        wk = works.get(name) if not any(name in g for g in shared_launches(w)) else None
+        per[name] = {"ms_per_step": round(ms, 3), "launches": n, "us": round(1000 * ms / n, 2)}
+        row = kernel_row(1000 * ms, wk["flops"] if wk else 0, wk["bytes"] if wk else 0)
+        per[name].update(tflops=row["tflops"], gbs=row["gbs"])
         ev.destroy(a + b)
     dom = max((k for k in per if k in works and works[k]["flops"]), key=lambda k: per[k]["ms_per_step"])
     # timed region, with the dominant kernel's launches bracketed on the call's stream (graph mode:
@@ -505,8 +508,7 @@ def bench_backward(args, w):
         H.hero_kernel_timer(H.HERO_K[name], [], [])
         us = 1000.0 * sum(ev.elapsed_ms(x, y) for x, y in zip(a, b)) / K
         wk = works[name]
-        per[name] = {"us": round(us, 2), "tflops": round(wk["flops"] / us * 1e-6, 1) if wk["flops"] else None,
-                     "gbs": round(wk["bytes"] / us * 1e-3, 1)}
+        per[name] = kernel_row(us, wk["flops"], wk["bytes"])
         ev.destroy(a + b)
     dom = max((k for k in per if works[k]["flops"]), key=lambda k: per[k]["us"])
     run = graphed(db.run) if args.graph else db.run
@@ -627,8 +629,7 @@ def bench_router_backward(args, w):
         H.hero_kernel_timer(H.HERO_K[name], [], [])
         us = 1000.0 * sum(ev.elapsed_ms(x, y) for x, y in zip(a, b)) / K
         wk = works[name]
-        per[name] = {"us": round(us, 2), "tflops": round(wk["flops"] / us * 1e-6, 1) if wk["flops"] else None,
-                     "gbs": round(wk["bytes"] / us * 1e-3, 1)}
+        per[name] = kernel_row(us, wk["flops"], wk["bytes"])
         ev.destroy(a + b)
     dom = max(per, key=lambda k: per[k]["us"])
     ks, ke = ev.create(K), ev.create(K)
@@ -734,6 +735,40 @@ ROUTER_GROUP = ("rowstats", "router_gemm", "router_pre", "router_mem", "router_p
 BAND = 1e-3          # decision band on the gate around the layer's threshold
 
 
+def shared_launches(w):
+    """Kernels that share launches in calls of few tokens, where the timer of a kernel inside another's
+    launch brackets nothing: up to these sizes a group is reported as one row."""
+    groups = []
+    if w.dtype != "bf16" or w.T <= DECODE_TOKENS:
+        groups.append(("rowstats", "router_gemm"))
+    if w.T <= ROUTER_TOKENS[w.dtype]:
+        groups.append(("router_pre", "router_mem", "router_post"))
+    if w.T <= DECODE_TOKENS:
+        groups += [("select", "ffn_gate_up", "adapter_down"), ("ffn_down", "adapter_up")]
+    return groups
+
+
+def kernel_row(us, flops, nbytes):
+    """One row of a kernel table: its time and, where it did counted work in a time, its rates."""
+    return {"us": round(us, 2), "tflops": round(flops / us * 1e-6, 1) if flops and us > 0 else None,
+            "gbs": round(nbytes / us * 1e-3, 1) if nbytes and us > 0 else None}
+
+
+def kernel_table(w, us, active, works):
+    """Mean time and rates per layer of every kernel, or group of kernels with a common launch, over the
+    layers it worked in: us[k] per step, active[k] the layers (indices into works)."""
+    groups = [tuple(k for k in g if k in us) for g in shared_launches(w)]
+    per = {}
+    for name in us:
+        g = next((g for g in groups if name in g), (name,))
+        layers = sorted(set().union(*(active[k] for k in g)))
+        if name == g[0] and layers:
+            n = len(layers)
+            fl, by = (sum(works[i][k][what] for k in g for i in active[k]) / n for what in ("flops", "bytes"))
+            per["+".join(g)] = kernel_row(sum(us[k] for k in g if active[k]) / n, fl, by)
+    return per
+
+
 def measure_forward(w, dp, K, warmup, memory="matrix", graph=False, kernels=True):
     """Time K steps of the workload's call (a hero_routed_layer call at the workload's j, or one
     hero_routed_stack call) with every input resident in HBM.
@@ -794,7 +829,7 @@ def measure_forward(w, dp, K, warmup, memory="matrix", graph=False, kernels=True
         if kernels or graph:
             names = [k for k in H.KERNELS[:H.HERO_K["adapter_up"] + 1]
                      if not (k == "router_mem" and w.ablation & 12)]
-            handles = {}
+            handles, us, active = {}, {}, {}
             for name in names:
                 a, b = ev.create(K * L), ev.create(K * L)
                 handles[name] = (a, b)
@@ -805,18 +840,14 @@ def measure_forward(w, dp, K, warmup, memory="matrix", graph=False, kernels=True
             for name in names:
                 H.hero_kernel_timer(H.HERO_K[name], [], [])
                 a, b = handles[name]
-                active = [i for i in range(L) if not ((name.startswith("ffn") and nfs[i] == 0) or
-                                                       (name.startswith("adapter") and nas[i] == 0))]
-                if active:
-                    n_launch = K * len(active)
-                    us = 1000.0 * sum(ev.elapsed_ms(x, y) for x, y in zip(a[:n_launch], b[:n_launch])) / n_launch
-                    fl = sum(works[i][name]["flops"] for i in active) / len(active)
-                    by = sum(works[i][name]["bytes"] for i in active) / len(active)
-                    per[name] = {"us": round(us, 2), "tflops": round(fl / us * 1e-6, 1) if fl else None,
-                                 "gbs": round(by / us * 1e-3, 1)}
+                active[name] = [i for i in range(L) if not ((name.startswith("ffn") and nfs[i] == 0) or
+                                                             (name.startswith("adapter") and nas[i] == 0))]
+                n_launch = K * len(active[name])
+                us[name] = 1000.0 * sum(ev.elapsed_ms(x, y) for x, y in zip(a[:n_launch], b[:n_launch])) / K
                 ev.destroy(a + b)
+            per = kernel_table(w, us, active, works)
         if graph:
-            dom_ms_step = per[dom]["us"] * sum(1 for x in nfs if x > 0) / 1000.0
+            dom_ms_step = us[dom] / 1000.0
     finally:
         dp.stats = stats_saved
     return dict(ms_step=ms_step, step_ms=step_ms, dom_ms_step=dom_ms_step, layer_stats=layer_stats,
@@ -855,12 +886,14 @@ def dominant_roofline(w, m, traffic=None):
 
 def router_group(m):
     """The router, compaction and memory kernels as one group: algorithmic bytes of a mean layer
-    over the group's summed mean launch times, against the HBM peak."""
+    over the group's summed mean launch times, against the HBM peak (in a decode step without the
+    compaction, which is part of the gate/up launch)."""
     per, works = m["per"], m["works"]
-    if not all(k in per for k in ROUTER_GROUP if k != "router_mem") or not per:
+    rows = [r for r in per if all(k in ROUTER_GROUP for k in r.split("+"))]
+    names = [k for r in rows for k in r.split("+")]
+    if not all(k in names for k in ROUTER_GROUP if k not in ("router_mem", "select")):
         return None
-    names = [k for k in ROUTER_GROUP if k in per]
-    us = sum(per[k]["us"] for k in names)
+    us = sum(per[r]["us"] for r in rows)
     by = sum(wk[k]["bytes"] for wk in works for k in names) / len(works)
     return {"kernels": names, "us": round(us, 2), "bytes": int(by), "gbs": round(by / us * 1e-3, 1),
             "frac_hbm": round(by / us * 1e-3 / PEAK_HBM_GBS, 4)}

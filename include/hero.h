@@ -252,7 +252,10 @@ typedef enum hero_kernel {
  * hipEventRecord(start_events[i]) and hipEventRecord(stop_events[i]) on the
  * call's stream, with i cycling over the n_slots caller-created hipEvent_t
  * handles (passed as void*).  A kernel that shares another's launch (calls of few
- * tokens) records an empty interval.
+ * tokens) records an empty interval: the row pass that of the router's product; the three
+ * router kernels after it record theirs as HERO_K_ROUTER_MEM; in a decode step the decision and the
+ * adapter's down-projection ride in HERO_K_FFN_GATE_UP, and HERO_K_ADAPTER_UP holds the FFN's
+ * reduction and scatter as well (fp32: HERO_K_FFN_DOWN holds the adapter's up-projection).
  * While kernel 24 or 25 is attached the router backward's weight gradients, which otherwise run
  * on beside kernel 25, end inside 24's interval.  n_slots = 0 detaches.  The registry is process
  * global and must not be changed while routed calls are being enqueued.

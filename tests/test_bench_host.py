@@ -162,6 +162,39 @@ def test_router_backward_work_counts():
     assert bench.router_backward_work(w, 1)["router_bwd_token"]["bytes"] < wk["router_bwd_token"]["bytes"]
 
 
+def test_shared_launches_are_one_row():
+    """In calls of few tokens kernels share launches and the timers of those inside another's launch bracket nothing:
+    such a group is one row with the group's work over its time, a zero interval gives no rate, and the limits are the
+    library's."""
+    import re
+    from paper_2609_08189_amd import synth
+    names = ("rowstats", "router_gemm", "router_pre", "router_mem", "router_post", "select", "ffn_gate_up", "ffn_down",
+             "adapter_down", "adapter_up")
+    empty = ("rowstats", "router_pre", "router_post", "select", "adapter_down")
+    us = {k: 0.0 if k in empty else 80.0 for k in names}
+    w = synth.WORKLOADS["llama2_7b_decode"]
+    works = [bench.kernel_work(w, 200, 56, w.T, j) for j in (1, 2)]
+    active = {k: [0, 1] for k in names}
+    per = bench.kernel_table(w, us, active, works)
+    assert set(per) == {"rowstats+router_gemm", "router_pre+router_mem+router_post", "select+ffn_gate_up+adapter_down",
+                        "ffn_down+adapter_up"}
+    row = per["ffn_down+adapter_up"]
+    assert row["us"] == 80.0
+    assert row["tflops"] == round((works[0]["ffn_down"]["flops"] + works[0]["adapter_up"]["flops"]) / 80.0 * 1e-6, 1)
+    g = bench.router_group(dict(per=per, works=works))
+    assert g["us"] == 80.0 and "select" not in g["kernels"] and "rowstats" in g["kernels"]
+    # layers without adapter tokens, a launch of its own per kernel, and an interval of zero
+    big = w.replace(T=4096)
+    per = bench.kernel_table(big, us, dict(active, adapter_up=[1], adapter_down=[]), works)
+    assert set(per) == set(names) - {"adapter_down"}
+    assert per["adapter_up"]["us"] == 80.0 and per["ffn_down"]["us"] == 40.0
+    assert per["rowstats"]["gbs"] is None
+    src = {n: open(os.path.join(ROOT, "paper_2609_08189_amd", "csrc", n)).read() for n in ("hero_kernels.h", "k_router.hip")}
+    of = lambda f, k: int(re.search(k + r" = (\d+)", src[f]).group(1))   # noqa: E731
+    assert bench.DECODE_TOKENS == of("hero_kernels.h", "kDecodeTokens")
+    assert bench.ROUTER_TOKENS == {"bf16": of("k_router.hip", "kTokenRowsBf16"), "f32": of("k_router.hip", "kTokenRowsF32")}
+
+
 def test_router_backward_rows_touch_dhbar_once():
     """bf16: the row's own gradient is added by the product's epilogue, so the row pass reads and writes the earlier
     states' gradients only (none at j = 1); fp32: all of them."""
