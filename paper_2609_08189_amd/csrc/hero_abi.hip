@@ -41,11 +41,6 @@ struct Layout {
       total;
 };
 
-// At most this many tokens (a decode batch) the adapter branch runs beside the FFN branch with a
-// partial-sum region of its own: inside the FFN's launches (decode_route_fits), or on a second
-// stream (wide adapters).
-constexpr int kOverlapTokens = 256;
-
 Layout layout_of(const hero_dims& d, int T, bool stack) {
   const size_t es = esize(d.dtype), t = static_cast<size_t>(T);
   Layout L{};
@@ -66,11 +61,12 @@ Layout layout_of(const hero_dims& d, int T, bool stack) {
   L.counts = take(16);
   L.lambda = take(16);
   L.act = take(t * d.d_ff * es);
-  // the FFN's split-K partials and the adapter's hidden rows: one region used in turn, or two
-  // when the branches overlap
+  // the FFN's split-K partials and the adapter's hidden rows: one region used in turn, or two in a
+  // decode step, where the adapter branch runs beside the FFN branch: inside its launches
+  // (decode_route_fits), or on a second stream (wide adapters)
   const size_t pa = hero::adapter_part_floats(d.dtype, d.d, d.d_r, T) * 4;
   const size_t pf = hero::ffn_part_floats(d.dtype, d.d, d.d_ff, T) * 4;
-  if (T <= kOverlapTokens) {
+  if (T <= hero::kDecodeTokens) {
     L.part = take(pf);
     L.part_ad = take(pa);
   } else {
@@ -466,7 +462,7 @@ int run_layer(const LayerCall& c) {
   if (e != hipSuccess) return HERO_E_LAUNCH;
   // the two branches write disjoint rows of h_out and read only hbar, u, the gates and the lists:
   // for a decode batch the adapter's latency-bound launches run beside the FFN's weight stream
-  const bool ovl = sd && D.dtype == HERO_BF16 && T <= kOverlapTokens && n_ffn_max > 0 && n_ad_max > 0;
+  const bool ovl = sd && D.dtype == HERO_BF16 && T <= kDecodeTokens && n_ffn_max > 0 && n_ad_max > 0;
   const hipStream_t s_ad = ovl ? sd->s : st;
   if (ovl && fork() != hipSuccess) return HERO_E_LAUNCH;
   if (n_ffn_max > 0) {

@@ -20,9 +20,13 @@ hipError_t launch_rowstats(int dtype, const void* hbar, const void* prev1, const
 // written as router_gemm_splits(dtype, d, T, d_e + d_head) partial sums over K slices, slice z at
 // P + z T (d_e + d_head).
 int router_gemm_splits(int dtype, int d, int T, int N);
-// launch_router_gemm and launch_rowstats in one launch, for bf16 calls of at most 256 tokens
-// (router_gemm_splits slices of P)
+// The most tokens of a decode step.  One limit for all that depends on it: the launches the two
+// branches share (decode_route_fits, f32_route_fits), whose adapter partials must outlive the down
+// product's, the workspace region of their own that the partials have up to it, and the products
+// whose rows fit one workgroup.
 constexpr int kDecodeTokens = 256;
+// launch_router_gemm and launch_rowstats in one launch, for bf16 calls of at most kDecodeTokens
+// tokens (router_gemm_splits slices of P)
 bool decode_head_fits(int dtype, int T, int d, int d_e, int N);
 hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                               const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,

@@ -998,8 +998,6 @@ hipError_t run_tile(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_coun
 // about 7 us each: one 8B layer at 1 token 107 -> 85 us, 48 tokens 140 -> 102, the 7B decode stack of
 // 256 tokens (a graph) 4.42 -> 3.74 ms with decode_head.
 // ---------------------------------------------------------------------------
-constexpr int kRouteTokens = 256;
-
 struct RouteArgs {
   SelectArgs sel;
   int na;                  // adapter workgroups (a multiple of 8): row tiles of 32 tokens x K-slices
@@ -1020,13 +1018,13 @@ struct RouteFinish {
   size_t stride;
 };
 
-// The branch decision of select_kernel for T <= 256 tokens by one wave: lane l holds tokens
+// The branch decision of select_kernel for T <= kDecodeTokens by one wave: lane l holds tokens
 // l, l + 64, ...  The n_skip-th smallest key is found bit by bit over ballots, its ties by token
-// index.  list receives the FFN tokens in ascending order (256 ints); write: the outputs of
+// index.  list receives the FFN tokens in ascending order (kDecodeTokens ints); write: the outputs of
 // SelectArgs too; adapters (may be null): the other tokens, also ascending.  Returns the FFN count.
 __device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* list, bool write,
                                            int* adapters = nullptr) {
-  constexpr int Q = kRouteTokens / kWave;
+  constexpr int Q = kDecodeTokens / kWave;
   float l[Q];
   uint32_t key[Q];
   unsigned long long valid[Q], skip[Q];
@@ -1263,7 +1261,7 @@ __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t
       if (route.sel.mode != 0) return n_max;
       int n = 0;
 #pragma unroll
-      for (int i = 0; i < kRouteTokens / kWave; ++i) {
+      for (int i = 0; i < kDecodeTokens / kWave; ++i) {
         const int t = static_cast<int>(threadIdx.x & 63) + kWave * i;
         n += __popcll(__ballot(t < route.sel.T && route.sel.logit[min(t, route.sel.T - 1)] >= route.sel.thr));
       }
@@ -1344,6 +1342,7 @@ __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t
     // the wave's own list of FFN tokens, in the 1 KiB of the first stage that only its loads fill
     const int* rows = A.idx;
     if constexpr (ROUTE) {
+      static_assert(kDecodeTokens * sizeof(int) <= 1024, "the list fits the first load's KiB");
       int* list = reinterpret_cast<int*>(sa + pw * 1024);
       select_wave(route.sel, lane, list, id == 0 && pw == 0);
       rows = list;
@@ -1618,14 +1617,14 @@ struct F32Job {
   int tiles() const { return mt() * ((N + 15) / 16); }
 };
 
-// ROUTE: the row lists are decided here (at most kRouteTokens tokens); else sel.counts holds the
+// ROUTE: the row lists are decided here (at most kDecodeTokens tokens); else sel.counts holds the
 // row counts: [0] of the first job, [1] of the second
 template <bool DUAL, bool V0, bool V1, bool ROUTE, class E0, class E1>
 __global__ __launch_bounds__(256) void f32_pair(F32Job<E0> j0, F32Job<E1> j1, int tiles0, SelectArgs sel) {
   const int b = static_cast<int>(blockIdx.x);
   int nf, na;
   if constexpr (ROUTE) {
-    __shared__ int lists[2][kRouteTokens];
+    __shared__ int lists[2][kDecodeTokens];
     __shared__ int s_nf;
     if (threadIdx.x < kWave) {
       const int n = select_wave(sel, static_cast<int>(threadIdx.x), lists[0], b == 0, lists[1]);
@@ -2062,7 +2061,8 @@ constexpr int kMaxSplitGU = 8, kMaxSplitDown = 16;
 // At most 256 rows (a decode batch): the skinny products.  Gate/up: one workgroup per CU, each
 // with 2-4 blocks of 16 columns of W_g and W_u and the whole of K.  Down: blocks of 8 x 16 output
 // columns by kSkinnyDownS K-slices, whose fp32 partial sums a pass adds in a fixed order.
-constexpr int kSkinnyRows = 256, kSkinnyDownNB = 8, kSkinnyDownS = 8;
+constexpr int kSkinnyRows = kDecodeTokens, kSkinnyDownNB = 8, kSkinnyDownS = 8;
+static_assert(kSkinnyRows <= 4 * 64, "the row blocks of skinny_gateup_nb");
 bool skinny_gateup_fits(int n_max, int d, int d_ff) {
   const int nb = d_ff / 16;
   return n_max <= kSkinnyRows && d % BK == 0 && d_ff % 16 == 0 && nb <= 4 * kCUs;
@@ -2621,14 +2621,14 @@ hipError_t launch_adapter_up(int dtype, const float* part, const int* idx_ad, co
 }
 
 bool decode_route_fits(int dtype, int T, int n_ffn_max, int d, int d_ff, int d_r) {
-  return dtype == 1 && T <= kRouteTokens && n_ffn_max > 0 && !adapter_wide(d_r) && d % 256 == 0 &&
+  return dtype == 1 && T <= kDecodeTokens && n_ffn_max > 0 && !adapter_wide(d_r) && d % 256 == 0 &&
          skinny_gateup_fits(n_ffn_max, d, d_ff) && skinny_down_fits(n_ffn_max, d, d_ff);
 }
 
 // fp32, few tiles in each product: the decision rides with the first pair as long as one wave holds
 // the tokens
 bool f32_route_fits(int dtype, int T, int n_ffn_max, int n_ad_max, int d, int d_ff, int d_r) {
-  return dtype != 1 && T <= kRouteTokens && !f32_tiles_large(n_ffn_max, d_ff) && !f32_tiles_large(n_ffn_max, d) &&
+  return dtype != 1 && T <= kDecodeTokens && !f32_tiles_large(n_ffn_max, d_ff) && !f32_tiles_large(n_ffn_max, d) &&
          !f32_tiles_large(n_ad_max, d_r) && !f32_tiles_large(n_ad_max, d);
 }
 
