@@ -323,7 +323,7 @@ int run_layer(const LayerCall& c) {
   const void* prev1 = c.j >= 2 ? c.prev1 : nullptr;
   const void* prev2 = c.j >= 3 ? c.prev2 : nullptr;
   const bool f32_head = f32_head_fits(D.dtype, T, D.d_e + D.d_head);
-  if (f32_head || decode_head_fits(D.dtype, T, D.d, D.d_e, D.d_e + D.d_head)) {
+  if (f32_head || decode_head_fits(D.dtype, T)) {
     // few tokens: the row pass and the router's product in one launch, timed as the product
     e = timed(HERO_K_ROWSTATS, st, nothing);
     if (e == hipSuccess)

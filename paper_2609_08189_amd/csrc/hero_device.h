@@ -81,7 +81,6 @@ template <typename T> struct Raw8;
 template <> struct Raw8<bf16_t> {
   u32x4 v;
   __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const u32x4*>(p); }
-  __device__ __forceinline__ void zero() { v = u32x4{0u, 0u, 0u, 0u}; }
   __device__ __forceinline__ float operator[](int i) const {
     const uint32_t w = v[i >> 1];
     return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
@@ -93,7 +92,6 @@ template <> struct Raw8<float> {
     a = *reinterpret_cast<const f32x4*>(p);
     b = *reinterpret_cast<const f32x4*>(p + 4);
   }
-  __device__ __forceinline__ void zero() { a = b = f32x4{0.f, 0.f, 0.f, 0.f}; }
   __device__ __forceinline__ float operator[](int i) const { return i < 4 ? a[i] : b[i - 4]; }
 };
 

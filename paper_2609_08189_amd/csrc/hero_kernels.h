@@ -27,12 +27,11 @@ int router_gemm_splits(int dtype, int d, int T, int N);
 constexpr int kDecodeTokens = 256;
 // launch_router_gemm and launch_rowstats in one launch, for bf16 calls of at most kDecodeTokens
 // tokens (router_gemm_splits slices of P)
-bool decode_head_fits(int dtype, int T, int d, int d_e, int N);
+bool decode_head_fits(int dtype, int T);
 hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                               const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
                               float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);
 // ... on the tiles of launch_router_gemm, for its more than 64 tokens
-bool decode_head_tiles_fit(int N);
 hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                                     const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
                                     float eps_norm, float* P, float* rowstat, void* u, hipStream_t s);

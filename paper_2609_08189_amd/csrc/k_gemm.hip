@@ -1986,12 +1986,11 @@ int router_gemm_splits(int dtype, int d, int T, int N) {
   return static_cast<int>(std::max(1LL, std::min(4LL, kCUs / std::max(1LL, tiles))));
 }
 
-bool decode_head_tiles_fit(int N) { return N % TileRouterSmall::OUT_N == 0; }
-
 hipError_t launch_decode_head_tiles(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                                     const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
                                     float eps_norm, float* P, float* rowstat, void* u, hipStream_t s) {
   using C = TileRouterSmall;
+  static_assert(C::OUT_N == 128, "d_e + d_head is a multiple of 128");
   const int N = d_e + d_head, splits = router_gemm_splits(1, d, T, N);
   const int mt = (T + C::BM - 1) / C::BM, nt = N / C::OUT_N, tiles = (mt * nt + 7) / 8 * 8;
   EpiStoreF32Rows epi{{P, N, static_cast<size_t>(T) * N}, tiles, T, d, j, static_cast<const bf16_t*>(hbar),

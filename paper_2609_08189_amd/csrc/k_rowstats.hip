@@ -89,19 +89,19 @@ __global__ __launch_bounds__(512) void decode_head_kernel(const bf16_t* __restri
 }
 }  // namespace
 
-bool decode_head_fits(int dtype, int T, int d, int d_e, int N) {
-  return dtype == 1 && T <= kDecodeTokens && d % (64 * kHeadSplits) == 0 && d_e % 16 == 0 && N % 16 == 0 &&
-         router_gemm_splits(dtype, d, T, N) == kHeadSplits && (T <= kHeadTokens || decode_head_tiles_fit(N));
-}
+bool decode_head_fits(int dtype, int T) { return dtype == 1 && T <= kDecodeTokens; }
 
 hipError_t launch_decode_head(const void* hbar, const void* prev1, const void* prev2, const void* norm_w,
                               const void* w_hd, const void* ps1, int T, int d, int d_e, int d_head, int j,
                               float eps_norm, float* P, float* rowstat, void* u, hipStream_t s) {
   if (T <= 0) return hipSuccess;
+  const int N = d_e + d_head;
+  // what every bf16 model has (the argument checks of the calls)
+  if (d % (64 * kHeadSplits) || d_e % 16 || N % 128 || router_gemm_splits(1, d, T, N) != kHeadSplits)
+    return hipErrorInvalidValue;
   if (T > kHeadTokens)
     return launch_decode_head_tiles(hbar, prev1, prev2, norm_w, w_hd, ps1, T, d, d_e, d_head, j, eps_norm, P, rowstat,
                                     u, s);
-  const int N = d_e + d_head;
   decode_head_kernel<<<N / 16 * kHeadSplits + (T + 1) / 2, 512, 0, s>>>(
       static_cast<const bf16_t*>(hbar), static_cast<const bf16_t*>(prev1), static_cast<const bf16_t*>(prev2),
       static_cast<const bf16_t*>(norm_w), static_cast<const bf16_t*>(w_hd), static_cast<const bf16_t*>(ps1), T, d, d_e,

@@ -25,40 +25,9 @@ __device__ __forceinline__ int lane_prefix(unsigned long long bal, int lane) {
   return __popcll(bal & ((1ull << lane) - 1ull));
 }
 
-// R == 1: token t = tid keeps its logit in a register for all passes (T <= NT);
-// R == 0: every pass reads the logits again (any T).
-template <int R>
-struct Logits {
-  float v[R > 0 ? R : 1];
-  __device__ __forceinline__ void load(const float* lg, int T) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int t = static_cast<int>(threadIdx.x) + NT * r;
-      v[r] = t < T ? lg[t] : 0.f;
-    }
-  }
-  __device__ __forceinline__ float at(const float* lg, int r, int t) const {
-    if constexpr (R > 0) {
-      return v[r];
-    } else {
-      return lg[t];
-    }
-  }
-};
-
-// for (r = 0; NT r < T; ++r) f(r, t = tid + NT r), unrolled when the chunk count is static
-template <int R, class F>
-__device__ __forceinline__ void for_chunks(int T, F&& f) {
-  if constexpr (R > 0) {
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      if (NT * r < T) f(r, static_cast<int>(threadIdx.x) + NT * r);
-  } else {
-    for (int r = 0; NT * r < T; ++r) f(r, static_cast<int>(threadIdx.x) + NT * r);
-  }
-}
-
-template <int R>
+// HELD: at most NT tokens, thread t keeps token t's logit in a register for all passes; otherwise
+// every pass reads the logits again, NT of them at a time (any T).
+template <bool HELD>
 __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   __shared__ uint32_t hist[256];
   __shared__ int wcount[NW];
@@ -70,8 +39,9 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int T = a.T;
   const bool budget = a.mode == 1;
-  Logits<R> lg;
-  lg.load(a.logit, T);
+  const int chunks = HELD ? 1 : (T + NT - 1) / NT;
+  const float held = HELD && tid < T ? a.logit[tid] : 0.f;
+  auto logit = [&](int t) { return HELD ? held : a.logit[t]; };
 
   // adapter iff key < vstar, or key == vstar and t <= tstar
   uint32_t vstar = 0u;
@@ -85,13 +55,14 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
       for (int i = tid; i < 256; i += NT) hist[i] = 0u;
       __syncthreads();
       const uint32_t prefix = s_prefix;
-      for_chunks<R>(T, [&](int r, int t) {
+      for (int r = 0; r < chunks; ++r) {
+        const int t = tid + NT * r;
         if (t < T) {
-          const uint32_t key = order_key(lg.at(a.logit, r, t));
+          const uint32_t key = order_key(logit(t));
           if (shift == 24 || (key >> (shift + 8)) == (prefix >> (shift + 8)))
             atomicAdd(&hist[(key >> shift) & 255u], 1u);
         }
-      });
+      }
       __syncthreads();
       if (wave == 0) {
         // lane l owns bins [4l, 4l+4); inclusive scan of their sums across the wave
@@ -128,9 +99,9 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     const int k = s_k;
     if (tid == 0) s_tstar = -1;
     int run = 0;
-    for_chunks<R>(T, [&](int r, int t) {
-      if (run >= k) return;   // uniform: every thread holds the same run
-      const bool pred = t < T && order_key(lg.at(a.logit, r, t)) == vstar;
+    for (int r = 0; r < chunks && run < k; ++r) {   // uniform: every thread holds the same run
+      const int t = tid + NT * r;
+      const bool pred = t < T && order_key(logit(t)) == vstar;
       const unsigned long long bal = __ballot(pred);
       if (lane == 0) wcount[wave] = __popcll(bal);
       __syncthreads();
@@ -143,7 +114,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
       if (pred && run + wpre + lane_prefix(bal, lane) + 1 == k) s_tstar = t;
       run += tot;
       __syncthreads();
-    });
+    }
     __syncthreads();
     tstar = s_tstar;
   }
@@ -151,11 +122,12 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   // decision and compaction
   int nf = 0, na = 0;
   float lmin = __builtin_inff();
-  for_chunks<R>(T, [&](int r, int t) {
+  for (int r = 0; r < chunks; ++r) {
+    const int t = tid + NT * r;
     const bool valid = t < T;
     bool ffn = false;
     if (valid) {
-      const float l = lg.at(a.logit, r, t);
+      const float l = logit(t);
       if (budget) {
         const uint32_t key = order_key(l);
         const bool skip = a.n_skip > 0 && (key < vstar || (key == vstar && t <= tstar));
@@ -186,7 +158,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     nf += tot;
     na += nvalid - tot;
     __syncthreads();
-  });
+  }
 
   // smallest FFN logit
 #pragma unroll
@@ -415,7 +387,7 @@ __global__ __launch_bounds__(NT) void select_run_kernel(SelectArgs a) {
 hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
   // above 1024 tokens contiguous runs per thread; runs past 32 tokens would spill
   if (a.T <= NT)
-    select_kernel<1><<<1, NT, 0, s>>>(a);
+    select_kernel<true><<<1, NT, 0, s>>>(a);
   else if (a.T <= 4 * NT)
     select_run_kernel<4><<<1, NT, 0, s>>>(a);
   else if (a.T <= 8 * NT)
@@ -425,7 +397,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s) {
   else if (a.T <= 32 * NT)
     select_run_kernel<32><<<1, NT, 0, s>>>(a);
   else
-    select_kernel<0><<<1, NT, 0, s>>>(a);
+    select_kernel<false><<<1, NT, 0, s>>>(a);
   return hipGetLastError();
 }
 
