@@ -15,8 +15,8 @@ from tests.oracle_inputs import adapter_of, dims_of, ffn_of
 from tests.parity import row_rel_err
 
 # the Llama shapes scaled down to keep the oracle quick, at token counts whose FFN products take
-# the launch configurations the benchmark times: 256-row tiles at 8192 tokens (as the 8B stack's
-# ~20k FFN rows do) and the persistent 192-row gate/up kernel at 4096 tokens (as the 8B layer does)
+# the launch configurations the benchmark times: a gate/up product of 192-row tiles at 8192 and 4096
+# tokens (as the 8B layer's) and of 256-row tiles at 3760 tokens (as the 8B stack's ~20k FFN rows)
 CONTRAST = synth.Workload("contrast", "bf16", d=1024, d_ff=3584, d_r=64, L_R=32, d_m=128, T=8192,
                           mode="budget", budget=0.3882, layer_j=17, bias="spread", batch=4, seq=2048,
                           ffn_std=0.05, adapter_std=0.2)

@@ -9,6 +9,7 @@ import pytest
 from paper_2609_08189_amd import synth
 from tests.contrast import CONTRAST, mutant_errors, sample_rows
 from tests.parity import TOL, check_layer, oracle_layer
+from tests.phase_rule import phase_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -43,11 +44,19 @@ def _run(w, seed):
 
 @pytest.mark.parametrize("d_r", [32, 64, 96, 128])
 def test_contrast_stack_tiles(d_r):
-    """8192 tokens: the FFN products run 256-row tiles, as at the 8B stack's ~20k FFN rows."""
+    """8192 tokens (5012 FFN rows by 28 column tiles): three rounds of 192-row gate/up tiles."""
+    assert phase_rows(5012, 28) == 192
     _run(CONTRAST.replace(d_r=d_r), seed=d_r)
 
 
+def test_contrast_256_row_tiles():
+    """3760 tokens (2300 FFN rows by 28 column tiles): 256-row gate/up tiles, as at the 8B stack's ~20k FFN rows."""
+    assert phase_rows(2300, 28) == phase_rows(20047, 112) == 256
+    _run(CONTRAST.replace(T=3760, batch=1, seq=3760), seed=3)
+
+
 def test_contrast_layer_tiles_wide_adapter():
-    """4096 tokens: the persistent 192-row gate/up kernel, as at the 8B layer; adapter rank 256
+    """4096 tokens (2506 FFN rows): 192-row gate/up tiles, as at the 8B layer's 2995 rows; adapter rank 256
     on the matrix-core adapter path."""
+    assert phase_rows(2506, 28) == phase_rows(2995, 112) == 192
     _run(CONTRAST.replace(d_r=256, T=4096, batch=2), seed=7)

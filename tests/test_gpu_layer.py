@@ -6,6 +6,7 @@ import pytest
 
 from paper_2609_08189_amd import synth
 from tests.parity import check_layer
+from tests.phase_rule import phase_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -123,10 +124,10 @@ def test_llama31_8b_paper_operating_point_full_shape():
     torch.cuda.empty_cache()
 
 
-def test_persistent_gate_up_ragged():
-    """More FFN tiles than CUs (the persistent gate/up kernel: each tile's results leave during
-    the next tile) with a row count that is not a multiple of the tile height."""
+def test_gate_up_256_rows_ragged():
+    """1461 FFN rows by 40 column tiles: the gate/up product in one round of 256-row tiles, the last of them ragged."""
     w = BF16_SMALL.replace(d_ff=5120, T=2001, budget=0.27)
+    assert phase_rows(1461, 40) == 256
     _run(w, 3)
 
 
