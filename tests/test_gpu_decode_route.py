@@ -1,6 +1,7 @@
 """A routed decode step's folded launches (row pass with the router's product; decision and adapter down-projection in
 the gate/up launch; adapter up-projection with the down product's reduction) at the edges of their layouts, against
-the oracle: token counts around the 16-, 32- and 64-row blocks, every narrow adapter rank, all tokens on one branch."""
+the oracle: token counts around the 16-, 32- and 64-row blocks, every narrow adapter rank, one to four column blocks per
+gate/up workgroup, all tokens or all but one on one branch."""
 import numpy as np
 import pytest
 
@@ -35,14 +36,24 @@ def test_ranks_and_widths(d, d_ff, d_r):
     _layer(100, d, d_ff, d_r, tiled=False)
 
 
+@pytest.mark.parametrize("T,d_r,mode,tiled", [(100, 64, "budget", True), (256, 32, "threshold", False)])
+@pytest.mark.parametrize("d_ff,blocks", [(4096, 1), (8192, 2), (8320, 3), (12416, 4), (16384, 4)])
+def test_column_blocks(d_ff, blocks, T, d_r, mode, tiled):
+    """blocks: the most 16-column blocks of W_g and W_u that one of at most 256 workgroups takes (7B: 3, 8B: 4)."""
+    nb = d_ff // 16
+    assert -(-nb // min(256, nb)) == blocks
+    _layer(T, 256, d_ff, d_r, mode=mode, tiled=tiled)
+
+
 @pytest.mark.parametrize("T", [1, 70])
 @pytest.mark.parametrize("beta", [-50.0, 50.0])
 def test_threshold_one_branch(T, beta):
     _layer(T, mode="threshold", beta=beta)
 
 
-@pytest.mark.parametrize("budget", [0.0, 1.0])
+@pytest.mark.parametrize("budget", [0.0, 1.0 / 70, 69.0 / 70, 1.0])
 def test_budget_one_branch(budget):
+    """No, one, all but one and all of 70 tokens on the adapter (all: without a FFN row no launch is folded)."""
     _layer(70, budget=budget)
 
 
