@@ -517,17 +517,21 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
 //   * A k-tile is four products of a half by a half.  Each half is read from LDS into registers
 //     one product ahead, so a half of a stage is free again half a k-tile after its k-tile began,
 //     and its loads for k-tile kt + 2 are issued then: they have one to one and a half k-tiles to
-//     land (half a k-tile to one with whole stages), and the waits leave 8 of them in flight.  Two
-//     barriers a k-tile.
+//     land (half a k-tile to one with whole stages), and the waits leave the loads of one k-tile in
+//     flight (8, 7 and 6 a wave at 256, 192 and 128 rows).  Two barriers a k-tile.
 //   * The loads write the LDS that the fragment reads read, so the compiler keeps their order:
 //     they are written in the order they shall issue in, one between two MFMAs.  Issued as a burst
 //     ahead of the reads (the order of the source before), the same loop lost all of its gain.
 //   * The 16 x 16 x 32 instruction: at the same nominal rate as 32 x 32 x 16 it sustains a higher
 //     clock on random data under the board's power limit.
-// What bounds it is that limit: on zero operands the Llama-3.1-8B gate/up product (4096 rows) runs
-// at 1.84 PFLOP/s (the loop with whole stages: 1.57), on random ones at 1.44 (1.38); 20047 rows
-// 3510 -> 3390 us, its down product 1845 -> 1760 us, 2995 rows on 192-row tiles 550 -> 525 and
-// 265 -> 257 us.  Four waves of 128 x 128 (a third fewer LDS reads) reached 1.39.
+// What bounds it: the matrix cores are busy for 75 % of its cycles (counters of the 8B stack's
+// gate/up and down; the loop with whole stages 67 %), at the clock that the power limit leaves on
+// random operands, 1.7-1.8 GHz.  A register-only loop of the same instruction has 95 % at 1.87 GHz (on
+// zeros 2.32).  The other quarter is waiting, at the two barriers and for loads and fragments (25 %
+// of the waves' time); the fragment reads take 29 % of the LDS's cycles, bank conflicts 0.3 %.  4096 rows of the
+// Llama-3.1-8B gate/up product: 1.84 PFLOP/s on zeros (whole stages 1.57), 1.44 on random operands
+// (1.38); 20047 rows 3510 -> 3390 us, its down product 1845 -> 1760 us, 2995 rows on 192-row tiles
+// 550 -> 525 and 265 -> 257 us.  Four waves of 128 x 128 (a third fewer LDS reads) reached 1.39.
 // Epilogues: the gate/up products finish in registers and stage bf16; the others stage 16-row
 // blocks in fp32 and take 8-column pieces (emit8) or the whole block (block).
 // A grid with gridDim.y = S > 1 splits K as mfma_gemm does.
@@ -870,11 +874,13 @@ hipError_t run_phase(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_cou
   const int n_tiles = N_out / Phase<256, DUAL>::OUT_N;
   if (M_max <= 0 || n_tiles <= 0) return hipSuccess;
   const auto blocks = [&](int BM) { return ((M_max + BM - 1) / BM * n_tiles + 7) / 8 * 8; };
-  if (!exact && m_count) {
-    // enough for any choice at any count up to M_max
-    const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 4 * kCUs)});
-    phase_gemm_any<DUAL, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
-    return hipGetLastError();
+  if constexpr (!TwoTerm<Epi>::value) {   // the products of two terms know their rows
+    if (!exact && m_count) {
+      // enough for any choice at any count up to M_max
+      const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 4 * kCUs)});
+      phase_gemm_any<DUAL, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
+      return hipGetLastError();
+    }
   }
   switch (phase_rows(M_max, n_tiles)) {
     case 256: phase_gemm<Phase<256, DUAL>, Epi><<<blocks(256), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
@@ -2155,7 +2161,7 @@ int down_split_space(int n, int d, int d_ff) {
   return split_ways((n + 191) / 192 * (d / 128), d_ff / BK, kMaxSplitDown);
 }
 // ... and that its 128 x 256 tiles take: the most that fit one round of workgroups, of at least two
-// k-tiles.  8B shape, 390 of at most 640 rows: 85 us in two slices of 192 x 128 tiles, 57 in three.
+// k-tiles.  8B shape, 390 of at most 640 rows: 85 us in two slices of 192 x 128 tiles, 65 in three.
 int down_split(int n, int d, int d_ff) {
   const int S = split_ways((n + 127) / 128 * (d / 256), d_ff / BK / 2, kMaxSplitDown);
   const size_t space = ffn_part_floats(1, d, d_ff, n) / (static_cast<size_t>(n) * d);
