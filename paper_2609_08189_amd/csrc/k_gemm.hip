@@ -1007,9 +1007,9 @@ hipError_t run_tile(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_coun
 struct RouteArgs {
   SelectArgs sel;
   int na;                  // adapter workgroups (a multiple of 8): row tiles of 32 tokens x K-slices
-  int slices, d_r;
+  int slices, groups, d_r; // slices divides groups = adapter_groups(d)
   const bf16_t *u, *w1;
-  float* part;             // [slices][T][d_r]
+  float* part;             // [groups][T][d_r]
 };
 
 struct RouteFinish {
@@ -1114,58 +1114,63 @@ __device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* l
   return nf;
 }
 
-// z of 32 tokens against all d_r = 32 TN columns over one K-slice, by the eight waves of a
-// workgroup, each over an eighth of the slice; the partial tiles are added in wave order
+// z of 32 tokens against all d_r = 32 TN columns over one K-slice, by the eight waves of a workgroup.
+// The sums have the order of adapter_down_bf16, so that a token's z is the same bits at every call
+// size: the slice holds groups / slices of that kernel's K groups, each the sum of four pieces in
+// turn, a piece a wave; eight pieces (two groups) a pass.
 template <int TN>
 __device__ __forceinline__ void route_adapter(const RouteArgs& a, int K, int wg, unsigned char* smem) {
   constexpr int SB = 4, R = 32 * TN, RPITCH = R + 1;
   float* red = reinterpret_cast<float*>(smem);
   static_assert(8 * 32 * RPITCH * 4 <= 160 * 1024, "partials fit in LDS");
   const int T = a.sel.T;
-  const int tile = wg / a.slices, g = wg % a.slices, m0 = 32 * tile;
+  const int tile = wg / a.slices, m0 = 32 * tile;
   if (m0 >= T) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int kw = K / a.slices / 8, kbeg = g * (K / a.slices) + wave * kw;
+  const int gpw = a.groups / a.slices, g0 = wg % a.slices * gpw;
+  const int kw = K / (4 * a.groups);   // a multiple of 16 SB (adapter_groups)
   const bf16_t* arow = a.u + static_cast<size_t>(min(m0 + (lane & 31), T - 1)) * K + 8 * (lane >> 5);
   const bf16_t* brow = a.w1 + static_cast<size_t>(lane & 31) * K + 8 * (lane >> 5);
-  f32x16 acc[TN];
-#pragma unroll
-  for (int b = 0; b < TN; ++b)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-  for (int k = kbeg; k < kbeg + kw; k += 16 * SB) {
-    bf16x8 fa[SB], fb[SB][TN];
-#pragma unroll
-    for (int st = 0; st < SB; ++st) {
-      const int kk = min(k + 16 * st, kbeg + kw - 16);   // past the slice: loaded again, not used
-      fa[st] = *reinterpret_cast<const bf16x8*>(arow + kk);
+  for (int q = 0; q < gpw; q += 2) {   // the pass's first group
+    const int ng = min(2, gpw - q);
+    if (wave < 4 * ng) {
+      const int kbeg = (4 * (g0 + q) + wave) * kw;
+      f32x16 acc[TN];
 #pragma unroll
       for (int b = 0; b < TN; ++b)
-        fb[st][b] = *reinterpret_cast<const bf16x8*>(brow + static_cast<size_t>(32 * b) * K + kk);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+      for (int k = kbeg; k < kbeg + kw; k += 16 * SB) {
+        bf16x8 fa[SB], fb[SB][TN];
+#pragma unroll
+        for (int st = 0; st < SB; ++st) {
+          fa[st] = *reinterpret_cast<const bf16x8*>(arow + k + 16 * st);
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+            fb[st][b] = *reinterpret_cast<const bf16x8*>(brow + static_cast<size_t>(32 * b) * K + k + 16 * st);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int st = 0; st < SB; ++st)
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[st], fb[st][b], acc[b], 0, 0, 0);
+      }
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          red[(wave * 32 + out_row32(r, lane)) * RPITCH + b * 32 + (lane & 31)] = acc[b][r];
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int st = 0; st < SB; ++st)
-      if (k + 16 * st < kbeg + kw)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[st], fb[st][b], acc[b], 0, 0, 0);
-  }
-#pragma unroll
-  for (int b = 0; b < TN; ++b)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      red[(wave * 32 + i) * RPITCH + b * 32 + (lane & 31)] = acc[b][r];
+    __syncthreads();
+    for (int e = threadIdx.x; e < ng * 32 * R; e += 512) {
+      const int g = e / (32 * R), i = e / R % 32, n = e % R;
+      if (m0 + i >= T) continue;
+      const float* p = red + (4 * g * 32 + i) * RPITCH + n;
+      a.part[(static_cast<size_t>(g0 + q + g) * T + m0 + i) * R + n] =
+          p[0] + p[32 * RPITCH] + p[64 * RPITCH] + p[96 * RPITCH];
     }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 32 * R; e += 512) {
-    const int i = e / R, n = e % R;
-    if (m0 + i >= T) continue;
-    float v = 0.f;
-#pragma unroll
-    for (int w = 0; w < 8; ++w) v += red[(w * 32 + i) * RPITCH + n];
-    a.part[(static_cast<size_t>(g) * T + m0 + i) * R + n] = v;
+    __syncthreads();   // the next pass overwrites the partial tiles
   }
 }
 
@@ -2670,14 +2675,15 @@ void decode_finish_launch(int G, int blocks, const RouteFinish& f, hipStream_t s
   }
 }
 
-// K-slices of the adapter's down-projection beside the gate/up product: the most that leave the
-// product's workgroups a CU each, in whole 16-deep steps for eight waves
+// Workgroups per 32 tokens of the adapter's down-projection beside the gate/up product: the most that
+// leave the product's workgroups a CU each and have two of the adapter_groups(d) K groups (eight
+// pieces, one a wave)
 int route_slices(int T, int d, int d_ff) {
   const int NB = skinny_gateup_blocks(d_ff), spare = kCUs - (d_ff / 16 + NB - 1) / NB;
   const int tiles = (T + 31) / 32;
-  int G = adapter_groups(d);
-  while (G > 1 && (tiles * G > spare || d % (128 * G) != 0)) G >>= 1;
-  return G;
+  int S = std::max(1, adapter_groups(d) / 2);
+  while (S > 1 && tiles * S > spare) S >>= 1;
+  return S;
 }
 }  // namespace
 
@@ -2686,6 +2692,7 @@ hipError_t launch_route_gateup(const DecodeRoute& r, hipStream_t s) {
   ra.sel = r.sel;
   if (r.n_ad_max > 0) {
     ra.slices = route_slices(r.sel.T, r.d, r.d_ff);
+    ra.groups = adapter_groups(r.d);
     ra.na = ((r.sel.T + 31) / 32 * ra.slices + 7) / 8 * 8;
     ra.d_r = r.d_r;
     ra.u = static_cast<const bf16_t*>(r.u);
@@ -2723,7 +2730,7 @@ hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s) {
   f.stride = static_cast<size_t>(r.n_ffn_max) * r.d;
   const size_t n8 = static_cast<size_t>(r.n_ffn_max) * (r.d / 8);
   const int blocks = f.up_blocks + static_cast<int>((n8 + 255) / 256);
-  const int G = route_slices(r.sel.T, r.d, r.d_ff);
+  const int G = adapter_groups(r.d);
   switch (r.d_r) {
     case 32: decode_finish_launch<32>(G, blocks, f, s); break;
     case 64: decode_finish_launch<64>(G, blocks, f, s); break;

@@ -74,3 +74,34 @@ def test_row_pass_is_the_prefills(T):
         torch.cuda.synchronize()
         u.append(dp.ws[:T * d * 2].view(torch.int16).clone())
     assert torch.equal(*u)
+
+
+@pytest.mark.parametrize("T", [20, 64, 256])
+@pytest.mark.parametrize("d,d_ff,d_r", [(4096, 128, 128), (2048, 8320, 64), (1280, 384, 32)])
+def test_adapter_sums_are_the_prefills(d, d_ff, d_r, T):
+    """A token's adapter sums u W_1^T are formed in the same order in a decode step, where they share the gate/up launch,
+    as in a call of 300 tokens with launches of their own: each row of u and W_1 is [x, x], [w, -w], so a sum is only the
+    rounding that its order leaves, scaled up by W_2; the gates are exactly 0 or 1."""
+    import torch
+    from paper_2609_08189_amd.device import DeviceProblem
+    h = []
+    for n in (T, 300):
+        w = synth.Workload("adapter_sums", "bf16", d=d, d_ff=d_ff, d_r=d_r, L_R=8, d_m=32, T=n, mode="threshold",
+                           budget=0.3, bias="spread")
+        prob = synth.make_problem(w, seed=5, layer_j=3)
+        prob.beta = np.where(np.arange(n) % 3 > 0, -50.0, 50.0).astype(np.float32)
+        dp = DeviceProblem(prob)
+        rows = torch.randn(300, d // 2, generator=torch.Generator().manual_seed(9)).to(torch.bfloat16).cuda()
+        dp.hbar.copy_(torch.cat([rows, rows], 1)[:n])
+        half = dp.ffn[0]["norm_w"][:d // 2].clone()
+        dp.ffn[0]["norm_w"][d // 2:] = half
+        w1, w2 = dp.adapter[0]["w1"], dp.adapter[0]["w2"]
+        w1[:, d // 2:] = -w1[:, :d // 2]
+        w2.mul_(2.0 ** 30)
+        dp.run_layer(3)
+        torch.cuda.synchronize()
+        ad = torch.arange(T, device="cuda") % 3 > 0
+        moved = dp.h_out[:T][ad] != dp.hbar[:T][ad]
+        assert moved.any()
+        h.append(dp.h_out[:T][ad].view(torch.int16).clone())
+    assert torch.equal(*h)
