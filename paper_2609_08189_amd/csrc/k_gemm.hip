@@ -1006,14 +1006,14 @@ hipError_t run_tile(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_coun
 // ---------------------------------------------------------------------------
 struct RouteArgs {
   SelectArgs sel;
-  int na;                  // adapter workgroups (a multiple of 8): row tiles of 32 tokens x K-slices
-  int slices, groups, d_r; // slices divides groups = adapter_groups(d)
+  int na;                  // adapter workgroups (a multiple of 8): row tiles of 32 tokens x blocks of 32 tn columns
+  int tn, groups, d_r;     // groups: adapter_groups(d)
   const bf16_t *u, *w1;
-  float* part;             // [groups][T][d_r]
+  float* z;                // [T][d_r]
 };
 
 struct RouteFinish {
-  const float* part_ad;
+  const float* z;
   const int *idx_ad, *idx_ffn, *counts;
   const bf16_t *w2, *hbar;
   const float* gate;
@@ -1114,27 +1114,30 @@ __device__ __forceinline__ int select_wave(const SelectArgs& a, int lane, int* l
   return nf;
 }
 
-// z of 32 tokens against all d_r = 32 TN columns over one K-slice, by the eight waves of a workgroup.
-// The sums have the order of adapter_down_bf16, so that a token's z is the same bits at every call
-// size: the slice holds groups / slices of that kernel's K groups, each the sum of four pieces in
-// turn, a piece a wave; eight pieces (two groups) a pass.
+// z of 32 tokens against 32 TN of the d_r columns, by the eight waves of a workgroup.  The sums have
+// the order of adapter_down_bf16 and adapter_up_tile, so that a token's z is the same bits at every
+// call size: adapter_groups(d) K groups, each the sum of four pieces in turn, a piece a wave; eight
+// pieces (two groups) a pass.  K groups on workgroups of their own left decode_finish eight partials
+// to read: 8.9 for 8.1 us at 256 tokens of d = 4096.
 template <int TN>
 __device__ __forceinline__ void route_adapter(const RouteArgs& a, int K, int wg, unsigned char* smem) {
-  constexpr int SB = 4, R = 32 * TN, RPITCH = R + 1;
+  constexpr int SB = 4, R = 32 * TN, RPITCH = R + 1, Q = 32 * R / 512;
   float* red = reinterpret_cast<float*>(smem);
   static_assert(8 * 32 * RPITCH * 4 <= 160 * 1024, "partials fit in LDS");
-  const int T = a.sel.T;
-  const int tile = wg / a.slices, m0 = 32 * tile;
+  const int T = a.sel.T, ncb = a.d_r / R;
+  const int m0 = 32 * (wg / ncb), n0 = R * (wg % ncb);
   if (m0 >= T) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gpw = a.groups / a.slices, g0 = wg % a.slices * gpw;
   const int kw = K / (4 * a.groups);   // a multiple of 16 SB (adapter_groups)
   const bf16_t* arow = a.u + static_cast<size_t>(min(m0 + (lane & 31), T - 1)) * K + 8 * (lane >> 5);
-  const bf16_t* brow = a.w1 + static_cast<size_t>(lane & 31) * K + 8 * (lane >> 5);
-  for (int q = 0; q < gpw; q += 2) {   // the pass's first group
-    const int ng = min(2, gpw - q);
+  const bf16_t* brow = a.w1 + static_cast<size_t>(n0 + (lane & 31)) * K + 8 * (lane >> 5);
+  float z[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) z[q] = 0.f;
+  for (int g = 0; g < a.groups; g += 2) {   // the pass's first group
+    const int ng = min(2, a.groups - g);
     if (wave < 4 * ng) {
-      const int kbeg = (4 * (g0 + q) + wave) * kw;
+      const int kbeg = (4 * g + wave) * kw;
       f32x16 acc[TN];
 #pragma unroll
       for (int b = 0; b < TN; ++b)
@@ -1163,14 +1166,19 @@ __device__ __forceinline__ void route_adapter(const RouteArgs& a, int K, int wg,
           red[(wave * 32 + out_row32(r, lane)) * RPITCH + b * 32 + (lane & 31)] = acc[b][r];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < ng * 32 * R; e += 512) {
-      const int g = e / (32 * R), i = e / R % 32, n = e % R;
-      if (m0 + i >= T) continue;
-      const float* p = red + (4 * g * 32 + i) * RPITCH + n;
-      a.part[(static_cast<size_t>(g0 + q + g) * T + m0 + i) * R + n] =
-          p[0] + p[32 * RPITCH] + p[64 * RPITCH] + p[96 * RPITCH];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int e = threadIdx.x + 512 * q;
+      const float* p = red + (e / R) * RPITCH + e % R;
+      for (int x = 0; x < ng; ++x, p += 4 * 32 * RPITCH)
+        z[q] += p[0] + p[32 * RPITCH] + p[64 * RPITCH] + p[96 * RPITCH];
     }
     __syncthreads();   // the next pass overwrites the partial tiles
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int e = threadIdx.x + 512 * q, m = m0 + e / R;
+    if (m < T) a.z[static_cast<size_t>(m) * a.d_r + n0 + e % R] = z[q];
   }
 }
 
@@ -1244,10 +1252,10 @@ __global__ __launch_bounds__(512) void skinny_gemm(ARows<bf16_t> A, const bf16_t
   __shared__ __attribute__((aligned(1024))) unsigned char smem[kLds];
   if constexpr (ROUTE) {
     if (static_cast<int>(blockIdx.x) < route.na) {
-      switch (route.d_r) {
-        case 32: route_adapter<1>(route, K, blockIdx.x, smem); break;
-        case 64: route_adapter<2>(route, K, blockIdx.x, smem); break;
-        case 96: route_adapter<3>(route, K, blockIdx.x, smem); break;
+      switch (route.tn) {
+        case 1: route_adapter<1>(route, K, blockIdx.x, smem); break;
+        case 2: route_adapter<2>(route, K, blockIdx.x, smem); break;
+        case 3: route_adapter<3>(route, K, blockIdx.x, smem); break;
         default: route_adapter<4>(route, K, blockIdx.x, smem); break;
       }
       return;
@@ -1856,7 +1864,7 @@ __global__ __launch_bounds__(256) void adapter_down_bf16(const bf16_t* __restric
 //   hid = SiLU(sum_g part[g]) for the 32 rows, rounded to bf16 (the MFMA A operand), in LDS;
 //   each wave computes 64 columns; results are staged in LDS and every thread then writes
 //   8-column pieces h_out[t] = hbar[t] + (1 - g_t) acc with hbar fetched at the start.
-// BY_TOKEN: the partials are held by token (row idx[m]) instead of by list position.
+// BY_TOKEN: the G partials are held by token (row idx[m]) instead of by list position.
 template <int KR, int G, bool BY_TOKEN>
 __device__ __forceinline__ void adapter_up_tile(const float* __restrict__ part, const int* __restrict__ idx,
                                                 const int* __restrict__ m_count, const bf16_t* __restrict__ w2,
@@ -2102,10 +2110,9 @@ hipError_t skinny_gateup_nb_rb(const GateUpCall& c, hipStream_t s) {
   const bf16_t *b0 = c.tiled ? c.tiled : c.wg, *b1 = c.tiled ? nullptr : c.wu;
   const int ldb = c.tiled ? 0 : c.d, tiled = c.tiled ? nb : 0;
   if (c.route) {
-    // as few workgroups as keep the most blocks of one, at least those the adapter leaves free
-    const int gmin = (nb + NB - 1) / NB;
-    const int G = std::min(nb, std::max(gmin, kCUs - c.route->na) / 8 * 8 >= gmin
-                                   ? std::max(gmin, kCUs - c.route->na) / 8 * 8 : gmin);
+    // as few workgroups as keep the most blocks of one, in whole eights: each streams the activations
+    // (256 tokens, with all the CUs that the adapter leaves: 8B layer 140 us, so 136)
+    const int G = std::min(nb, ((nb + NB - 1) / NB + 7) / 8 * 8);
     skinny_gemm<C, true><<<c.route->na + G, 512, 0, s>>>(c.A, b0, b1, ldb, tiled, c.act, c.d_ff, 0, nullptr, c.n_max,
                                                          c.d, nb, G, 1, *c.route);
     return hipGetLastError();
@@ -2249,14 +2256,14 @@ __global__ __launch_bounds__(256) void scatter_reduce(const float* __restrict__ 
 }
 
 // The last launch of a routed decode step: the first up_blocks workgroups are the adapter's
-// up-projection (32 rows x 256 columns each, partials by token), the others scatter_reduce.  The
+// up-projection (32 rows x 256 columns each, z by token), the others scatter_reduce.  The
 // two write disjoint rows of h_out.
-template <int KR, int G>
+template <int KR>
 __global__ __launch_bounds__(256) void decode_finish(RouteFinish f) {
   const int b = static_cast<int>(blockIdx.x);
   if (b < f.up_blocks) {
     const int nc = f.d / 256;
-    adapter_up_tile<KR, G, true>(f.part_ad, f.idx_ad, f.counts + 1, f.w2, f.hbar, f.gate, f.out, f.T, f.d,
+    adapter_up_tile<KR, 1, true>(f.z, f.idx_ad, f.counts + 1, f.w2, f.hbar, f.gate, f.out, f.T, f.d,
                                  b / nc * 32, b % nc * 256);
   } else {
     scatter_reduce_block(b - f.up_blocks, f.part, f.S, f.stride, f.counts, f.n_ffn_max, f.idx_ffn, f.hbar, f.gate,
@@ -2665,25 +2672,14 @@ hipError_t launch_f32_route_out(const DecodeRoute& r, hipStream_t s) {
 }
 
 namespace {
-template <int KR>
-void decode_finish_launch(int G, int blocks, const RouteFinish& f, hipStream_t s) {
-  switch (G) {
-    case 1: decode_finish<KR, 1><<<blocks, 256, 0, s>>>(f); break;
-    case 2: decode_finish<KR, 2><<<blocks, 256, 0, s>>>(f); break;
-    case 4: decode_finish<KR, 4><<<blocks, 256, 0, s>>>(f); break;
-    default: decode_finish<KR, 8><<<blocks, 256, 0, s>>>(f); break;
-  }
-}
-
-// Workgroups per 32 tokens of the adapter's down-projection beside the gate/up product: the most that
-// leave the product's workgroups a CU each and have two of the adapter_groups(d) K groups (eight
-// pieces, one a wave)
-int route_slices(int T, int d, int d_ff) {
+// Width, in 32-column blocks, of the adapter's workgroups beside the gate/up product: the narrowest
+// that leaves the product's workgroups a CU each
+int route_width(int T, int d_ff, int d_r) {
   const int NB = skinny_gateup_blocks(d_ff), spare = kCUs - (d_ff / 16 + NB - 1) / NB;
-  const int tiles = (T + 31) / 32;
-  int S = std::max(1, adapter_groups(d) / 2);
-  while (S > 1 && tiles * S > spare) S >>= 1;
-  return S;
+  const int tiles = (T + 31) / 32, all = d_r / 32;
+  int tn = 1;
+  while (tn < all && (all % tn != 0 || tiles * (all / tn) > spare)) ++tn;
+  return tn;
 }
 }  // namespace
 
@@ -2691,13 +2687,13 @@ hipError_t launch_route_gateup(const DecodeRoute& r, hipStream_t s) {
   RouteArgs ra{};
   ra.sel = r.sel;
   if (r.n_ad_max > 0) {
-    ra.slices = route_slices(r.sel.T, r.d, r.d_ff);
+    ra.tn = route_width(r.sel.T, r.d_ff, r.d_r);
     ra.groups = adapter_groups(r.d);
-    ra.na = ((r.sel.T + 31) / 32 * ra.slices + 7) / 8 * 8;
+    ra.na = ((r.sel.T + 31) / 32 * (r.d_r / 32 / ra.tn) + 7) / 8 * 8;
     ra.d_r = r.d_r;
     ra.u = static_cast<const bf16_t*>(r.u);
     ra.w1 = static_cast<const bf16_t*>(r.w1);
-    ra.part = r.part_ad;
+    ra.z = r.part_ad;
   }
   return skinny_gateup({ARows<bf16_t>{static_cast<const bf16_t*>(r.u), nullptr, r.d}, static_cast<const bf16_t*>(r.w_gate),
                         static_cast<const bf16_t*>(r.w_up), static_cast<const bf16_t*>(r.w_gate_up_tiled),
@@ -2713,7 +2709,7 @@ hipError_t launch_route_down(const DecodeRoute& r, hipStream_t s) {
 
 hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s) {
   RouteFinish f{};
-  f.part_ad = r.part_ad;
+  f.z = r.part_ad;
   f.idx_ad = r.sel.idx_ad;
   f.idx_ffn = r.sel.idx_ffn;
   f.counts = r.sel.counts;
@@ -2730,12 +2726,11 @@ hipError_t launch_route_finish(const DecodeRoute& r, hipStream_t s) {
   f.stride = static_cast<size_t>(r.n_ffn_max) * r.d;
   const size_t n8 = static_cast<size_t>(r.n_ffn_max) * (r.d / 8);
   const int blocks = f.up_blocks + static_cast<int>((n8 + 255) / 256);
-  const int G = adapter_groups(r.d);
   switch (r.d_r) {
-    case 32: decode_finish_launch<32>(G, blocks, f, s); break;
-    case 64: decode_finish_launch<64>(G, blocks, f, s); break;
-    case 96: decode_finish_launch<96>(G, blocks, f, s); break;
-    case 128: decode_finish_launch<128>(G, blocks, f, s); break;
+    case 32: decode_finish<32><<<blocks, 256, 0, s>>>(f); break;
+    case 64: decode_finish<64><<<blocks, 256, 0, s>>>(f); break;
+    case 96: decode_finish<96><<<blocks, 256, 0, s>>>(f); break;
+    case 128: decode_finish<128><<<blocks, 256, 0, s>>>(f); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
