@@ -838,17 +838,24 @@ __global__ __launch_bounds__(512, 2) void phase_gemm(ARows<bf16_t> A, BRows<bf16
 // rows: 54-57, 78 and 97 us for 128-, 192- and 256-row tiles at K = 4096; 187, 258 and 345 at
 // 14336).  The smaller tiles move more bytes per product and only pay while their finer rounds
 // leave fewer CUs idle, so beyond four (128) and eight (192) rounds they are not considered.
+// SPILL: the epilogues of the two backwards, whose 256-row tiles spill 96 and 36 registers and so are
+// hardly faster a row than 192-row ones.  With the weights above against these, whole calls at the 8B shape:
+// block backward 1135 -> 1085 us at 2800 tokens, 5768 -> 5511 at 16000, router backward 1010 -> 962 at
+// 8192; 256 rows stay where they make a single round (block backward of 700 tokens: 626, on 128 rows 636).
+template <bool SPILL>
 __host__ __device__ inline int phase_rows(int M, int n_tiles) {
   auto tiles = [&](int BM) { return (M + BM - 1) / BM * n_tiles; };
   auto cost = [&](int BM, int w) { return (tiles(BM) + kCUs - 1) / kCUs * w; };
-  int best = 256, c = cost(256, 125);
-  if (tiles(192) <= 8 * kCUs && cost(192, 100) < c) {
+  int best = 256, c = cost(256, SPILL ? 152 : 125);
+  if ((SPILL || tiles(192) <= 8 * kCUs) && cost(192, 100) < c) {
     best = 192;
     c = cost(192, 100);
   }
-  if (tiles(128) <= 4 * kCUs && cost(128, 75) < c) best = 128;
+  if (tiles(128) <= 4 * kCUs && cost(128, SPILL ? 80 : 75) < c) best = 128;
   return best;
 }
+template <class Epi>
+constexpr bool kSpill = DualHook<Epi>::value || TwoTerm<Epi>::value;
 
 // Threshold routing: the host only knows an upper bound of the row count, so the workgroups choose
 // the tile height themselves from the count on the device.
@@ -858,7 +865,7 @@ __global__ __launch_bounds__(512, 2) void phase_gemm_any(ARows<bf16_t> A, BRows<
                                                          int n_tiles) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * Phase<256, DUAL>::STAGE];
   const int M = min(*m_count, M_max);
-  const int bm = phase_rows(M, n_tiles);
+  const int bm = phase_rows<kSpill<Epi>>(M, n_tiles);
   if (bm == 256)
     phase_tile<Phase<256, DUAL>>(A, B, epi, M, M_max, K, n_tiles, smem);
   else if (bm == 192)
@@ -877,12 +884,13 @@ hipError_t run_phase(ARows<bf16_t> A, BRows<bf16_t> B, Epi epi, const int* m_cou
   if constexpr (!TwoTerm<Epi>::value) {   // the products of two terms know their rows
     if (!exact && m_count) {
       // enough for any choice at any count up to M_max
-      const int grid = std::max({blocks(256), std::min(blocks(192), 8 * kCUs), std::min(blocks(128), 4 * kCUs)});
+      const int grid = std::max({blocks(256), kSpill<Epi> ? blocks(192) : std::min(blocks(192), 8 * kCUs),
+                                 std::min(blocks(128), 4 * kCUs)});
       phase_gemm_any<DUAL, Epi><<<grid, 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles);
       return hipGetLastError();
     }
   }
-  switch (phase_rows(M_max, n_tiles)) {
+  switch (phase_rows<kSpill<Epi>>(M_max, n_tiles)) {
     case 256: phase_gemm<Phase<256, DUAL>, Epi><<<blocks(256), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
     case 192: phase_gemm<Phase<192, DUAL>, Epi><<<blocks(192), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;
     default: phase_gemm<Phase<128, DUAL>, Epi><<<blocks(128), 512, 0, s>>>(A, B, epi, m_count, M_max, K, n_tiles); break;

@@ -44,6 +44,9 @@ def test_down_product(T, rows, mode):
 
 
 @pytest.mark.parametrize("known", [True, False])
-@pytest.mark.parametrize("T", [1365, 2203, 3001])
-def test_block_backward(T, known):
-    _run_small(BF16.replace(d=256, d_ff=2816, d_r=32, T=T, budget=0.01), T, budget_mode=known)
+@pytest.mark.parametrize("T,d_ff,rows", [(1365, 2816, 128), (2203, 2816, 256), (3001, 2816, 192), (3300, 16384, 192)])
+def test_block_backward(T, d_ff, rows, known):
+    """rows: the tile height of the gate/up recompute (3300: more than eight rounds of 192-row tiles)."""
+    w = BF16.replace(d=256, d_ff=d_ff, d_r=32, T=T, budget=0.01)
+    assert phase_rows(T - int(w.budget * T + 0.5), d_ff // 128, spill=True) == rows
+    _run_small(w, T, budget_mode=known)

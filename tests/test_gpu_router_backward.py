@@ -12,6 +12,7 @@ import pytest
 from oracle import hero_oracle as O
 from paper_2609_08189_amd import synth
 from tests.oracle_inputs import adapter_of, dims_of, ffn_of, router_of, state_of
+from tests.phase_rule import phase_rows
 
 TOL = 1e-4
 
@@ -123,6 +124,13 @@ def test_router_backward_one_token():
 def test_router_backward_1500_tokens(c_from_forward):
     """94 batches of 16 tokens, the last one ragged (12 tokens)."""
     _run(BF16.replace(T=1500), 3, seed=61, c_from_forward=c_from_forward)
+
+
+@pytest.mark.parametrize("T,rows", [(2177, 128), (4501, 192)])
+def test_router_backward_tile_heights(T, rows):
+    """rows: the tile height of the product into dL/dhbar_j, whose epilogue adds the row's own terms (256: the layer below)."""
+    assert phase_rows(T, 2048 // 256, spill=True) == rows and phase_rows(4096, 4096 // 256, spill=True) == 256
+    _run(BF16.replace(d=2048, T=T), 3, seed=71)
 
 
 def test_router_backward_llama31_8b_layer_full_shape():
