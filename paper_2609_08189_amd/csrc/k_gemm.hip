@@ -526,8 +526,8 @@ __global__ __launch_bounds__(C::NT) void mfma_gemm(ARows<bf16_t> A, BRows<bf16_t
 //     clock on random data under the board's power limit.
 // What bounds it: the matrix cores are busy for 75 % of its cycles (counters of the 8B stack's
 // gate/up and down; the loop with whole stages 67 %), at the clock that the power limit leaves on
-// random operands, 1.7-1.8 GHz.  A register-only loop of the same instruction has 95 % at 1.87 GHz (on
-// zeros 2.32).  The other quarter is waiting, at the two barriers and for loads and fragments (25 %
+// random operands, 1.7-1.8 GHz.  A register-only loop of the same instruction has 91-94 % at 1.87 GHz
+// (on zeros 96 % at 2.32).  The other quarter is waiting, at the two barriers and for loads and fragments (25 %
 // of the waves' time); the fragment reads take 29 % of the LDS's cycles, bank conflicts 0.3 %.  4096 rows of the
 // Llama-3.1-8B gate/up product: 1.84 PFLOP/s on zeros (whole stages 1.57), 1.44 on random operands
 // (1.38); 20047 rows 3510 -> 3390 us, its down product 1845 -> 1760 us, 2995 rows on 192-row tiles
